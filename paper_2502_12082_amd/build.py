@@ -2,8 +2,8 @@
 
     python paper_2502_12082_amd/build.py        # from the repository root
 
-Every .hip file under csrc/ is compiled with hipcc into _build/, in parallel,
-and linked into paper_2502_12082_amd/libentmax_attn.so next to this file.
+Every .hip file under csrc/ is compiled with hipcc into _build/, in parallel
+(the solver in parts), and linked into paper_2502_12082_amd/libentmax_attn.so next to this file.
 """
 from __future__ import annotations
 
@@ -30,15 +30,28 @@ CFLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", os.path.join(ROOT, "include"),
 ]
-# Per-file additions (none: every file builds with the default backend
-# options; the solver measured the same or faster without a non-default
-# register-form option that an earlier build used).
-FILE_FLAGS = {}
+# Files compiled in several parts, in parallel: (macro, number of parts).
+PARTS = {"ea_tau.hip": ("EA_TAU_PART", 5)}
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = [HIPCC] + CFLAGS + FILE_FLAGS.get(os.path.basename(src), []) + ["-c", src, "-o", obj]
+def _units():
+    """(source, object, extra flags) of every translation unit, the files with
+    several parts (the longest to compile) first."""
+    srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")),
+                  key=lambda s: (os.path.basename(s) not in PARTS, s))
+    for src in srcs:
+        name = os.path.basename(src)
+        macro, parts = PARTS.get(name, (None, 1))
+        for i in range(parts):
+            if macro:
+                yield src, os.path.join(BUILD, "%s.%d.o" % (name, i)), ["-D%s=%d" % (macro, i)]
+            else:
+                yield src, os.path.join(BUILD, name + ".o"), []
+
+
+def _compile(unit) -> str:
+    src, obj, flags = unit
+    cmd = [HIPCC] + CFLAGS + flags + ["-c", src, "-o", obj]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:
@@ -50,10 +63,10 @@ def _compile(src: str) -> str:
 
 def build(jobs: int | None = None) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
-    jobs = jobs or min(len(srcs), max(1, (os.cpu_count() or 2)))
+    units = list(_units())
+    jobs = jobs or min(len(units), max(1, (os.cpu_count() or 2)))
     with cf.ThreadPoolExecutor(jobs) as ex:
-        objs = list(ex.map(_compile, srcs))
+        objs = list(ex.map(_compile, units))
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp] + objs)
     os.replace(tmp, LIB)

@@ -155,6 +155,10 @@ inline hipError_t launch_kernel(void (*kernel)(A), dim3 grid, dim3 block, hipStr
 }
 
 hipError_t launch_tau(const TauArgs& a, int dtype, int head_dim, hipStream_t s);
+hipError_t launch_tau_bf16_64(const TauArgs& a, hipStream_t s);
+hipError_t launch_tau_bf16_128(const TauArgs& a, hipStream_t s);
+hipError_t launch_tau_f32_64(const TauArgs& a, hipStream_t s);
+hipError_t launch_tau_f32_128(const TauArgs& a, hipStream_t s);
 // The no-mask forward: tau, then O (and O2 if a.o2) in the same kernel.
 hipError_t launch_tau_fused(const TauArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_fwd(const FwdArgs& a, int dtype, int head_dim, bool train, hipStream_t s);

@@ -627,6 +627,12 @@ constexpr int SV_G1_MAX_N = 32768;
 constexpr int WARM_STOP = SV_NT / 2;
 // above it, at d = 64, the first stream covers every key block
 constexpr int WARM_ALL = 3 * SV_NT / 4;
+// Newton steps of a refined collection bound, and the most lists of a wave
+// (of 64) over half of their capacity for which it is tried (in the last quarter of the blocks)
+constexpr int REFINE_STEPS = 3;
+constexpr int REFINE_LISTS = 4;
+// quads beyond their share of 1.5 times the capacity at which lists are given up
+constexpr int GIVE_UP_MIN = 24;
 static_assert(SV_ROWS == 64 * SV_WAVES, "one 64-row query block per wave (G = 2)");
 
 // G = 2: each wave owns one 64-row query block as two groups of 32 rows.
@@ -1082,9 +1088,40 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     });
     cc[gq] = k;
   };
-  float sb[G];  // collection thresholds
+  float sb[G];   // collection thresholds (score units)
+  float xb[G];   // bounds that refine() took from the lists (x units)
 #pragma unroll
-  for (int gq = 0; gq < G; ++gq) sb[gq] = -INFINITY;
+  for (int gq = 0; gq < G; ++gq) sb[gq] = xb[gq] = -INFINITY;
+  // Raises the collection threshold of group gq by Newton steps on f
+  // restricted to the scores in the row's two lists (all lanes of the wave).
+  // Like the top-eight bound, but over every candidate so far, so that a row
+  // with a wide support keeps little more than its support: the restricted f
+  // is convex and decreasing and no larger than f, so the steps stay below
+  // its root, which is no larger than tau.
+  auto refine = [&](int gq) {
+    cmax[gq] = wave_max(cc[gq]);
+    float b = c * sb[gq];
+#pragma unroll 1
+    for (int it = 0; it < REFINE_STEPS; ++it) {
+      float f = 0.f, fp = 0.f;
+      scan_quads(gq, [&](const f32x4& v, int) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float pj, uj;
+          Gamma<GK>::pu(relu_z(c, v[i], b), g, pj, uj);
+          f += pj;
+          fp += uj;
+        }
+      });
+      f = sum_halves(f) - 1.f;
+      fp = sum_halves(fp);
+      if (row_ok[gq] && f > 0.f) b += f / (g * fp);
+    }
+    if (row_ok[gq]) {
+      xb[gq] = fmaxf(xb[gq], b);
+      sb[gq] = fmaxf(sb[gq], b / c - 1e-5f * fmaxf(fabsf(b / c), 1.f / c));
+    }
+  };
   __shared__ int fill_dead;              // a list overflowed: stop collecting
   if (threadIdx.x == 0) fill_dead = 0;   // read after the first block's barrier
   // With a cache slot, a first stream over the leading key blocks finds
@@ -1160,7 +1197,9 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   // The collection starts after the first stream's blocks, whose maxima are
   // in, and takes them last, at the bound of all the others: fewer of their
   // scores pass than at the bound of the first stream alone.
-  stream_from(W < nkb ? W : 0, [&](int kb, const E* kt) {
+  const int first = W < nkb ? W : 0;
+  auto nth = [&](int kb) { return kb >= first ? kb - first : kb - first + nkb; };  // its place in the stream
+  stream_from(first, [&](int kb, const E* kt) {
     // once the lists have overflowed, the first stream's blocks need nothing
     // more (their maxima are in)
     if (kb < W && fill_dead) return;
@@ -1189,10 +1228,27 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
         if (row_ok[gq]) sb[gq] = fmaxf(sb[gq], score_bound(u, (kb & 31) == 0));
       }
     }
-    // a block adds at most 8 quads to each list
+    // Lists that would pass their capacity by half at their present rate are
+    // given up at once: collecting and filtering them further would be lost
+    // (solver at n = 8192, d = 128, alpha 1.5, c = 1/4 and 1/2: 1.65 and 1.60
+    // against 1.93 and 1.86 ms).
+    if ((kb & 7) == 0 &&
+        __ballot(any_over(cc, GIVE_UP_MIN + 3 * a.cap / 2 * nth(kb) / nkb)) != 0ull) {
+      fill_dead = 1;
+      return;
+    }
+    // A block adds at most 8 quads to each list.  Where a few lists fill up
+    // late, among others that fit, they belong to rows with a wide support:
+    // their bound is refined before they are filtered, since one row whose
+    // list overflows would have the whole workgroup stream K for every
+    // evaluation, and the launch wait for it (n = 8192, d = 128, alpha 1.5,
+    // c = 1: 0.67 against 1.16 ms with 2 such tiles of 512).  Where many are
+    // long the scans cost more than they save (alpha 1.25, c = 2: 2.27
+    // against 1.60 ms).
 #pragma unroll
     for (int gq = 0; gq < G; ++gq) {
       if (__ballot(cc[gq] > a.cap - 8) != 0ull) {
+        if (newton_bound && 4 * nth(kb) >= 3 * nkb && __popcll(__ballot(cc[gq] > a.cap / 2)) <= REFINE_LISTS) refine(gq);
         filter(gq, sb[gq]);
         if (__ballot(cc[gq] > a.cap - 8) != 0ull) {
           fill_dead = 1;
@@ -1233,6 +1289,8 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
       // the bound may round above the root by a few ulps (rows whose whole
       // support is among the eight reach it)
       lo[gq] = fminf(b - 4e-6f * fmaxf(1.f, fabsf(b)), hi[gq]);
+      // the lists hold no score at or below a bound that refine() took
+      lo[gq] = fmaxf(lo[gq], fminf(xb[gq] - 4e-6f * fmaxf(1.f, fabsf(xb[gq])), hi[gq]));
       tau[gq] = 0.5f * (lo[gq] + hi[gq]);
     }
   }
@@ -1716,6 +1774,26 @@ hipError_t launch_solve_d(const TauArgs& a, hipStream_t s) {
   return launch_solve_g<E, D, 2>(a, s);
 }
 
+}  // namespace
+
+// Every part of this file is compiled on its own (EA_TAU_PART, see build.py),
+// since its instantiations take minutes to compile one after another: the
+// solver for each input type and head dimension, and the no-mask forward.
+#if EA_TAU_PART == 0
+hipError_t launch_tau_bf16_64(const TauArgs& a, hipStream_t s) { return launch_solve_d<__bf16, 64>(a, s); }
+#elif EA_TAU_PART == 1
+hipError_t launch_tau_bf16_128(const TauArgs& a, hipStream_t s) { return launch_solve_d<__bf16, 128>(a, s); }
+#elif EA_TAU_PART == 2
+hipError_t launch_tau_f32_64(const TauArgs& a, hipStream_t s) { return launch_solve_d<float, 64>(a, s); }
+#elif EA_TAU_PART == 3
+hipError_t launch_tau_f32_128(const TauArgs& a, hipStream_t s) { return launch_solve_d<float, 128>(a, s); }
+#elif EA_TAU_PART == 4
+hipError_t launch_tau(const TauArgs& a, int dtype, int head_dim, hipStream_t s) {
+  if (dtype == 0) return head_dim == 64 ? launch_tau_bf16_64(a, s) : launch_tau_bf16_128(a, s);
+  return head_dim == 64 ? launch_tau_f32_64(a, s) : launch_tau_f32_128(a, s);
+}
+
+namespace {
 template <int MODE>
 hipError_t launch_tau_mode(const TauArgs& a, int dtype, int head_dim, hipStream_t s) {
   if (dtype == 0)
@@ -1725,15 +1803,12 @@ hipError_t launch_tau_mode(const TauArgs& a, int dtype, int head_dim, hipStream_
 
 }  // namespace
 
-hipError_t launch_tau(const TauArgs& a, int dtype, int head_dim, hipStream_t s) {
-  if (dtype == 0)
-    return head_dim == 64 ? launch_solve_d<__bf16, 64>(a, s) : launch_solve_d<__bf16, 128>(a, s);
-  return head_dim == 64 ? launch_solve_d<float, 64>(a, s) : launch_solve_d<float, 128>(a, s);
-}
-
 hipError_t launch_tau_fused(const TauArgs& a, int dtype, int head_dim, hipStream_t s) {
   return a.o2 ? launch_tau_mode<FUSED_O2>(a, dtype, head_dim, s)
               : launch_tau_mode<FUSED_O>(a, dtype, head_dim, s);
 }
+#else
+#error "EA_TAU_PART must be 0 .. 4"
+#endif
 
 }  // namespace ea
