@@ -176,6 +176,39 @@ ea_status entmax_attn_bwd_stage(int stage, const ea_shape* shape, const ea_param
                                 void* workspace, size_t ws_bytes, void* stream);
 
 /*
+ * The forward and backward with element lists.  Where a 64-row query block
+ * has few nonzero probabilities the forward's solver also writes them out, as
+ * lists of (z = x - tau, key) per row, into `lists`; the later stages then work
+ * on the listed entries of that block instead of recomputing the scores of its
+ * key blocks.  The results are those of entmax_attn_fwd / entmax_attn_bwd up
+ * to rounding, and the residuals are the same; `lists` is one more buffer that
+ * the forward writes and the backward reads (and sorts into parts of its own,
+ * the same ones on every call).  A backward may be given lists only with the
+ * residuals of the forward that wrote them; if another forward has written
+ * new thresholds to those residuals since, its blocks are computed without
+ * the lists.
+ *   stage      as for the *_stage functions, or EA_ALL_STAGES
+ *   lists      16-byte aligned, entmax_attn_lists_bytes bytes, or NULL: then
+ *              the functions without lists
+ *   workspace  as for those (a forward without one lists no block); NULL in a
+ *              backward of all stages: as entmax_attn_bwd_noalloc
+ * Sequences of more than 65536 keys have no lists: entmax_attn_lists_bytes
+ * gives 0, and a call with lists returns EA_ERR_UNSUPPORTED.  A backward with
+ * lists launches 4 kernels.
+ */
+#define EA_ALL_STAGES (-1)
+ea_status entmax_attn_lists_bytes(const ea_shape* shape, const ea_params* params, size_t* bytes);
+ea_status entmax_attn_fwd_lists(int stage, const ea_shape* shape, const ea_params* params,
+                                const void* q, const void* k, const void* v, void* o,
+                                const ea_residuals* res, void* lists, size_t lists_bytes,
+                                void* workspace, size_t ws_bytes, void* stream);
+ea_status entmax_attn_bwd_lists(int stage, const ea_shape* shape, const ea_params* params,
+                                const void* q, const void* k, const void* v, const void* dout,
+                                const ea_residuals* res, void* lists, size_t lists_bytes,
+                                float* dq, float* dk, float* dv, void* workspace, size_t ws_bytes,
+                                void* stream);
+
+/*
  * The backward without a workspace, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  Arguments, results and errors are those of

@@ -35,7 +35,9 @@ SYMBOLS = ("entmax_attn_default_params", "entmax_attn_sizes", "entmax_attn_fwd",
            "entmax_attn_bwd", "entmax_attn_fwd_stage", "entmax_attn_bwd_stage",
            "entmax_attn_status_string", "entmax_attn_last_hip_error", "entmax_rows_fwd",
            "entmax_rows_bwd", "entmax_attn_fwd_dense", "entmax_attn_bwd_dense",
-           "entmax_attn_bwd_noalloc")
+           "entmax_attn_bwd_noalloc", "entmax_attn_lists_bytes", "entmax_attn_fwd_lists",
+           "entmax_attn_bwd_lists")
+EA_ALL_STAGES = -1
 NOALLOC_MAX_ROWS = 1048576  # EA_NOALLOC_MAX_ROWS of include/entmax_attn.h
 
 
@@ -52,6 +54,10 @@ class Params(ctypes.Structure):
 
 
 class ResidualPtrs(ctypes.Structure):
+    """The ABI's ea_residuals.  `lists` and `lists_bytes`, set by
+    Residuals.ptrs(), name the element lists that belong to them; the calls
+    below then pass those on."""
+    lists, lists_bytes = None, 0
     _fields_ = [(f, ctypes.c_void_p) for f in
                 ("tau", "o2", "block_mask", "q_count", "q_index", "k_count", "k_index", "stats",
                  "tau_lo")]
@@ -98,6 +104,16 @@ _lib.entmax_rows_bwd.restype = ctypes.c_int
 _lib.entmax_attn_bwd_noalloc.argtypes = [_P(Shape), _P(Params), _v, _v, _v, _v, _P(ResidualPtrs),
                                          _v, _v, _v, _v]
 _lib.entmax_attn_bwd_noalloc.restype = ctypes.c_int
+_lib.entmax_attn_lists_bytes.argtypes = [_P(Shape), _P(Params), _P(ctypes.c_size_t)]
+_lib.entmax_attn_lists_bytes.restype = ctypes.c_int
+_lib.entmax_attn_fwd_lists.argtypes = [ctypes.c_int, _P(Shape), _P(Params), _v, _v, _v, _v,
+                                       _P(ResidualPtrs), _v, ctypes.c_size_t, _v, ctypes.c_size_t,
+                                       _v]
+_lib.entmax_attn_fwd_lists.restype = ctypes.c_int
+_lib.entmax_attn_bwd_lists.argtypes = [ctypes.c_int, _P(Shape), _P(Params), _v, _v, _v, _v,
+                                       _P(ResidualPtrs), _v, ctypes.c_size_t, _v, _v, _v, _v,
+                                       ctypes.c_size_t, _v]
+_lib.entmax_attn_bwd_lists.restype = ctypes.c_int
 _lib.entmax_attn_last_hip_error.argtypes = []
 _lib.entmax_attn_last_hip_error.restype = ctypes.c_char_p
 
@@ -132,31 +148,81 @@ def entmax_attn_sizes(shape: Shape, params: Params) -> Sizes:
     return z
 
 
-def entmax_attn_fwd(shape, params, q, k, v, o, res: ResidualPtrs, workspace, ws_bytes, stream):
+def entmax_attn_lists_bytes(shape: Shape, params: Params) -> int:
+    n = ctypes.c_size_t()
+    _check(_lib.entmax_attn_lists_bytes(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(n)),
+           "entmax_attn_lists_bytes")
+    return n.value
+
+
+def _lists_of(res: ResidualPtrs, shape, params):
+    """The lists of res, as (pointer, bytes), if they serve this shape."""
+    if res.lists is None:
+        return None, 0
+    n = ctypes.c_size_t()
+    st = _lib.entmax_attn_lists_bytes(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(n))
+    return (res.lists, res.lists_bytes) if st == EA_OK and 0 < n.value <= res.lists_bytes else (None, 0)
+
+
+def entmax_attn_fwd_lists(stage, shape, params, q, k, v, o, res: ResidualPtrs, lists, lists_bytes,
+                          workspace, ws_bytes, stream):
     """Raw call; pointers are ints (device addresses), stream an int handle."""
+    return _lib.entmax_attn_fwd_lists(stage, ctypes.byref(shape), ctypes.byref(params), q, k, v, o,
+                                      ctypes.byref(res), lists, lists_bytes, workspace, ws_bytes,
+                                      stream)
+
+
+def entmax_attn_bwd_lists(stage, shape, params, q, k, v, dout, res: ResidualPtrs, lists,
+                          lists_bytes, dq, dk, dv, workspace, ws_bytes, stream):
+    return _lib.entmax_attn_bwd_lists(stage, ctypes.byref(shape), ctypes.byref(params), q, k, v,
+                                      dout, ctypes.byref(res), lists, lists_bytes, dq, dk, dv,
+                                      workspace, ws_bytes, stream)
+
+
+def entmax_attn_fwd(shape, params, q, k, v, o, res: ResidualPtrs, workspace, ws_bytes, stream):
+    lists = _lists_of(res, shape, params)
+    if lists[0]:
+        return entmax_attn_fwd_lists(EA_ALL_STAGES, shape, params, q, k, v, o, res, *lists, workspace,
+                                     ws_bytes, stream)
     return _lib.entmax_attn_fwd(ctypes.byref(shape), ctypes.byref(params), q, k, v, o,
                                 ctypes.byref(res), workspace, ws_bytes, stream)
 
 
 def entmax_attn_bwd(shape, params, q, k, v, dout, res: ResidualPtrs, dq, dk, dv, workspace,
                     ws_bytes, stream):
+    lists = _lists_of(res, shape, params)
+    if lists[0] and workspace:
+        return entmax_attn_bwd_lists(EA_ALL_STAGES, shape, params, q, k, v, dout, res, *lists, dq, dk,
+                                     dv, workspace, ws_bytes, stream)
     return _lib.entmax_attn_bwd(ctypes.byref(shape), ctypes.byref(params), q, k, v, dout,
                                 ctypes.byref(res), dq, dk, dv, workspace, ws_bytes, stream)
 
 
 def entmax_attn_bwd_noalloc(shape, params, q, k, v, dout, res: ResidualPtrs, dq, dk, dv, stream):
+    lists = _lists_of(res, shape, params)
+    if lists[0]:
+        return entmax_attn_bwd_lists(EA_ALL_STAGES, shape, params, q, k, v, dout, res, *lists, dq, dk,
+                                     dv, None, 0, stream)
     return _lib.entmax_attn_bwd_noalloc(ctypes.byref(shape), ctypes.byref(params), q, k, v, dout,
                                         ctypes.byref(res), dq, dk, dv, stream)
 
 
 def entmax_attn_fwd_stage(stage, shape, params, q, k, v, o, res: ResidualPtrs, workspace,
                           ws_bytes, stream):
+    lists = _lists_of(res, shape, params)
+    if lists[0] and stage >= 0:
+        return entmax_attn_fwd_lists(stage, shape, params, q, k, v, o, res, *lists, workspace,
+                                     ws_bytes, stream)
     return _lib.entmax_attn_fwd_stage(stage, ctypes.byref(shape), ctypes.byref(params), q, k, v,
                                       o, ctypes.byref(res), workspace, ws_bytes, stream)
 
 
 def entmax_attn_bwd_stage(stage, shape, params, q, k, v, dout, res: ResidualPtrs, dq, dk, dv,
                           workspace, ws_bytes, stream):
+    lists = _lists_of(res, shape, params)
+    if lists[0] and stage >= 0:
+        return entmax_attn_bwd_lists(stage, shape, params, q, k, v, dout, res, *lists, dq, dk, dv,
+                                     workspace, ws_bytes, stream)
     return _lib.entmax_attn_bwd_stage(stage, ctypes.byref(shape), ctypes.byref(params), q, k, v,
                                       dout, ctypes.byref(res), dq, dk, dv, workspace, ws_bytes,
                                       stream)
@@ -191,6 +257,15 @@ def make_params(alpha=1.5, scale=None, causal=False, need_bwd=True, max_iter=Non
     return p
 
 
+def _lists_limit(device) -> int:
+    """Largest element lists that Residuals allocates: a sixteenth of the
+    device's memory."""
+    device = torch.device(device)
+    if device.type != "cuda":
+        return 1 << 30
+    return torch.cuda.get_device_properties(device).total_memory // 16
+
+
 class Residuals:
     """Device buffers (torch tensors) that the forward fills and the backward
     reads, sized by entmax_attn_sizes."""
@@ -214,12 +289,19 @@ class Residuals:
         # fp32 inputs: the low part of tau (tau + tau_lo to ~fp64 precision)
         self.tau_lo = (torch.empty(z.tau_lo // 4, dtype=torch.float32, device=device).view(BH, n)
                        if z.tau_lo else None)
+        # the forward's element lists (see entmax_attn_fwd_lists), or None
+        nbytes = entmax_attn_lists_bytes(shape, params)
+        self.lists = (torch.empty(nbytes, dtype=torch.uint8, device=device)
+                      if 0 < nbytes <= _lists_limit(device) else None)
 
     def ptrs(self) -> ResidualPtrs:
         f = lambda t: None if t is None else t.data_ptr()
-        return ResidualPtrs(f(self.tau), f(self.o2), f(self.block_mask), f(self.q_count),
-                            f(self.q_index), f(self.k_count), f(self.k_index), f(self.stats),
-                            f(self.tau_lo))
+        p = ResidualPtrs(f(self.tau), f(self.o2), f(self.block_mask), f(self.q_count),
+                         f(self.q_index), f(self.k_count), f(self.k_index), f(self.stats),
+                         f(self.tau_lo))
+        if self.lists is not None:
+            p.lists, p.lists_bytes = self.lists.data_ptr(), self.lists.numel()
+        return p
 
 
 def _stream_handle(device):
@@ -292,6 +374,8 @@ def _check_residuals(res, shape: Shape, device, need_o2: bool):
         _need(res.stats, "res.stats", (2, BH, T), torch.int32, device)
     if shape.dtype == EA_F32:
         _need(res.tau_lo, "res.tau_lo", (BH, n), torch.float32, device)
+    if res.lists is not None:
+        _check_bytes(res.lists, "res.lists", entmax_attn_lists_bytes(shape, res.params), device)
 
 
 def _check_bytes(ws, name, need_bytes, device):
@@ -361,7 +445,8 @@ def backward(q, k, v, dout, res: Residuals, dq=None, dk=None, dv=None, workspace
     rp = res.ptrs()
     _check(entmax_attn_bwd(shape, res.params, q.data_ptr(), k.data_ptr(), v.data_ptr(),
                            dout.data_ptr(), rp, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
-                           workspace.data_ptr(), workspace.numel() * 4, _stream_handle(q.device)),
+                           workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+                           _stream_handle(q.device)),
            "entmax_attn_bwd")
     return dq, dk, dv
 

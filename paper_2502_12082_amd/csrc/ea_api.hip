@@ -115,6 +115,28 @@ void fill_sizes(const Dims& d, ea_sizes* z) {
   z->tau_lo = d.dtype == EA_F32 ? (size_t)(d.BH * d.n) * 4 : 0;
 }
 
+// Element lists: one ListBlock per query block, written by the forward, then
+// the buckets that each backward sorts them into (always the same ones), each
+// part 256-byte aligned.  Fills *b (if given) from the buffer `lists`.
+size_t up256(size_t b) { return (b + 255) / 256 * 256; }
+size_t lists_layout(const Dims& d, char* lists, Buckets* b) {
+  if (d.n > LIST_MAX_SEQLEN) return 0;
+  const size_t blocks = (size_t)(d.BH * d.T);
+  size_t at = up256(blocks * sizeof(ListBlock));
+  auto part = [&](size_t bytes) {
+    char* p = lists ? lists + at : nullptr;
+    at += up256(bytes);
+    return p;
+  };
+  Buckets t;
+  t.used = reinterpret_cast<int32_t*>(part(blocks * 4));
+  t.off = reinterpret_cast<uint16_t*>(part(blocks * (size_t)(d.T + 1) * 2));
+  t.z = reinterpret_cast<float*>(part(blocks * LIST_ENTRIES * 4));
+  t.code = reinterpret_cast<uint16_t*>(part(blocks * LIST_ENTRIES * 2));
+  if (b) *b = t;
+  return at;
+}
+
 bool tensor_ok(const void* p) { return p && aligned(p, 16); }
 bool small_ok(const void* p) { return p && aligned(p, 4); }
 
@@ -241,7 +263,7 @@ ea_status prep_fwd(const ea_shape* shape, const ea_params* params, const void* q
 
 ea_status run_fwd_stage(int stage, const Dims& d, const ea_params* params, const void* q,
                         const void* k, const void* v, void* o, const ea_residuals* res,
-                        void* workspace, size_t ws_bytes, hipStream_t s) {
+                        void* workspace, size_t ws_bytes, ListBlock* lists, hipStream_t s) {
   const float c = (params->alpha - 1.0f) * params->scale;
   const float gamma = 1.0f / (params->alpha - 1.0f);
   const int gk = gamma_kind(params->alpha);
@@ -257,13 +279,13 @@ ea_status run_fwd_stage(int stage, const Dims& d, const ea_params* params, const
                (int)d.BH, (int)d.n, (int)d.T, c, params->alpha, gamma, params->causal,
                params->max_iter, params->tol, gk,
                const_cast<float*>(tau_lo_of(res, d)), c64_of(params), g64_of(params),
-               res->q_count, res->q_index};
+               res->q_count, res->q_index, lists};
     return from_hip(launch_tau(ta, d.dtype, (int)d.d, s));
   }
   FwdArgs fa{q, k, v, o, params->need_bwd ? res->o2 : nullptr, res->tau, res->q_count,
              res->q_index, (int)d.BH, (int)d.n, (int)d.T, c, gamma, params->causal, gk,
              tau_lo_of(res, d), c64_of(params), g64_of(params),
-             res->block_mask, res->k_count, res->k_index};
+             res->block_mask, res->k_count, res->k_index, lists};
   return from_hip(launch_fwd(fa, d.dtype, (int)d.d, params->need_bwd != 0, s));
 }
 
@@ -293,10 +315,14 @@ ea_status prep_bwd(const ea_shape* shape, const ea_params* params, const void* q
 
 ea_status run_bwd_stage(int stage, const Dims& d, const ea_params* params, const void* q,
                         const void* k, const void* v, const void* dout, const ea_residuals* res,
-                        float* dq, float* dk, float* dv, void* workspace, hipStream_t s) {
+                        float* dq, float* dk, float* dv, void* workspace, void* lists_buf,
+                        hipStream_t s) {
   float* delta = static_cast<float*>(workspace);
+  const ListBlock* lists = static_cast<const ListBlock*>(lists_buf);
+  Buckets buckets{};
+  if (lists) lists_layout(d, static_cast<char*>(lists_buf), &buckets);
   if (stage == 0) {
-    DeltaArgs da{dout, res->o2, delta, d.BH * d.n};
+    DeltaArgs da{dout, res->o2, delta, d.BH * d.n, lists, res->tau, buckets, (int)d.BH, (int)d.n, (int)d.T};
     return from_hip(launch_delta(da, d.dtype, (int)d.d, s));
   }
   const float c = (params->alpha - 1.0f) * params->scale;
@@ -304,8 +330,12 @@ ea_status run_bwd_stage(int stage, const Dims& d, const ea_params* params, const
   BwdArgs ba{q, k, v, dout, res->tau, delta, res->q_count, res->q_index, res->k_count,
              res->k_index, dq, dk, dv, (int)d.BH, (int)d.n, (int)d.T, c, gamma,
              params->scale, params->causal, gamma_kind(params->alpha), tau_lo_of(res, d),
-             c64_of(params), g64_of(params)};
-  if (stage == 1) return from_hip(launch_bwd_dkdv(ba, d.dtype, (int)d.d, s));
+             c64_of(params), g64_of(params), lists, buckets};
+  if (stage == 1) {
+    const ea_status st = from_hip(launch_bwd_dkdv(ba, d.dtype, (int)d.d, s));
+    if (st != EA_OK || !lists) return st;
+    return from_hip(launch_bwd_dkdv_lists(ba, d.dtype, (int)d.d, s));
+  }
   return from_hip(launch_bwd_dq(ba, d.dtype, (int)d.d, s));
 }
 
@@ -319,7 +349,7 @@ ea_status entmax_attn_fwd(const ea_shape* shape, const ea_params* params, const 
   if (st != EA_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   for (int stage = 0; stage < 2; ++stage)
-    if ((st = run_fwd_stage(stage, d, params, q, k, v, o, res, workspace, ws_bytes, s)) != EA_OK)
+    if ((st = run_fwd_stage(stage, d, params, q, k, v, o, res, workspace, ws_bytes, nullptr, s)) != EA_OK)
       return st;
   return EA_OK;
 }
@@ -332,7 +362,7 @@ ea_status entmax_attn_fwd_stage(int stage, const ea_shape* shape, const ea_param
   Dims d;
   ea_status st = prep_fwd(shape, params, q, k, v, o, res, workspace, &d);
   if (st != EA_OK) return st;
-  return run_fwd_stage(stage, d, params, q, k, v, o, res, workspace, ws_bytes,
+  return run_fwd_stage(stage, d, params, q, k, v, o, res, workspace, ws_bytes, nullptr,
                        static_cast<hipStream_t>(stream));
 }
 
@@ -345,7 +375,7 @@ ea_status entmax_attn_bwd(const ea_shape* shape, const ea_params* params, const 
   if (st != EA_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   for (int stage = 0; stage < 3; ++stage)
-    if ((st = run_bwd_stage(stage, d, params, q, k, v, dout, res, dq, dk, dv, workspace, s)) != EA_OK)
+    if ((st = run_bwd_stage(stage, d, params, q, k, v, dout, res, dq, dk, dv, workspace, nullptr, s)) != EA_OK)
       return st;
   return EA_OK;
 }
@@ -358,8 +388,75 @@ ea_status entmax_attn_bwd_stage(int stage, const ea_shape* shape, const ea_param
   Dims d;
   ea_status st = prep_bwd(shape, params, q, k, v, dout, res, dq, dk, dv, workspace, ws_bytes, &d);
   if (st != EA_OK) return st;
-  return run_bwd_stage(stage, d, params, q, k, v, dout, res, dq, dk, dv, workspace,
+  return run_bwd_stage(stage, d, params, q, k, v, dout, res, dq, dk, dv, workspace, nullptr,
                        static_cast<hipStream_t>(stream));
+}
+
+ea_status entmax_attn_lists_bytes(const ea_shape* shape, const ea_params* params, size_t* bytes) {
+  Dims d;
+  const ea_status st = check_shape(shape, params, &d);
+  if (st != EA_OK) return st;
+  if (!bytes) return EA_ERR_INVALID_ARG;
+  *bytes = lists_layout(d, nullptr, nullptr);
+  return EA_OK;
+}
+
+namespace {
+
+// Checks of a lists buffer (null: no lists).
+ea_status check_lists(const Dims& d, const void* lists, size_t lists_bytes) {
+  if (!lists) return EA_OK;
+  const size_t need = lists_layout(d, nullptr, nullptr);
+  if (need == 0) return EA_ERR_UNSUPPORTED;
+  if (!aligned(lists, 16)) return EA_ERR_INVALID_ARG;
+  return lists_bytes < need ? EA_ERR_WORKSPACE : EA_OK;
+}
+
+// The stages of one call: all of them, or one.
+int first_stage(int stage) { return stage == EA_ALL_STAGES ? 0 : stage; }
+int last_stage(int stage, int last) { return stage == EA_ALL_STAGES ? last : stage; }
+
+}  // namespace
+
+ea_status entmax_attn_fwd_lists(int stage, const ea_shape* shape, const ea_params* params, const void* q,
+                                const void* k, const void* v, void* o, const ea_residuals* res,
+                                void* lists, size_t lists_bytes, void* workspace, size_t ws_bytes,
+                                void* stream) {
+  if (stage < EA_ALL_STAGES || stage > 1) return EA_ERR_INVALID_ARG;
+  Dims d;
+  ea_status st = prep_fwd(shape, params, q, k, v, o, res, workspace, &d);
+  if (st != EA_OK || (st = check_lists(d, lists, lists_bytes)) != EA_OK) return st;
+  for (int x = first_stage(stage); x <= last_stage(stage, 1); ++x)
+    if ((st = run_fwd_stage(x, d, params, q, k, v, o, res, workspace, ws_bytes,
+                            static_cast<ListBlock*>(lists), static_cast<hipStream_t>(stream))) != EA_OK)
+      return st;
+  return EA_OK;
+}
+
+ea_status entmax_attn_bwd_lists(int stage, const ea_shape* shape, const ea_params* params, const void* q,
+                                const void* k, const void* v, const void* dout, const ea_residuals* res,
+                                void* lists, size_t lists_bytes, float* dq, float* dk, float* dv,
+                                void* workspace, size_t ws_bytes, void* stream) {
+  if (stage < EA_ALL_STAGES || stage > 2) return EA_ERR_INVALID_ARG;
+  Dims d;
+  ea_status st;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (workspace || stage != EA_ALL_STAGES) {
+    st = prep_bwd(shape, params, q, k, v, dout, res, dq, dk, dv, workspace, ws_bytes, &d);
+    if (st != EA_OK || (st = check_lists(d, lists, lists_bytes)) != EA_OK) return st;
+  } else {  // delta in the library's scratch, as in entmax_attn_bwd_noalloc
+    if ((st = check_shape(shape, params, &d)) != EA_OK) return st;
+    if (d.BH * d.n > (int64_t)EA_NOALLOC_MAX_ROWS) return EA_ERR_UNSUPPORTED;
+    if ((st = prep_bwd_args(shape, params, q, k, v, dout, res, dq, dk, dv, &d)) != EA_OK) return st;
+    if ((st = check_lists(d, lists, lists_bytes)) != EA_OK) return st;
+    hipError_t e = hipSuccess;
+    workspace = scratch_for(s, &e);
+    if (!workspace) return from_hip(e);
+  }
+  for (int x = first_stage(stage); x <= last_stage(stage, 2); ++x)
+    if ((st = run_bwd_stage(x, d, params, q, k, v, dout, res, dq, dk, dv, workspace, lists, s)) != EA_OK)
+      return st;
+  return EA_OK;
 }
 
 ea_status entmax_attn_bwd_noalloc(const ea_shape* shape, const ea_params* params, const void* q,
@@ -376,7 +473,7 @@ ea_status entmax_attn_bwd_noalloc(const ea_shape* shape, const ea_params* params
   float* delta = scratch_for(s, &e);
   if (!delta) return from_hip(e);
   for (int stage = 0; stage < 3; ++stage)
-    if ((st = run_bwd_stage(stage, d, params, q, k, v, dout, res, dq, dk, dv, delta, s)) != EA_OK)
+    if ((st = run_bwd_stage(stage, d, params, q, k, v, dout, res, dq, dk, dv, delta, nullptr, s)) != EA_OK)
       return st;
   return EA_OK;
 }
@@ -449,7 +546,7 @@ ea_status entmax_attn_bwd_dense(const ea_shape* shape, const ea_params* params, 
   res.o2 = const_cast<float*>(o2);
   hipStream_t s = static_cast<hipStream_t>(stream);
   for (int stage = 0; stage < 3; ++stage)
-    if ((st = run_bwd_stage(stage, d, params, q, k, v, dout, &res, dq, dk, dv, workspace, s)) != EA_OK)
+    if ((st = run_bwd_stage(stage, d, params, q, k, v, dout, &res, dq, dk, dv, workspace, nullptr, s)) != EA_OK)
       return st;
   return EA_OK;
 }

@@ -56,7 +56,204 @@ __global__ __launch_bounds__(256) void delta_kernel(DeltaArgs a) {
   if (row < a.rows && sl == 0) a.delta[row] = acc;
 }
 
+// ------------------------------------- element lists sorted by key block
+
+// Lanes whose `key` (of `bits` bits) equals the calling lane's, among the
+// lanes of `active`.
+__device__ __forceinline__ unsigned long long same_key(int key, int bits, unsigned long long active) {
+  unsigned long long m = active;
+  for (int b = 0; b < bits; ++b) {
+    const unsigned long long set = __ballot((key >> b) & 1);
+    m &= (key >> b) & 1 ? set : ~set;
+  }
+  return m;
+}
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
+constexpr int PREP_NT = 256;
+constexpr int PREP_T = LIST_MAX_SEQLEN / BLK;  // most key blocks
+constexpr int PREP_STAGE = 3072;               // entries that fit the staging memory
+// Buckets::used: the block's lists are good (for dQ), and sorted (for dK, dV)
+constexpr int LISTED = 1, SORTED = 2;
+
+// One workgroup per 64-row query block: delta of its rows, and, where the
+// forward listed the block, its entries sorted by key block for the dK/dV
+// kernel (a counting sort: each wave takes 32 of the 128 lists, counts its
+// entries per key block, and places them after those of the waves before).
+// Entries of one key block keep the order of (wave, entry, list), so the sort
+// is deterministic.  The lists are used only if their thresholds are the
+// residuals' (a forward that did not write lists may have filled the
+// residuals again).
+template <typename E, int D>
+__global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
+  constexpr int PER = D / 16;  // 16 lanes per row
+  constexpr int W = PREP_NT / 64;
+  __shared__ uint32_t cursor[W][PREP_T];
+  __shared__ float zs[PREP_STAGE];
+  __shared__ uint16_t cs[PREP_STAGE];
+  __shared__ uint32_t wsum[W];
+  const int t = threadIdx.x, lane = lane_id(), w = wave_id();
+  const int bh = blockIdx.x / a.T, qb = blockIdx.x % a.T;
+  const size_t blk = blockIdx.x;
+  const int nr = min(BLK, a.n - qb * BLK);
+  const long long row0 = (long long)bh * a.n + (long long)qb * BLK;
+#pragma unroll
+  for (int r = t >> 4; r < BLK; r += PREP_NT / 16) {
+    float acc = 0.f;
+    if (r < nr) {
+      const E* dO = static_cast<const E*>(a.dout) + (row0 + r) * D + (t & 15) * PER;
+      const float* o2 = a.o2 + (row0 + r) * D + (t & 15) * PER;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) acc = fmaf((float)dO[e], o2[e], acc);
+    }
+#pragma unroll
+    for (int m = 8; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
+    if (r < nr && (t & 15) == 0) a.delta[row0 + r] = acc;
+  }
+
+  const ListBlock& lb = a.lists[blk];
+  const int T = a.T;
+  bool same = true;
+  if (t < nr) same = __float_as_uint(lb.tau[t]) == __float_as_uint(a.tau[row0 + t]);
+  const bool used = __syncthreads_and(same && lb.used == 1);
+  // The dK/dV work of a head is split only if most of its blocks are listed:
+  // its other blocks cost a pass of their own over every key block.
+  int listed = 0;
+  for (int x0 = 0; x0 < T; x0 += PREP_NT)
+    listed += __syncthreads_count(x0 + t < T && a.lists[(size_t)bh * T + min(x0 + t, T - 1)].used == 1);
+  const bool sorted = used && 4 * listed >= 3 * T;
+  if (t == 0) a.buckets.used[blk] = sorted ? LISTED | SORTED : used ? LISTED : 0;
+  if (!sorted) return;
+
+  const int bits = 32 - __clz(max(T - 1, 1));
+  for (int x = t; x < W * T; x += PREP_NT) cursor[x / T][x % T] = 0;
+  const int id = 32 * w + (lane & 31), half = lane >> 5, cnt = lb.count[id];
+  int most = cnt;  // longest list of the wave
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) most = max(most, __shfl_xor(most, o));
+  // Lanes below 32 take the even entries of their list, the others the odd;
+  // loads in batches of eight entries per lane.
+  constexpr int B = 8;
+  auto keys = [&](int e0, int (&key)[B]) {
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int e = e0 + 2 * u + half;
+      key[u] = e < cnt ? (int)lb.key[LIST_IDS * e + id] : -1;
+    }
+  };
+  __syncthreads();
+  for (int e0 = 0; e0 < most; e0 += 2 * B) {
+    int key[B];
+    keys(e0, key);
+#pragma unroll
+    for (int u = 0; u < B; ++u)
+      if (key[u] >= 0) atomicAdd(&cursor[w][key[u] >> 6], 1u);
+  }
+  __syncthreads();
+  // exclusive sums in the order (key block, wave)
+  uint16_t* const off = a.buckets.off + blk * (size_t)(T + 1);
+  const int per = (T + PREP_NT - 1) / PREP_NT;
+  uint32_t mine = 0;
+  for (int k = 0; k < per; ++k) {
+    const int j = t * per + k;
+    if (j < T)
+      for (int x = 0; x < W; ++x) mine += cursor[x][j];
+  }
+  uint32_t incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t v = __shfl_up(incl, o);
+    if (lane >= o) incl += v;
+  }
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  uint32_t start = incl - mine;
+  for (int x = 0; x < w; ++x) start += wsum[x];
+  const uint32_t total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  for (int k = 0; k < per; ++k) {
+    const int j = t * per + k;
+    if (j < T) {
+      off[j] = (uint16_t)start;
+      for (int x = 0; x < W; ++x) {
+        const uint32_t v = cursor[x][j];
+        cursor[x][j] = start;
+        start += v;
+      }
+    }
+  }
+  if (t == 0) off[T] = (uint16_t)total;
+  __syncthreads();
+  float* const zg = a.buckets.z + blk * LIST_ENTRIES;
+  uint16_t* const cg = a.buckets.code + blk * LIST_ENTRIES;
+  const bool staged = total <= PREP_STAGE;
+  for (int e0 = 0; e0 < most; e0 += 2 * B) {
+    int key[B];
+    float z[B];
+    keys(e0, key);
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int e = e0 + 2 * u + half;
+      z[u] = e < cnt ? lb.z[LIST_IDS * e + id] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const bool ok = key[u] >= 0;
+      const unsigned long long act = __ballot(ok);
+      if (act == 0ull) break;
+      const int kb = key[u] >> 6;
+      const unsigned long long m = same_key(kb, bits, act);
+      if (ok) {
+        const int rank = lanes_below(m);
+        const uint32_t p = cursor[w][kb] + (uint32_t)rank;
+        if (rank == __popcll(m) - 1) cursor[w][kb] = p + 1;  // (all lanes have read it by then)
+        const uint16_t code = (uint16_t)((id & 63) * 64 + (key[u] & 63));
+        if (staged) {
+          zs[p] = z[u];
+          cs[p] = code;
+        } else {
+          zg[p] = z[u];
+          cg[p] = code;
+        }
+      }
+    }
+  }
+  if (!staged) return;
+  __syncthreads();
+  for (uint32_t p = t; p < total; p += PREP_NT) {
+    zg[p] = zs[p];
+    cg[p] = cs[p];
+  }
+}
+
 // ------------------------------------------------------------------ dK dV
+
+// The query blocks of list[0 .. cnt) that have no element lists, in order, in
+// out (in LDS); returns their number.  Every thread of the workgroup.
+template <int NT>
+__device__ int unlisted_blocks(const int32_t* list, int cnt, const int32_t* used, uint16_t* out) {
+  __shared__ int wcount[NT / 64];
+  int total = 0;
+  for (int e0 = 0; e0 < cnt; e0 += NT) {
+    const int e = e0 + (int)threadIdx.x;
+    const int qb = e < cnt ? list[e] : 0;
+    const bool b = e < cnt && !(used[qb] & SORTED);
+    const unsigned long long m = __ballot(b);
+    __syncthreads();  // wcount of the round before has been read
+    if (lane_id() == 0) wcount[wave_id()] = __popcll(m);
+    __syncthreads();
+    int at = total;
+#pragma unroll
+    for (int x = 0; x < NT / 64; ++x) {
+      if (x < wave_id()) at += wcount[x];
+      total += wcount[x];
+    }
+    if (b) out[at + lanes_below(m)] = (uint16_t)qb;
+  }
+  __syncthreads();
+  return total;
+}
 
 template <typename E, int D, int GK>
 __global__ __launch_bounds__(BWD_NT) void dkdv_kernel(BwdArgs a) {
@@ -87,18 +284,29 @@ __global__ __launch_bounds__(BWD_NT) void dkdv_kernel(BwdArgs a) {
   const float c = a.c, g = a.gamma;
   constexpr bool PRECISE = precise_path<E, GK>();
 
+  // Without tables (the no-mask mode) every valid query block is visited.
+  // With element lists only the query blocks without them are: their entries
+  // are compacted into `unlisted` first, and a key block that has none is
+  // left to the list kernel.
+  const bool dense = a.k_index == nullptr;
+  const int32_t* list = dense ? nullptr : a.k_index + ((size_t)bh * T + kb) * T;
+  int cnt = dense ? (a.causal ? T - kb : T) : a.k_count[(size_t)bh * T + kb];
+  __shared__ uint16_t unlisted[LIST_MAX_SEQLEN / BLK];
+  bool some = a.lists != nullptr;
+  if (some) {
+    const int left = unlisted_blocks<BWD_NT>(list, cnt, a.buckets.used + (size_t)bh * T, unlisted);
+    if (left == 0) return;
+    some = left != cnt;  // where every block is left, the table serves as it is
+    cnt = left;
+  }
+  auto qb_of = [&](int e) { return dense ? (a.causal ? kb + e : e) : some ? (int)unlisted[e] : list[e]; };
+
   typename M::frag kf[KS], vf[KS];
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) {
     kf[kk] = load_row_frag_global<E, D>(Kg, j, n, kk);
     vf[kk] = load_row_frag_global<E, D>(Vg, j, n, kk);
   }
-
-  // Without tables (the no-mask mode) every valid query block is visited.
-  const bool dense = a.k_index == nullptr;
-  const int32_t* list = dense ? nullptr : a.k_index + ((size_t)bh * T + kb) * T;
-  const int cnt = dense ? (a.causal ? T - kb : T) : a.k_count[(size_t)bh * T + kb];
-  auto qb_of = [&](int e) { return dense ? (a.causal ? kb + e : e) : list[e]; };
 
   f32x16 dk[NTD], dv[NTD];
 #pragma unroll
@@ -280,13 +488,6 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
   [[maybe_unused]] const float* delg = a.delta + (size_t)bh * n;
   const float c = a.c, g = a.gamma;
 
-  F kf[KS], vf[KS];
-#pragma unroll
-  for (int kk = 0; kk < KS; ++kk) {
-    kf[kk] = load_row_frag_global<E, D>(Kg, j, n, kk);
-    vf[kk] = load_row_frag_global<E, D>(Vg, j, n, kk);
-  }
-
   // Query-block lists of the two key blocks (without tables, in the no-mask
   // mode, every valid query block), merged in ascending order.
   const bool dense = a.k_index == nullptr;
@@ -295,19 +496,34 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
   typedef const __attribute__((address_space(4))) int32_t ci32;
   const ci32* kcount = (const ci32*)a.k_count;
   const ci32* kindex = (const ci32*)a.k_index;
+  __shared__ uint16_t unlisted[2][LIST_MAX_SEQLEN / BLK];
+  bool some = a.lists != nullptr;
   auto count_of = [&](int kb) {
     if (kb >= T) return 0;
     return dense ? (a.causal ? T - kb : T) : kcount[(size_t)bh * T + kb];
   };
-  auto entry_of = [&](int kb, int e) {
+  auto entry_of = [&](auto left, int kb, int e) {
+    if constexpr (decltype(left)::value) return __builtin_amdgcn_readfirstlane((int)unlisted[kb - kbA][e]);
     return dense ? (a.causal ? kb + e : e) : kindex[((size_t)bh * T + kb) * T + e];
   };
-  const int nA = count_of(kbA), nB = count_of(kbB);
+  int nA = count_of(kbA), nB = count_of(kbB);
   int pA = 0, pB = 0;
+  // With element lists, only the query blocks without them (see dkdv_kernel).
+  if (some) {
+    const int32_t* used = a.buckets.used + (size_t)bh * T;
+    const int tA = nA, tB = nB;
+    nA = unlisted_blocks<BWD2_NT>(a.k_index + ((size_t)bh * T + kbA) * T, nA, used, unlisted[0]);
+    nB = unlisted_blocks<BWD2_NT>(a.k_index + ((size_t)bh * T + min(kbB, T - 1)) * T, nB, used, unlisted[1]);
+    if (nA == 0 && nB == 0) return;
+    // (scalar registers: they steer the loop below)
+    nA = __builtin_amdgcn_readfirstlane(nA);
+    nB = __builtin_amdgcn_readfirstlane(nB);
+    some = nA != tA || nB != tB;  // where every block is left, the tables serve as they are
+  }
   // the next query block of the union, and whether each key block lists it
-  auto next = [&](int& qb, bool& inA, bool& inB) {
-    const int hA = pA < nA ? entry_of(kbA, pA) : T;
-    const int hB = pB < nB ? entry_of(kbB, pB) : T;
+  auto next = [&](auto left, int& qb, bool& inA, bool& inB) {
+    const int hA = pA < nA ? entry_of(left, kbA, pA) : T;
+    const int hB = pB < nB ? entry_of(left, kbB, pB) : T;
     qb = min(hA, hB);
     inA = hA == qb;
     inB = hB == qb;
@@ -315,6 +531,13 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
     pB += inB ? 1 : 0;
     return qb < T;
   };
+
+  F kf[KS], vf[KS];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) {
+    kf[kk] = load_row_frag_global<E, D>(Kg, j, n, kk);
+    vf[kk] = load_row_frag_global<E, D>(Vg, j, n, kk);
+  }
 
   f32x16 dk[NTH], dv[NTH];
 #pragma unroll
@@ -439,41 +662,49 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
     if (half_valid(qb * BLK + 32 * ch)) accum(qbuf[b], dobuf[b], ch, pa, dh, dl);
   };
 
-  // Union entries e (stage b0), e + 1 and e + 2 (in flight).
-  int q0 = 0, q1 = 0;
-  bool a0 = false, b0_ = false, a1 = false, b1_ = false;
-  bool h0 = next(q0, a0, b0_);
-  bool h1 = h0 && next(q1, a1, b1_);
-  if (h0) issue(q0, 0);
-  if (h1) issue(q1, 1);
-  int st = 0;
-  while (h0) {
-    int q2 = 0;
-    bool a2 = false, b2_ = false;
-    const bool h2 = h1 && next(q2, a2, b2_);
-    if (h1) {
-      wait_all_but_latest();
-    } else {
-      dma_wait();
+  // `left`: only the query blocks left in `unlisted`, a loop of its own, so
+  // that the one over whole tables keeps its scalar loads alone.
+  auto run = [&](auto left) {
+    // Union entries e (stage b0), e + 1 and e + 2 (in flight).
+    int q0 = 0, q1 = 0;
+    bool a0 = false, b0_ = false, a1 = false, b1_ = false;
+    bool h0 = next(left, q0, a0, b0_);
+    bool h1 = h0 && next(left, q1, a1, b1_);
+    if (h0) issue(q0, 0);
+    if (h1) issue(q1, 1);
+    int st = 0;
+    while (h0) {
+      int q2 = 0;
+      bool a2 = false, b2_ = false;
+      const bool h2 = h1 && next(left, q2, a2, b2_);
+      if (h1) {
+        wait_all_but_latest();
+      } else {
+        dma_wait();
+      }
+      // block q0 is staged (each wave waited for its own copies); every wave
+      // is done with the previous step, whose stage receives block q2
+      lds_barrier();
+      if (h2) issue(q2, st == 0 ? 2 : st - 1);
+      const bool act = wave_ok && (mineA ? a0 : b0_);
+      if (act) phase1(q0, st, st);
+      lds_barrier();  // the posted operands are visible
+      if (act) phase2(q0, st);
+      q0 = q1;
+      a0 = a1;
+      b0_ = b1_;
+      h0 = h1;
+      q1 = q2;
+      a1 = a2;
+      b1_ = b2_;
+      h1 = h2;
+      st = st == 2 ? 0 : st + 1;
     }
-    // block q0 is staged (each wave waited for its own copies); every wave
-    // is done with the previous step, whose stage receives block q2
-    lds_barrier();
-    if (h2) issue(q2, st == 0 ? 2 : st - 1);
-    const bool act = wave_ok && (mineA ? a0 : b0_);
-    if (act) phase1(q0, st, st);
-    lds_barrier();  // the posted operands are visible
-    if (act) phase2(q0, st);
-    q0 = q1;
-    a0 = a1;
-    b0_ = b1_;
-    h0 = h1;
-    q1 = q2;
-    a1 = a2;
-    b1_ = b2_;
-    h1 = h2;
-    st = st == 2 ? 0 : st + 1;
-  }
+  };
+  if (some)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
 
   if (!wave_ok) return;
   float* dK = a.dk + head;
@@ -492,6 +723,296 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
   }
 }
 
+// ----------------------------------------------- dK dV, listed query blocks
+
+// dK and dV of one key block from the entries of its listed query blocks.
+// The entries of up to LK_NT query blocks at a time are copied into LDS (at
+// most LK_CHUNK per round), sorted by key (counting sort, deterministic as in
+// prep_kernel), and dealt out in equal, consecutive shares to the groups of
+// lanes, whatever their keys: a key that many queries attend to is shared by
+// several groups.  A group adds up dV and dK of one key after another in
+// registers (p dO_i and dS Q_i, with dP = <dO_i, V_j> summed over its lanes).
+// The group in whose share a key starts owns it: groups whose share starts
+// inside a key post their part of it in LDS, and the owner adds the parts in
+// order.  Per entry this reads one row of dO and one of Q from L2.
+constexpr int LK_NT = 256;
+constexpr int LK_CHUNK = 2048;
+
+template <typename E, int D, int GK>
+__global__ __launch_bounds__(LK_NT, 2) void dkdv_lists_kernel(BwdArgs a) {
+  using R = RowGroup<E, D>;
+  constexpr int VPL = R::VPL, LPR = R::LPR, NG = LK_NT / LPR, W = LK_NT / 64;
+  __shared__ uint32_t code[LK_CHUNK];   // (query row << 6) | key
+  __shared__ float zv[LK_CHUNK];
+  __shared__ uint16_t order[LK_CHUNK];
+  __shared__ int cursor[W][BLK];
+  __shared__ int kstart[BLK + 1];
+  __shared__ int wsum[W];
+  __shared__ uint16_t run_qb[LK_NT], run_from[LK_NT], run_num[LK_NT];
+  __shared__ int run_at[LK_NT];
+  __shared__ __attribute__((aligned(16))) u32x4 vt[BLK * LPR];        // rows of V
+  __shared__ __attribute__((aligned(16))) float part[NG][2 * D];      // dV, dK of a share's leading key
+  const int t = threadIdx.x, lane = lane_id(), w = wave_id(), sub = lane % LPR, grp = t / LPR;
+  const int n = a.n, T = a.T;
+  int bh, kb;
+  head_major(blockIdx.x, a.BH, T, bh, kb);
+  const size_t head = (size_t)bh * n * D;
+  const E* Q = static_cast<const E*>(a.q) + head;
+  const E* V = static_cast<const E*>(a.v) + head;
+  const E* dO = static_cast<const E*>(a.dout) + head;
+  const float* del = a.delta + (size_t)bh * n;
+  const int k0 = kb * BLK;
+  const int32_t* list = a.k_index + ((size_t)bh * T + kb) * T;
+  const int cnt = a.k_count[(size_t)bh * T + kb];
+  const int32_t* used = a.buckets.used + (size_t)bh * T;
+
+  // whether the other dK/dV kernel wrote this key block (some query block of
+  // its list is not sorted): the first round then adds to it as the later
+  // ones do; if none is, nothing is left to do
+  bool other = false, any = false;
+  for (int e = t; e < cnt; e += LK_NT) {
+    const bool mine = (used[list[e]] & SORTED) != 0;
+    any |= mine;
+    other |= !mine;
+  }
+  bool add = __syncthreads_or(other);
+  if (add && !__syncthreads_or(any)) return;
+#pragma unroll
+  for (int r = grp; r < BLK; r += NG) vt[r * LPR + sub] = R::load(V, (uint32_t)min(k0 + r, n - 1));
+
+  // dK and dV of key kl, this lane's columns
+  auto put = [&](int kl, const float (&dv)[VPL], const float (&dk)[VPL]) {
+    if (k0 + kl >= n) return;
+    const size_t at = head + (size_t)(k0 + kl) * D + sub * VPL;
+#pragma unroll
+    for (int d = 0; d < VPL; d += 4) {
+      f32x4 x = {dv[d], dv[d + 1], dv[d + 2], dv[d + 3]};
+      f32x4 y = {a.scale * dk[d], a.scale * dk[d + 1], a.scale * dk[d + 2], a.scale * dk[d + 3]};
+      if (add) {
+        x += *reinterpret_cast<const f32x4*>(a.dv + at + d);
+        y += *reinterpret_cast<const f32x4*>(a.dk + at + d);
+      }
+      *reinterpret_cast<f32x4*>(a.dv + at + d) = x;
+      *reinterpret_cast<f32x4*>(a.dk + at + d) = y;
+    }
+  };
+
+  int e0 = 0;
+  do {
+    // The runs of this batch: query block, place in its buckets, length, and
+    // (run_at) the sum of the lengths before it.
+    const int e = e0 + t;
+    int qb = 0, from = 0, num = 0;
+    if (e < cnt) {
+      qb = list[e];
+      if (used[qb] & SORTED) {
+        const uint16_t* off = a.buckets.off + ((size_t)bh * T + qb) * (size_t)(T + 1) + kb;
+        from = off[0];
+        num = off[1] - from;
+      }
+    }
+    int incl = num;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o);
+      if (lane >= o) incl += v;
+    }
+    __syncthreads();  // wsum and the runs of the batch before have been read
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    int at = incl - num, total = 0;
+#pragma unroll
+    for (int x = 0; x < W; ++x) {
+      if (x < w) at += wsum[x];
+      total += wsum[x];
+    }
+    run_qb[t] = (uint16_t)qb;
+    run_from[t] = (uint16_t)from;
+    run_num[t] = (uint16_t)num;
+    run_at[t] = at;
+    __syncthreads();
+    // tp threads (a power of two) copy one run
+    const int runs = max(min(cnt - e0, LK_NT), 1);
+    int tp = 1;
+    while (2 * tp * runs <= LK_NT) tp *= 2;
+    const int run = t / tp;
+    int c0 = 0;  // entries [c0, c0 + LK_CHUNK) of the batch in this round
+    do {
+      const int M = min(total - c0, LK_CHUNK);
+      if (run < runs) {
+        const int rq = run_qb[run], ra = run_at[run], rn = min((int)run_num[run], c0 + LK_CHUNK - ra);
+        const size_t src = ((size_t)bh * T + rq) * LIST_ENTRIES + run_from[run];
+        constexpr int B = 4;
+        for (int x0 = max(0, c0 - ra) + t % tp; x0 < rn; x0 += B * tp) {
+          int cd[B];
+          float z[B];
+#pragma unroll
+          for (int u = 0; u < B; ++u) {
+            const int x = min(x0 + u * tp, rn - 1);
+            cd[u] = a.buckets.code[src + x];
+            z[u] = a.buckets.z[src + x];
+          }
+#pragma unroll
+          for (int u = 0; u < B; ++u) {
+            const int x = x0 + u * tp;
+            if (x < rn) {
+              code[ra + x - c0] = ((uint32_t)(rq * BLK + (cd[u] >> 6)) << 6) | (uint32_t)(cd[u] & 63);
+              zv[ra + x - c0] = z[u];
+            }
+          }
+        }
+      }
+      (&cursor[0][0])[t] = 0;  // W * BLK = LK_NT counters
+      __syncthreads();
+      // sort by key: wave w takes entries [w * q, (w + 1) * q)
+      const int q = (M + W - 1) / W, b0 = w * q, b1 = min(M, b0 + q);
+      for (int x = b0 + lane; x < b1; x += 64) atomicAdd(&cursor[w][code[x] & 63], 1);
+      __syncthreads();
+      if (w == 0) {
+        int s = 0;
+#pragma unroll
+        for (int x = 0; x < W; ++x) s += cursor[x][lane];
+        int in = s;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int v = __shfl_up(in, o);
+          if (lane >= o) in += v;
+        }
+        int p = in - s;
+        kstart[lane] = p;
+        if (lane == 63) kstart[BLK] = in;
+#pragma unroll
+        for (int x = 0; x < W; ++x) {
+          const int v = cursor[x][lane];
+          cursor[x][lane] = p;
+          p += v;
+        }
+      }
+      __syncthreads();
+      for (int x = b0; x < b1; x += 64) {
+        const bool ok = x + lane < b1;
+        const int key = ok ? (int)(code[x + lane] & 63u) : 0;
+        const unsigned long long m = same_key(key, 6, __ballot(ok));
+        if (ok) {
+          const int rank = lanes_below(m);
+          const int p = cursor[w][key] + rank;
+          if (rank == __popcll(m) - 1) cursor[w][key] = p + 1;
+          order[p] = (uint16_t)(x + lane);
+        }
+      }
+      __syncthreads();
+
+      // this group's share of the sorted entries
+      const int share = (M + NG - 1) / NG;
+      const int s0 = grp * share, s1 = min(M, s0 + share);
+      float dv[VPL] = {}, dk[VPL] = {};
+      int cur = -1;          // the key being added up
+      bool lead = false;     // it started in an earlier share
+      bool owe = false;      // after the loop: `cur` is this group's, unfinished
+      auto post_part = [&]() {
+#pragma unroll
+        for (int d = 0; d < VPL; ++d) {
+          part[grp][sub * VPL + d] = dv[d];
+          part[grp][D + sub * VPL + d] = dk[d];
+        }
+      };
+      // batches of U entries, the next one's rows in flight meanwhile (past
+      // the end of the share its last entry again)
+      constexpr int U = 4;
+      u32x4 ow[U], qw[U];
+      uint32_t cd[U];
+      float z[U], dl[U];
+      auto fetch = [&](int p0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int o = (int)order[max(min(p0 + u, s1 - 1), 0)];
+          cd[u] = code[o];
+          z[u] = zv[o];
+          ow[u] = R::load(dO, cd[u] >> 6);
+          qw[u] = R::load(Q, cd[u] >> 6);
+          dl[u] = del[cd[u] >> 6];
+        }
+      };
+      if (M > 0) fetch(s0);
+      for (int p0 = s0; __ballot(p0 < s1) != 0ull; p0 += U) {
+        u32x4 ow0[U], qw0[U];
+        uint32_t cd0[U];
+        float z0[U], dl0[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          ow0[u] = ow[u];
+          qw0[u] = qw[u];
+          cd0[u] = cd[u];
+          z0[u] = z[u];
+          dl0[u] = dl[u];
+        }
+        fetch(p0 + U);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (p0 + u < s1) {
+            const int kl = (int)(cd0[u] & 63u);
+            if (kl != cur) {
+              if (cur >= 0) {
+                if (lead)
+                  post_part();
+                else
+                  put(cur, dv, dk);
+              }
+              cur = kl;
+              lead = kstart[kl] < s0;
+#pragma unroll
+              for (int d = 0; d < VPL; ++d) dv[d] = dk[d] = 0.f;
+            }
+            float x[VPL], y[VPL];
+            R::unpack(ow0[u], x);
+            R::unpack(vt[kl * LPR + sub], y);
+            float dp = 0.f, pp, uu;
+#pragma unroll
+            for (int d = 0; d < VPL; ++d) dp = fmaf(x[d], y[d], dp);
+            dp = R::sum(dp);
+            Gamma<GK>::pu(z0[u], a.gamma, pp, uu);
+            const float ds = uu * (dp - dl0[u]);
+            R::unpack(qw0[u], y);
+#pragma unroll
+            for (int d = 0; d < VPL; ++d) {
+              dv[d] = fmaf(pp, x[d], dv[d]);
+              dk[d] = fmaf(ds, y[d], dk[d]);
+            }
+          }
+        }
+      }
+      if (cur >= 0) {
+        if (lead)
+          post_part();
+        else if (kstart[cur + 1] <= s1)
+          put(cur, dv, dk);
+        else
+          owe = true;
+      }
+      __syncthreads();
+      if (owe) {
+        for (int g = grp + 1; g * share < kstart[cur + 1]; ++g) {
+#pragma unroll
+          for (int d = 0; d < VPL; ++d) {
+            dv[d] += part[g][sub * VPL + d];
+            dk[d] += part[g][D + sub * VPL + d];
+          }
+        }
+        put(cur, dv, dk);
+      }
+      if (!add) {  // keys without entries
+        const float zero[VPL] = {};
+        for (int kl = grp; kl < BLK; kl += NG)
+          if (kstart[kl] == kstart[kl + 1]) put(kl, zero, zero);
+      }
+      add = true;
+      __syncthreads();
+      c0 += LK_CHUNK;
+    } while (c0 < total);
+    e0 += LK_NT;
+  } while (e0 < cnt);
+}
+
 // --------------------------------------------------------------------- dQ
 
 constexpr int DQ_NT = 256;
@@ -506,6 +1027,73 @@ constexpr int DQ_NT = 256;
 // against 0.531 at c = 16, 0.925 against 0.941 at alpha = 1.25, c = 1, 0.806
 // against 0.844 at alpha = 2, c = 1); at d = 64 that was slower (0.256
 // against 0.252 ms on B1 H8 n16384 causal).
+// dQ of a query block from its element lists (see gather_fwd): dP = <dO_i,
+// V_j> summed over a group's lanes, then dQ_i += dS K_j in registers.  Per
+// entry this reads one row of V and one of K from L2.
+template <typename E, int D, int GK>
+__device__ __forceinline__ void gather_dq(const BwdArgs& a, const ListBlock& lb, int bh, int qb) {
+  using R = RowGroup<E, D>;
+  constexpr int VPL = R::VPL, LPR = R::LPR, BATCH = 8;
+  const int lane = lane_id(), w = wave_id(), sub = lane % LPR;
+  const int n = a.n;
+  const size_t head = (size_t)bh * n * D;
+  const E* K = static_cast<const E*>(a.k) + head;
+  const E* V = static_cast<const E*>(a.v) + head;
+  const E* dO = static_cast<const E*>(a.dout) + head;
+  for (int r0 = w * R::GROUPS; r0 < BLK; r0 += 4 * R::GROUPS) {
+    const int row = r0 + lane / LPR, i = qb * BLK + row;
+    const int c0 = lb.count[row], cnt = c0 + lb.count[64 + row];
+    const uint32_t ir = (uint32_t)min(i, n - 1);
+    const float del = a.delta[(size_t)bh * n + ir];
+    float go[VPL], acc[VPL] = {};
+    R::unpack(R::load(dO, ir), go);
+    for (int base = 0; __ballot(base < cnt) != 0ull; base += LPR) {
+      float z = 0.f;
+      int key = 0;
+      if (cnt > 0) {
+        const int e = min(base + sub, cnt - 1);
+        const int at = e < c0 ? LIST_IDS * e + row : LIST_IDS * (e - c0) + 64 + row;
+        key = lb.key[at];
+        if (base + sub < cnt) z = lb.z[at];
+      }
+#pragma unroll
+      for (int u0 = 0; u0 < LPR; u0 += BATCH) {
+        if (u0 > 0 && __ballot(base + u0 < cnt) == 0ull) break;
+        u32x4 vw[BATCH], kw[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          const uint32_t j = (uint32_t)R::from(key, u0 + u);
+          vw[u] = R::load(V, j);
+          kw[u] = R::load(K, j);
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          float x[VPL], dp = 0.f, p, ue;
+          R::unpack(vw[u], x);
+#pragma unroll
+          for (int d = 0; d < VPL; ++d) dp = fmaf(go[d], x[d], dp);
+          dp = R::sum(dp);
+          Gamma<GK>::pu(R::from(z, u0 + u), a.gamma, p, ue);
+          // (nothing from the repeated entries past the end, whatever dP is)
+          const float ds = ue > 0.f ? ue * (dp - del) : 0.f;
+          R::unpack(kw[u], x);
+#pragma unroll
+          for (int d = 0; d < VPL; ++d) acc[d] = fmaf(ds, x[d], acc[d]);
+        }
+      }
+    }
+    if (i >= n) continue;
+    float* dQ = a.dq + head + (size_t)i * D + sub * VPL;
+#pragma unroll
+    for (int d = 0; d < VPL; d += 4) {
+      f32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = cnt > 0 ? a.scale * acc[d + e] : 0.f;
+      *reinterpret_cast<f32x4*>(dQ + d) = o;
+    }
+  }
+}
+
 template <typename E, int D, int GK>
 __global__ __launch_bounds__(DQ_NT, 2) void dq_kernel(BwdArgs a) {
   using TL = Tile<E, D>;
@@ -520,9 +1108,14 @@ __global__ __launch_bounds__(DQ_NT, 2) void dq_kernel(BwdArgs a) {
   const int lane = lane_id(), w = wave_id();
   const int qh = w & 1, kh = w >> 1;
   const int n = a.n, T = a.T;
-  const int bh = blockIdx.x % a.BH;
+  int bh = blockIdx.x % a.BH;
   int qb = blockIdx.x / a.BH;
+  if (a.lists) head_major(blockIdx.x, a.BH, T, bh, qb);
   if (a.causal) qb = T - 1 - qb;  // longest lists first
+  if (a.lists && (a.buckets.used[(size_t)bh * T + qb] & LISTED)) {
+    gather_dq<E, D, GK>(a, a.lists[(size_t)bh * T + qb], bh, qb);
+    return;
+  }
   const int q0 = qb * BLK + 32 * qh;
   const int i = q0 + (lane & 31);
   const bool wave_ok = q0 < n;
@@ -682,7 +1275,18 @@ hipError_t launch_dq_d(const BwdArgs& a, hipStream_t s) {
 }
 
 template <typename E, int D>
+hipError_t launch_dkdv_lists_d(const BwdArgs& a, hipStream_t s) {
+  dim3 grid((unsigned)(a.BH * a.T)), block(LK_NT);
+  auto kernel = dkdv_lists_kernel<E, D, 0>;
+  if (a.gk == 1) kernel = dkdv_lists_kernel<E, D, 1>;
+  if (a.gk == 2) kernel = dkdv_lists_kernel<E, D, 2>;
+  if (a.gk == 4) kernel = dkdv_lists_kernel<E, D, 4>;
+  return launch_kernel(kernel, grid, block, s, a);
+}
+
+template <typename E, int D>
 hipError_t launch_delta_d(const DeltaArgs& a, hipStream_t s) {
+  if (a.lists) return launch_kernel(prep_kernel<E, D>, dim3((unsigned)(a.BH * a.T)), dim3(PREP_NT), s, a);
   dim3 grid((unsigned)((a.rows + 15) / 16)), block(256);
   return launch_kernel(delta_kernel<E, D>, grid, block, s, a);
 }
@@ -697,6 +1301,12 @@ hipError_t launch_delta(const DeltaArgs& a, int dtype, int head_dim, hipStream_t
 hipError_t launch_bwd_dkdv(const BwdArgs& a, int dtype, int head_dim, hipStream_t s) {
   if (dtype == 0) return head_dim == 64 ? launch_dkdv_d<__bf16, 64>(a, s) : launch_dkdv_d<__bf16, 128>(a, s);
   return head_dim == 64 ? launch_dkdv_d<float, 64>(a, s) : launch_dkdv_d<float, 128>(a, s);
+}
+
+hipError_t launch_bwd_dkdv_lists(const BwdArgs& a, int dtype, int head_dim, hipStream_t s) {
+  if (dtype == 0)
+    return head_dim == 64 ? launch_dkdv_lists_d<__bf16, 64>(a, s) : launch_dkdv_lists_d<__bf16, 128>(a, s);
+  return head_dim == 64 ? launch_dkdv_lists_d<float, 64>(a, s) : launch_dkdv_lists_d<float, 128>(a, s);
 }
 
 hipError_t launch_bwd_dq(const BwdArgs& a, int dtype, int head_dim, hipStream_t s) {

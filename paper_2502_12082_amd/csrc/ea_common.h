@@ -473,4 +473,69 @@ struct Gamma {
   }
 };
 
+// ---------------------------------------------------------- element lists
+//
+// A gather takes one listed entry at a time: a group of LPR lanes holds one
+// row of a [*, D] operand, 16 bytes per lane, so that a wave works on 64 / LPR
+// rows (or entries) at once and every operand row is one coalesced access.
+template <typename E, int D>
+struct RowGroup {
+  static constexpr int VPL = 16 / (int)sizeof(E);  // elements per lane
+  static constexpr int LPR = D / VPL;              // lanes per row: 8, 16 or 32
+  static constexpr int GROUPS = 64 / LPR;          // rows per wave
+
+  __device__ __forceinline__ static u32x4 load(const E* base, uint32_t row) {
+    const uint32_t off = row * (uint32_t)(D * sizeof(E)) + (uint32_t)(lane_id() % LPR) * 16u;
+    return *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(base) + off);
+  }
+  __device__ __forceinline__ static void unpack(const u32x4& w, float (&x)[VPL]) {
+    if constexpr (VPL == 8) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[2 * i] = __uint_as_float(w[i] << 16);
+        x[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = __uint_as_float(w[i]);
+    }
+  }
+  // v of lane u of the calling lane's group
+  template <typename T>
+  __device__ __forceinline__ static T from(T v, int u) {
+    return __shfl(v, u, LPR);
+  }
+  // Sum of v over the group, in all its lanes (lanes exchange inside quads,
+  // then mirrored inside 8 and 16 lanes).
+  __device__ __forceinline__ static float sum(float v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    auto dpp = [](float x, auto ctrl) {
+      return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), decltype(ctrl)::value,
+                                                                  0xf, 0xf, true));
+    };
+    v += dpp(v, std::integral_constant<int, 0xB1>{});   // quad_perm 1, 0, 3, 2
+    v += dpp(v, std::integral_constant<int, 0x4E>{});   // quad_perm 2, 3, 0, 1
+    v += dpp(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+    if constexpr (LPR >= 16) v += dpp(v, std::integral_constant<int, 0x140>{});  // row_mirror
+#endif
+    if constexpr (LPR >= 32) v += __shfl_xor(v, 16);
+    return v;
+  }
+};
+
+// Block of a grid over B * H heads of T blocks each, workgroups being handed
+// to the eight XCDs in turn: with a multiple of eight heads, each XCD works
+// through its heads one after another, so that its L2 holds the operands of
+// one head; otherwise head by head over the whole chip.
+__device__ __forceinline__ void head_major(int b, int BH, int T, int& bh, int& blk) {
+  if (BH % 8 == 0) {
+    const int s = b >> 3;
+    bh = (b & 7) + 8 * (s / T);
+    blk = s % T;
+  } else {
+    bh = b / T;
+    blk = b % T;
+  }
+}
+
 }  // namespace ea

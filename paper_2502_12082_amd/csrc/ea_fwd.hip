@@ -59,6 +59,76 @@ __device__ void column_table(const FwdArgs& a, int col) {
   if (lane == 0) a.k_count[col] = listed;
 }
 
+// ------------------------------------------------- listed query blocks
+
+// O (and O2) of a query block from its element lists: RowGroup::GROUPS rows
+// of a wave at once, each group of lanes adding up p V_j (and u V_j) over its
+// row's entries in registers.  Per entry this reads one row of V from L2 and
+// takes about D / 8 VALU operations in place of the block products.
+template <typename E, int D, int GK, bool TRAIN>
+__device__ __forceinline__ void gather_fwd(const FwdArgs& a, const ListBlock& lb, int bh, int qb) {
+  using R = RowGroup<E, D>;
+  constexpr int VPL = R::VPL, LPR = R::LPR, BATCH = LPR < 16 ? LPR : 16;
+  const int lane = lane_id(), w = wave_id(), sub = lane % LPR;
+  const int n = a.n;
+  const size_t head = (size_t)bh * n * D;
+  const E* V = static_cast<const E*>(a.v) + head;
+  for (int r0 = w * R::GROUPS; r0 < BLK; r0 += 4 * R::GROUPS) {
+    const int row = r0 + lane / LPR, i = qb * BLK + row;
+    const int c0 = lb.count[row], cnt = c0 + lb.count[64 + row];
+    float o[VPL] = {}, o2[VPL] = {}, usum = 0.f;
+    for (int base = 0; __ballot(base < cnt) != 0ull; base += LPR) {
+      // lane `sub` of a group fetches the row's entry base + sub; past the
+      // end the last one again, with z = 0
+      float z = 0.f;
+      int key = 0;
+      if (cnt > 0) {
+        const int e = min(base + sub, cnt - 1);
+        const int at = e < c0 ? LIST_IDS * e + row : LIST_IDS * (e - c0) + 64 + row;
+        key = lb.key[at];
+        if (base + sub < cnt) z = lb.z[at];
+      }
+#pragma unroll
+      for (int u0 = 0; u0 < LPR; u0 += BATCH) {
+        if (u0 > 0 && __ballot(base + u0 < cnt) == 0ull) break;
+        u32x4 v[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) v[u] = R::load(V, (uint32_t)R::from(key, u0 + u));
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          float x[VPL], p, ue;
+          R::unpack(v[u], x);
+          Gamma<GK>::pu(R::from(z, u0 + u), a.gamma, p, ue);
+          usum += ue;
+#pragma unroll
+          for (int d = 0; d < VPL; ++d) {
+            o[d] = fmaf(p, x[d], o[d]);
+            if constexpr (TRAIN) o2[d] = fmaf(ue, x[d], o2[d]);
+          }
+        }
+      }
+    }
+    if (i >= n) continue;
+    const size_t off = head + (size_t)i * D + sub * VPL;
+    E* O = static_cast<E*>(a.o) + off;
+    const bool any = cnt > 0;  // (a row without entries read row 0 of V)
+    E ov[VPL];
+#pragma unroll
+    for (int d = 0; d < VPL; ++d) ov[d] = (E)(any ? o[d] : 0.f);
+    *reinterpret_cast<u32x4*>(O) = *reinterpret_cast<const u32x4*>(ov);
+    if constexpr (TRAIN) {
+      float* O2 = a.o2 + off;
+#pragma unroll
+      for (int d = 0; d < VPL; d += 4) {
+        f32x4 t;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = any && usum > 0.f ? o2[d + e] / usum : 0.f;
+        *reinterpret_cast<f32x4*>(O2 + d) = t;
+      }
+    }
+  }
+}
+
 // --------------------------------------------------------------- forward
 
 constexpr int FWD_NT = 256;
@@ -96,9 +166,14 @@ __global__ __launch_bounds__(FWD_NT, !TRAIN && D == 64 && sizeof(E) == 2 ? 4 : 2
   const int lane = lane_id(), w = wave_id();
   const int qh = w & 1, kh = w >> 1;
   const int n = a.n, T = a.T;
-  const int bh = blockIdx.x % a.BH;
+  int bh = blockIdx.x % a.BH;
   int qb = blockIdx.x / a.BH;
+  if (a.lists) head_major(blockIdx.x, a.BH, T, bh, qb);
   if (a.causal) qb = T - 1 - qb;  // longest lists first
+  if (a.lists && a.lists[(size_t)bh * T + qb].used) {
+    gather_fwd<E, D, GK, TRAIN>(a, a.lists[(size_t)bh * T + qb], bh, qb);
+    return;
+  }
   const int q0 = qb * BLK + 32 * qh;
   const int i = q0 + (lane & 31);
   const bool wave_ok = q0 < n;

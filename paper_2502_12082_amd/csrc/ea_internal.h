@@ -46,6 +46,32 @@ constexpr size_t solve_slot_bytes(int cap) {
 }
 static_assert(MAX_SEQLEN / 4 <= 65536, "a quad's key fits 16 bits");
 
+// Element lists: the nonzero probabilities of every row of a 64-row query
+// block, written by the masked path's solver where they are few, and read by
+// the forward and backward instead of recomputing the scores of whole blocks.
+// Each row has two lists of up to LIST_CAP entries (the keys that each half
+// of the solver's wave held for it): z = [x - tau]_+ and the 16-bit key, entry
+// e of list id = 64 * half + row at index LIST_IDS * e + id.  One record per
+// query block:
+constexpr int LIST_CAP = 48;
+constexpr int LIST_IDS = 2 * 64;
+constexpr int LIST_ENTRIES = LIST_CAP * LIST_IDS;  // at most, per query block
+constexpr int LIST_MAX_SEQLEN = 65536;             // keys fit 16 bits
+struct ListBlock {
+  float z[LIST_ENTRIES];
+  uint16_t key[LIST_ENTRIES];
+  uint8_t count[LIST_IDS];
+  float tau[64];  // the thresholds the z belong to
+  int32_t used;   // 1: the lists hold every nonzero probability of the block
+  int32_t pad[31];
+};
+static_assert(sizeof(ListBlock) % 128 == 0, "records keep their alignment");
+// A block is listed if it has at most LIST_PER_BLOCK entries per listed key
+// block (of 64 x 64 scores), or at most LIST_FEW in all: beyond that the
+// matrix products of whole blocks are faster than a gather per entry.
+constexpr int LIST_PER_BLOCK = 100;
+constexpr int LIST_FEW = 1024;
+
 struct TauArgs {
   const void* q;
   const void* k;
@@ -76,6 +102,7 @@ struct TauArgs {
   // written with it
   int32_t* q_count;   // [BH, T]
   int32_t* q_index;   // [BH, T, T]
+  ListBlock* lists;   // [BH * T] (masked path, n <= LIST_MAX_SEQLEN), or null
 };
 
 struct FwdArgs {
@@ -98,6 +125,17 @@ struct FwdArgs {
   const uint8_t* mask;  // [BH, T, T]
   int32_t* k_count;     // [BH, T]
   int32_t* k_index;     // [BH, T, T]
+  const ListBlock* lists;  // [BH * T], or null
+};
+
+// The element lists of a query block in the backward, sorted by key block:
+// entry p of bucket J at off[J] + p (off: [T + 1] per query block), with its
+// row and key within their blocks (row * 64 + key).
+struct Buckets {
+  int32_t* used;   // [BH * T]: whether the block's lists serve dQ, and its buckets dK and dV
+  uint16_t* off;   // [BH * T, T + 1]
+  float* z;        // [BH * T, LIST_ENTRIES]
+  uint16_t* code;  // [BH * T, LIST_ENTRIES]
 };
 
 struct BwdArgs {
@@ -118,6 +156,8 @@ struct BwdArgs {
   int gk;
   const float* tau_lo;  // fp32 inputs, general alpha: low part of tau (or null: 0)
   double c64, g64;
+  const ListBlock* lists;  // [BH * T], or null; then also
+  Buckets buckets;
 };
 
 struct DeltaArgs {
@@ -125,6 +165,11 @@ struct DeltaArgs {
   const float* o2;
   float* delta;
   int64_t rows;
+  // with element lists: their buckets are written too
+  const ListBlock* lists;  // [BH * T], or null
+  const float* tau;
+  Buckets buckets;
+  int BH, n, T;
 };
 
 // Row-wise alpha-entmax of a materialized [rows, n] score matrix.
@@ -164,6 +209,9 @@ hipError_t launch_tau_fused(const TauArgs& a, int dtype, int head_dim, hipStream
 hipError_t launch_fwd(const FwdArgs& a, int dtype, int head_dim, bool train, hipStream_t s);
 hipError_t launch_delta(const DeltaArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dkdv(const BwdArgs& a, int dtype, int head_dim, hipStream_t s);
+// dK and dV of the listed query blocks, added to what launch_bwd_dkdv (given
+// the same lists) wrote for the others.
+hipError_t launch_bwd_dkdv_lists(const BwdArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dq(const BwdArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_rows_fwd(const RowsArgs& a, int dtype, hipStream_t s);
 hipError_t launch_rows_bwd(const RowsArgs& a, int dtype, hipStream_t s);

@@ -667,11 +667,13 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   //  - quads, as pass 0 collects them: a quad array (16 bytes per entry)
   //    and its key array (2 bytes);
   //  - compacted singles, written by the first cached evaluation from the
-  //    quads: a score array (4 bytes) and its key-block array (2 bytes)
+  //    quads: a score array (4 bytes) and its key array (2 bytes: the key,
+  //    or its key block where keys take more than 16 bits, see kshift)
   //    after the quad arrays, so that the later evaluations read 4 bytes
   //    per score and the quads stay intact;
   //  - singles of a later fill (CandEntry, 8 bytes), up to `scap` per list
   //    over the whole slot.
+  const int kshift = n > LIST_MAX_SEQLEN ? 6 : 0;
   const int tile = a.tile0 + (int)blockIdx.x;
   char* const slot = a.cand && (int)blockIdx.x < a.slots
                          ? static_cast<char*>(a.cand) + (size_t)blockIdx.x * (solve_slot_bytes(a.cap) / 2 * G)
@@ -1015,7 +1017,8 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
           if (e0 + u < ns[gq]) use(gq, v[gq][u]);
     }
   };
-  // The compacted singles of list gq with their key blocks: use(score, kb).
+  // The compacted singles of list gq with their keys (the first key of the
+  // key block where kshift is 6): use(score, key).
   auto scan_compact = [&](int gq, auto&& use) {
     for (int e0 = 0; e0 < nsmax[gq]; e0 += 8) {
       float v[8];
@@ -1028,7 +1031,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (e0 + u < ns[gq]) use(v[u], kv[u]);
+        if (e0 + u < ns[gq]) use(v[u], kv[u] << kshift);
     }
   };
   // The quads of both lists with their keys: use(gq, quad, key).
@@ -1495,7 +1498,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
           // (__float_as_uint of a named float: a bit cast of the vector
           // element itself stored element 0 for every i)
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rs, off, 0, 0);
-          __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(key4 >> 4), rk, off >> 1, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b16((uint16_t)((4 * key4 + i) >> kshift), rk, off >> 1, 0, 0);
           cs[gq] += keep ? 1 : 0;
         }
       });
@@ -1566,6 +1569,31 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     }
     if (stop) break;
   }
+
+  // An entry of row group gq with z = [x - tau]_+ at the returned tau: sets
+  // its key block's mask bit and, where element lists are wanted, appends it
+  // to this lane's list of the row (LIST_CAP entries; lc counts on).
+  __shared__ int lsum[SV_WAVES];
+  if (lane == 0 && writer) lsum[qbl] = 0;
+  __syncthreads();
+  // (rows with half as many candidates again as a list holds are not tried)
+  const bool listable = cached && __ballot(any_over(lists == 1 ? ns : cc, LIST_CAP * 3 / 2)) == 0ull;
+  ListBlock* const lb = a.lists && listable && qb < T ? a.lists + ((size_t)bh * T + qb) : nullptr;
+  int lc[G] = {};
+  auto list_id = [&](int gq) { return 64 * (lane >> 5) + (q0 - qb * BLK) + 32 * gq + (lane & 31); };
+  auto emit = [&](int gq, float zp, int key) {
+    if (!(zp > 0.f)) return;
+    const int kv = key >> 6;
+    atomicOr(&bits[qbl * BW + (kv >> 5)], 1u << (kv & 31));
+    if (lb) {
+      if (lc[gq] < LIST_CAP) {
+        const int at = LIST_IDS * lc[gq] + list_id(gq);
+        lb->z[at] = zp;
+        lb->key[at] = (uint16_t)key;
+      }
+      ++lc[gq];
+    }
+  };
 
   if constexpr (precise_path<E, GK>()) {
     // ---- fp32 inputs, general alpha (ea_common.h): tau refined in fp64 and
@@ -1654,10 +1682,10 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     visit([&](int gq, float sv, int jv) {
       if (!row_ok[gq]) return;
       const float raw = fmaf(c, sv, -tau[gq]);
-      if (raw >= band[gq] || z64(gq, sv, jv) > 0.0) {
-        const int kv = jv >> 6;
-        atomicOr(&bits[qbl * BW + (kv >> 5)], 1u << (kv & 31));
-      }
+      if (raw >= band[gq])
+        emit(gq, __builtin_amdgcn_fmed3f(fmaf(c, sv, -(float)t64[gq]), 0.f, 1.f), jv);
+      else
+        emit(gq, (float)fmin(fmax(z64(gq, sv, jv), 0.0), 1.0), jv);
     });
   } else {
     if (lane < 32) {
@@ -1675,29 +1703,32 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
 #pragma unroll
       for (int gq = 0; gq < G; ++gq) {
         if (lists == 2) {
-          scan_singles(gq, [&](float sv, int jv) {
-            const int kv = jv >> 6;
-            if (in_support(relu_z(c, sv, tau[gq]))) atomicOr(&bits[qbl * BW + (kv >> 5)], 1u << (kv & 31));
-          });
-          continue;
-        }
-        if (lists == 1) {
-          scan_compact(gq, [&](float sv, int kv) {
-            if (in_support(relu_z(c, sv, tau[gq]))) atomicOr(&bits[qbl * BW + (kv >> 5)], 1u << (kv & 31));
-          });
-          continue;
-        }
-        scan_quads(gq, [&](const f32x4& v, int key4) {
-          bool any = false;
+          scan_singles(gq, [&](float sv, int jv) { emit(gq, relu_z(c, sv, tau[gq]), jv); });
+        } else if (lists == 1) {
+          scan_compact(gq, [&](float sv, int jv) { emit(gq, relu_z(c, sv, tau[gq]), jv); });
+        } else {
+          scan_quads(gq, [&](const f32x4& v, int key4) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) any |= in_support(relu_z(c, v[i], tau[gq])) != 0;
-          if (any) {
-            const int kv = key4 >> 4;  // key block of the quad
-            atomicOr(&bits[qbl * BW + (kv >> 5)], 1u << (kv & 31));
-          }
-        });
+            for (int i = 0; i < 4; ++i) emit(gq, relu_z(c, v[i], tau[gq]), 4 * key4 + i);
+          });
+        }
       }
     }
+  }
+  if (lb) {
+    // the lists' counts and thresholds; lsum[qbl] sums up their entries
+    int total = 0;
+#pragma unroll
+    for (int gq = 0; gq < G; ++gq) {
+      lb->count[list_id(gq)] = (uint8_t)min(lc[gq], LIST_CAP);
+      if (lane < 32 && row_ok[gq]) lb->tau[list_id(gq)] = a.tau[(size_t)bh * n + qi[gq]];
+      total += lc[gq] > LIST_CAP ? LIST_ENTRIES + 1 : lc[gq];
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
+    if (lane == 0) atomicAdd(&lsum[qbl], total);
+  } else if (lane == 0) {
+    atomicAdd(&lsum[qbl], LIST_ENTRIES + 1);
   }
   __syncthreads();
   if (!wave_ok || !writer) return;
@@ -1714,6 +1745,8 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     listed += __popcll(m);
   }
   if (lane == 0) a.q_count[(size_t)bh * T + qb] = listed;
+  if (a.lists && lane == 0)
+    a.lists[(size_t)bh * T + qb].used = cached && lsum[qbl] <= min(max(LIST_PER_BLOCK * listed, LIST_FEW), LIST_ENTRIES);
   if (a.stats && lane == 0) {
     a.stats[(size_t)bh * T + qb] = passes;
     a.stats[((size_t)a.BH + bh) * T + qb] = evals;
