@@ -1576,8 +1576,11 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   __shared__ int lsum[SV_WAVES];
   if (lane == 0 && writer) lsum[qbl] = 0;
   __syncthreads();
-  // (rows with half as many candidates again as a list holds are not tried)
-  const bool listable = cached && __ballot(any_over(lists == 1 ? ns : cc, LIST_CAP * 3 / 2)) == 0ull;
+  // (not tried where many rows hold half as many candidates again as a list
+  // takes; a few such rows may still fit, and one block that is not listed
+  // among many that are keeps the launches of the later kernels waiting for it)
+  const bool listable =
+      cached && __popcll(__ballot(any_over(lists == 1 ? ns : cc, LIST_CAP * 3 / 2))) <= 8;
   ListBlock* const lb = a.lists && listable && qb < T ? a.lists + ((size_t)bh * T + qb) : nullptr;
   int lc[G] = {};
   auto list_id = [&](int gq) { return 64 * (lane >> 5) + (q0 - qb * BLK) + 32 * gq + (lane & 31); };
