@@ -117,13 +117,13 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
   const int T = a.T;
   bool same = true;
   if (t < nr) same = __float_as_uint(lb.tau[t]) == __float_as_uint(a.tau[row0 + t]);
-  const bool used = __syncthreads_and(same && lb.used == 1);
+  const bool used = __syncthreads_and(same && lb.used >= LIST_DQ);
   // The dK/dV work of a head is split only if most of its blocks are listed:
   // its other blocks cost a pass of their own over every key block.
   int listed = 0;
   for (int x0 = 0; x0 < T; x0 += PREP_NT)
-    listed += __syncthreads_count(x0 + t < T && a.lists[(size_t)bh * T + min(x0 + t, T - 1)].used == 1);
-  const bool sorted = used && 4 * listed >= 3 * T;
+    listed += __syncthreads_count(x0 + t < T && a.lists[(size_t)bh * T + min(x0 + t, T - 1)].used == LIST_DKDV);
+  const bool sorted = used && lb.used == LIST_DKDV && 4 * listed >= 3 * T;
   if (t == 0) a.buckets.used[blk] = sorted ? LISTED | SORTED : used ? LISTED : 0;
   if (!sorted) return;
 
@@ -229,6 +229,18 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
 
 // ------------------------------------------------------------------ dK dV
 
+// The number of a head's T query blocks that are sorted for the list kernel.
+// Every thread of the workgroup.
+template <int NT>
+__device__ __forceinline__ int sorted_blocks(const int32_t* used, int T) {
+  int sorted = 0;
+  for (int x0 = 0; x0 < T; x0 += NT) {
+    const int x = x0 + (int)threadIdx.x;
+    sorted += __syncthreads_count(x < T && (used[min(x, T - 1)] & SORTED) != 0);
+  }
+  return __builtin_amdgcn_readfirstlane(sorted);
+}
+
 // The query blocks of list[0 .. cnt) that have no element lists, in order, in
 // out (in LDS); returns their number.  Every thread of the workgroup.
 template <int NT>
@@ -292,12 +304,12 @@ __global__ __launch_bounds__(BWD_NT) void dkdv_kernel(BwdArgs a) {
   const int32_t* list = dense ? nullptr : a.k_index + ((size_t)bh * T + kb) * T;
   int cnt = dense ? (a.causal ? T - kb : T) : a.k_count[(size_t)bh * T + kb];
   __shared__ uint16_t unlisted[LIST_MAX_SEQLEN / BLK];
-  bool some = a.lists != nullptr;
+  const int sorted = a.lists ? sorted_blocks<BWD_NT>(a.buckets.used + (size_t)bh * T, T) : 0;
+  if (a.lists && sorted == T) return;
+  const bool some = sorted > 0;
   if (some) {
-    const int left = unlisted_blocks<BWD_NT>(list, cnt, a.buckets.used + (size_t)bh * T, unlisted);
-    if (left == 0) return;
-    some = left != cnt;  // where every block is left, the table serves as it is
-    cnt = left;
+    cnt = unlisted_blocks<BWD_NT>(list, cnt, a.buckets.used + (size_t)bh * T, unlisted);
+    if (cnt == 0) return;
   }
   auto qb_of = [&](int e) { return dense ? (a.causal ? kb + e : e) : some ? (int)unlisted[e] : list[e]; };
 
@@ -497,7 +509,9 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
   const ci32* kcount = (const ci32*)a.k_count;
   const ci32* kindex = (const ci32*)a.k_index;
   __shared__ uint16_t unlisted[2][LIST_MAX_SEQLEN / BLK];
-  bool some = a.lists != nullptr;
+  const int sorted = a.lists ? sorted_blocks<BWD2_NT>(a.buckets.used + (size_t)bh * T, T) : 0;
+  if (a.lists && sorted == T) return;
+  const bool some = sorted > 0;
   auto count_of = [&](int kb) {
     if (kb >= T) return 0;
     return dense ? (a.causal ? T - kb : T) : kcount[(size_t)bh * T + kb];
@@ -511,14 +525,12 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
   // With element lists, only the query blocks without them (see dkdv_kernel).
   if (some) {
     const int32_t* used = a.buckets.used + (size_t)bh * T;
-    const int tA = nA, tB = nB;
     nA = unlisted_blocks<BWD2_NT>(a.k_index + ((size_t)bh * T + kbA) * T, nA, used, unlisted[0]);
     nB = unlisted_blocks<BWD2_NT>(a.k_index + ((size_t)bh * T + min(kbB, T - 1)) * T, nB, used, unlisted[1]);
     if (nA == 0 && nB == 0) return;
     // (scalar registers: they steer the loop below)
     nA = __builtin_amdgcn_readfirstlane(nA);
     nB = __builtin_amdgcn_readfirstlane(nB);
-    some = nA != tA || nB != tB;  // where every block is left, the tables serve as they are
   }
   // the next query block of the union, and whether each key block lists it
   auto next = [&](auto left, int& qb, bool& inA, bool& inB) {
@@ -766,17 +778,17 @@ __global__ __launch_bounds__(LK_NT, 2) void dkdv_lists_kernel(BwdArgs a) {
   const int cnt = a.k_count[(size_t)bh * T + kb];
   const int32_t* used = a.buckets.used + (size_t)bh * T;
 
+  const int sorted = sorted_blocks<LK_NT>(used, T);
+  if (sorted == 0) return;
   // whether the other dK/dV kernel wrote this key block (some query block of
   // its list is not sorted): the first round then adds to it as the later
-  // ones do; if none is, nothing is left to do
-  bool other = false, any = false;
-  for (int e = t; e < cnt; e += LK_NT) {
-    const bool mine = (used[list[e]] & SORTED) != 0;
-    any |= mine;
-    other |= !mine;
+  // ones do
+  bool add = false;
+  if (sorted < T) {
+    bool other = false;
+    for (int e = t; e < cnt; e += LK_NT) other |= !(used[list[e]] & SORTED);
+    add = __syncthreads_or(other);
   }
-  bool add = __syncthreads_or(other);
-  if (add && !__syncthreads_or(any)) return;
 #pragma unroll
   for (int r = grp; r < BLK; r += NG) vt[r * LPR + sub] = R::load(V, (uint32_t)min(k0 + r, n - 1));
 

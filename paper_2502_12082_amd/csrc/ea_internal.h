@@ -62,15 +62,29 @@ struct ListBlock {
   uint16_t key[LIST_ENTRIES];
   uint8_t count[LIST_IDS];
   float tau[64];  // the thresholds the z belong to
-  int32_t used;   // 1: the lists hold every nonzero probability of the block
+  int32_t used;   // ListUse: 0, or the lists hold every nonzero probability of the block
   int32_t pad[31];
 };
 static_assert(sizeof(ListBlock) % 128 == 0, "records keep their alignment");
-// A block is listed if it has at most LIST_PER_BLOCK entries per listed key
-// block (of 64 x 64 scores), or at most LIST_FEW in all: beyond that the
-// matrix products of whole blocks are faster than a gather per entry.
-constexpr int LIST_PER_BLOCK = 100;
-constexpr int LIST_FEW = 1024;
+// What a block's lists serve, by its entries per listed key block (64 x 64
+// scores): beyond these limits the matrix products of whole blocks are faster
+// than a gather per entry (bf16, us at B8 H12 n1024 d64 c = 1, 76 entries per
+// block: forward 33 against 67, dQ 43 against 58, dK/dV with the sort 101
+// against 97; at 512 per block, B64 H16 n128: 34 against 33, 42 against 28, 103
+// against 42).  fp32 products take 16 times as long, but a listed entry twice
+// the bytes: four times the limits (B8 H16 n512 d64, 136 per block: forward 31
+// against 124, dQ 41 against 127).  Among many key blocks a few entries are always
+// listed (the first rows of a causal head), since one block that is not makes
+// the whole head take both ways.
+enum ListUse { LIST_NONE = 0, LIST_FWD = 1, LIST_DQ = 2, LIST_DKDV = 3 };
+#if defined(__HIPCC__)
+__host__ __device__ inline int list_use(int entries, int blocks, int T, bool f32) {
+  const int per = f32 ? 4 * blocks : blocks, few = 32 * T < 1024 ? 32 * T : 1024;
+  if (entries > LIST_ENTRIES) return LIST_NONE;
+  if (entries <= few || entries <= 64 * per) return LIST_DKDV;
+  return entries <= 100 * per ? LIST_DQ : entries <= 150 * per ? LIST_FWD : LIST_NONE;
+}
+#endif
 
 struct TauArgs {
   const void* q;
@@ -200,6 +214,10 @@ inline hipError_t launch_kernel(void (*kernel)(A), dim3 grid, dim3 block, hipStr
 }
 
 hipError_t launch_tau(const TauArgs& a, int dtype, int head_dim, hipStream_t s);
+// The solver for sequences of up to SMALL_MAX_N keys, but fp32 inputs with a
+// general alpha (no candidate cache, no K passes beyond the first).
+constexpr int SMALL_MAX_N = 1024;
+hipError_t launch_tau_small(const TauArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_tau_bf16_64(const TauArgs& a, hipStream_t s);
 hipError_t launch_tau_bf16_128(const TauArgs& a, hipStream_t s);
 hipError_t launch_tau_f32_64(const TauArgs& a, hipStream_t s);

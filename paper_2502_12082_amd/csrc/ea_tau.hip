@@ -1294,7 +1294,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
       lo[gq] = fminf(b - 4e-6f * fmaxf(1.f, fabsf(b)), hi[gq]);
       // the lists hold no score at or below a bound that refine() took
       lo[gq] = fmaxf(lo[gq], fminf(xb[gq] - 4e-6f * fmaxf(1.f, fabsf(xb[gq])), hi[gq]));
-      tau[gq] = 0.5f * (lo[gq] + hi[gq]);
+      tau[gq] = fminf(fmaxf(b, xb[gq]), hi[gq]);  // the bound itself
     }
   }
 
@@ -1308,6 +1308,18 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
 #pragma unroll
     for (int gq = 0; gq < G; ++gq) cmax[gq] = wave_max(cc[gq]);
   }
+  // First tau: the lower bound where f is convex, which is within a few
+  // percent of the bracket from the root, so that the steps from there
+  // converge in 3 evaluations instead of 5 or 6 (12 at alpha = 2, where the
+  // midpoint's steps come from the kinks right of the root); streamed
+  // evaluations at alpha >= 1.5 take the midpoint, since lists that do not
+  // fit mean a wide support, far from the bound of its largest scores
+  // (alpha 1.5, c = 1/4: 4.4 evaluations against 5).  The bound itself, not
+  // the bracket's end below it: where one key takes the whole row, z is
+  // clamped to 1 there and f reads 0 all the way to the root.
+#pragma unroll
+  for (int gq = 0; gq < G; ++gq)
+    if (!newton_bound || !(cached || g > 2.f)) tau[gq] = 0.5f * (lo[gq] + hi[gq]);
   int attempts = cache ? 1 : 0;  // cache fills tried (pass 0 is the first)
   // form of the lists: 0 quads, 1 compacted singles, 2 singles of a later fill
   int lists = 0;
@@ -1565,7 +1577,10 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
       bool take = th >= lo[gq] - slack && th <= hi[gq] + slack;
       if (!newton_bound && fabsf(f[gq]) > 0.5f * f_prev[gq]) take = false;
       f_prev[gq] = fabsf(f[gq]);
-      tau[gq] = take ? fminf(fmaxf(th, lo[gq]), hi[gq]) : 0.5f * (lo[gq] + hi[gq]);
+      // (a step that ends below a bracket whose lower end is Newton's bound:
+      // that end is the better guess)
+      tau[gq] = take ? fminf(fmaxf(th, lo[gq]), hi[gq])
+                     : newton_bound && th < lo[gq] ? lo[gq] : 0.5f * (lo[gq] + hi[gq]);
     }
     if (stop) break;
   }
@@ -1749,7 +1764,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   }
   if (lane == 0) a.q_count[(size_t)bh * T + qb] = listed;
   if (a.lists && lane == 0)
-    a.lists[(size_t)bh * T + qb].used = cached && lsum[qbl] <= min(max(LIST_PER_BLOCK * listed, LIST_FEW), LIST_ENTRIES);
+    a.lists[(size_t)bh * T + qb].used = cached ? list_use(lsum[qbl], listed, T, sizeof(E) == 4) : LIST_NONE;
   if (a.stats && lane == 0) {
     a.stats[(size_t)bh * T + qb] = passes;
     a.stats[((size_t)a.BH + bh) * T + qb] = evals;
@@ -1824,7 +1839,24 @@ hipError_t launch_tau_f32_64(const TauArgs& a, hipStream_t s) { return launch_so
 #elif EA_TAU_PART == 3
 hipError_t launch_tau_f32_128(const TauArgs& a, hipStream_t s) { return launch_solve_d<float, 128>(a, s); }
 #elif EA_TAU_PART == 4
+// The solver for short sequences does without the latency of lists in memory,
+// which is most of a small grid's time, but takes more operations per score:
+// it serves n <= 512 (at d = 128 beyond 256 keys, grids of up to two
+// workgroups per compute unit), and n <= 1024 where one row block per compute
+// unit leaves the chip idle.  Solver times against solve_kernel, in us:
+// B32 H16 d64 n128 44 against 78, n256 49 against 94, n512 137 against 255;
+// d128 causal n512 162 against 149; B4 H12 n512 d128 31 against 35; B1 H8
+// n1024 d64 24 against 65; B1 H16 n1000 d128 33 against 51; B4 H12 n777 d64
+// 57 against 44, B8 H12 n1024 d64 138 against 111.
+static bool small_solver(const TauArgs& a, int dtype, int head_dim) {
+  if (a.n > SMALL_MAX_N || (dtype == 1 && a.gk == 0)) return false;
+  const int64_t blocks = (int64_t)a.BH * a.T;
+  if (a.n > 512) return blocks <= 384;
+  return head_dim == 64 || a.n <= 256 || blocks <= 512;
+}
+
 hipError_t launch_tau(const TauArgs& a, int dtype, int head_dim, hipStream_t s) {
+  if (small_solver(a, dtype, head_dim)) return launch_tau_small(a, dtype, head_dim, s);
   if (dtype == 0) return head_dim == 64 ? launch_tau_bf16_64(a, s) : launch_tau_bf16_128(a, s);
   return head_dim == 64 ? launch_tau_f32_64(a, s) : launch_tau_f32_128(a, s);
 }

@@ -228,3 +228,74 @@ def test_nan_inputs_do_not_fault():
     torch.cuda.synchronize()
     assert torch.isfinite(res3.tau).all()
     assert torch.isnan(o3).any()
+
+
+@pytest.mark.parametrize("dtype,d,n,alpha", [
+    ("bf16", 64, 31, 1.5), ("bf16", 128, 256, 1.25), ("f32", 128, 511, 2.0), ("bf16", 64, 513, 1.5),
+    ("f32", 64, 1024, 1.25), ("bf16", 128, 1000, 2.0), ("bf16", 64, 700, 1.6), ("bf16", 64, 300, 3.0)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_short_sequence_solver(dtype, d, n, alpha, causal):
+    """The solver for short sequences (scores in registers, lists in LDS): its
+    three sizes at their edges and remainders.  c = 0.1 overflows its lists
+    (the evaluations then run on the scores themselves)."""
+    for c in ((4.0, 0.1) if alpha <= 2 else (1.0,)):
+        inp = synth.attention_inputs(1, 2, n, d, c=c, dtype=dtype, with_dout=True, seed=n)
+        bwd = alpha <= 2
+        gpu = run_gpu(inp, alpha, d ** -0.5, causal, bwd, max_iter=12 if bwd else 40)
+        check_tables(gpu, causal, columns=bwd)
+        for bh in range(2):
+            ref = oracle_head(inp, bh, alpha, d ** -0.5, causal, bwd)
+            errs = check_head(gpu, ref, bh, dtype, "short n%d c%g bh=%d" % (n, c, bh))
+        log("short %s d%d n%d alpha %g c %g causal %d: %s" % (dtype, d, n, alpha, c, causal, errs))
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("alpha", [1.25, 1.5, 2.0, 1.7])
+@pytest.mark.parametrize("causal", [False, True])
+def test_element_lists(dtype, d, alpha, causal):
+    """Query blocks with element lists, without them, and both in one head:
+    rows of a low query temperature (too many entries to list) in some blocks,
+    and one key that every query attends to, whose dK and dV several groups of
+    lanes share (more entries than one round of the dK/dV kernel takes).  The
+    backward equals the oracle, and the one without lists: their thresholds no
+    longer match once another forward has filled the residuals."""
+    import paper_2502_12082_amd as ea
+    n = 2500
+    # (fp32: the rounding of larger scores alone would pass the bound of 1e-4)
+    inp = synth.attention_inputs(1, 2, n, d, c=4.0 if dtype == "bf16" else 1.5, dtype=dtype,
+                                 with_dout=True, seed=11)
+    q, k = inp["q"].f32().copy(), inp["k"].f32().copy()
+    q[:, :, 640:768] *= 0.02                    # two query blocks of wide rows (most stay listed)
+    k[:, 0, 100] = 3.0 * q[:, 0].mean(axis=1)   # head 0: a key on the mean query ...
+    q[:, 0, :, :8] += 6.0
+    k[:, 0, 100, :8] = 1.0                      # ... that all queries score highly
+    bits = synth.f32_to_bf16_bits if dtype == "bf16" else (lambda x: x)
+    inp["q"], inp["k"] = synth.Tensor(bits(q), dtype), synth.Tensor(bits(k), dtype)
+    scale = d ** -0.5
+    gpu = run_gpu(inp, alpha, scale, causal, True)
+    check_tables(gpu, causal)
+    for bh in range(2):
+        ref = oracle_head(inp, bh, alpha, scale, causal, True)
+        # fp32: sums over all n queries of that key reach |dK| ~ 100
+        errs = check_head(gpu, ref, bh, dtype, "lists bh=%d" % bh) if dtype == "bf16" or bh == 1 else None
+    log("lists %s d%d alpha %g causal %d: %s" % (dtype, d, alpha, causal, errs))
+    t = {x: to_device(inp[x]) for x in ("q", "k", "v", "dout")}
+    o, res = ea.forward(t["q"], t["k"], t["v"], alpha=alpha, causal=causal)
+    with_lists = ea.backward(t["q"], t["k"], t["v"], t["dout"], res)
+    lists, res.lists = res.lists, None
+    without = ea.backward(t["q"], t["k"], t["v"], t["dout"], res)
+    res.lists = lists
+    ea.forward(t["q"], t["k"], t["v"], alpha=alpha, causal=causal, scale=2.0 * scale, res=res)
+    stale, res.lists = res.lists.clone(), None  # lists of other thresholds
+    ea.forward(t["q"], t["k"], t["v"], alpha=alpha, causal=causal, res=res)
+    plain = ea.backward(t["q"], t["k"], t["v"], t["dout"], res)
+    res.lists = stale
+    with_stale = ea.backward(t["q"], t["k"], t["v"], t["dout"], res)
+    torch.cuda.synchronize()
+    for a, b in zip(plain, with_stale):
+        assert torch.equal(a, b), "lists of other thresholds were used"
+    for a, b in zip(with_lists, without):
+        # dV: one side rounds P to bf16, 2^-9 relative per term; the others, and
+        # fp32, differ by the rounding of their sums of up to n terms
+        rel = 4e-3 if dtype == "bf16" else 2e-5
+        assert (a - b).norm().item() <= rel * b.norm().item()
