@@ -1665,16 +1665,43 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
       if (!(raw > -band[gq])) return -1.0;
       return exact_x<D>(Qf + (size_t)qi[gq] * D, Kf + (size_t)jv * D, a.c64) - t64[gq];
     };
+    // With compacted lists (and whole keys in them) the fp64 scores are taken
+    // once and kept where the quads were: at B2 H4 n1025 d64 causal, alpha
+    // 1.7, recomputing them in each of the steps below and for the mask was
+    // most of the kernel's 366 us.
+    const bool kept = cached && lists == 1 && kshift == 0;
+    auto x64_at = [&](int e, int gq) { return reinterpret_cast<double*>(slot + entry_idx(e, gq) * 8u); };
+    auto kept_z = [&](auto&& use) {
+#pragma unroll
+      for (int gq = 0; gq < G; ++gq)
+        for (int e = 0; e < ns[gq]; ++e) use(gq, *x64_at(e, gq) - t64[gq]);
+    };
+    if (kept) {
+#pragma unroll
+      for (int gq = 0; gq < G; ++gq)
+        for (int e = 0; e < ns[gq]; ++e) {
+          const float raw = fmaf(c, ld_single(e, gq, true), -tau[gq]);
+          *x64_at(e, gq) = raw > -band[gq] ? exact_x<D>(Qf + (size_t)qi[gq] * D,
+                                                        Kf + (size_t)ld_block(e, gq, true) * D, a.c64)
+                                           : -1e300;  // below the band: outside the support
+        }
+    }
     for (int it = 0; it < 3; ++it) {
       double s0[G] = {}, s1[G] = {};
-      visit([&](int gq, float sv, int jv) {
-        if (!row_ok[gq]) return;
-        const double z = z64(gq, sv, jv);
+      auto add = [&](int gq, double z) {
         if (z > 0.0) {
-          s0[gq] += pow(z, a.g64);
-          s1[gq] += pow(z, a.g64 - 1.0);
+          const double u = pow(z, a.g64 - 1.0);
+          s0[gq] = fma(u, z, s0[gq]);
+          s1[gq] += u;
         }
-      });
+      };
+      if (kept) {
+        kept_z(add);
+      } else {
+        visit([&](int gq, float sv, int jv) {
+          if (row_ok[gq]) add(gq, z64(gq, sv, jv));
+        });
+      }
 #pragma unroll
       for (int gq = 0; gq < G; ++gq) {
         s0[gq] += __shfl_xor(s0[gq], 32);
@@ -1697,7 +1724,12 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     }
     for (int x = lane; x < TW; x += 64) bits[qbl * BW + x] = 0;
     __syncthreads();
-    visit([&](int gq, float sv, int jv) {
+    if (kept) {
+#pragma unroll
+      for (int gq = 0; gq < G; ++gq)
+        for (int e = 0; e < ns[gq]; ++e)
+          emit(gq, (float)fmin(fmax(*x64_at(e, gq) - t64[gq], 0.0), 1.0), ld_block(e, gq, true));
+    } else visit([&](int gq, float sv, int jv) {
       if (!row_ok[gq]) return;
       const float raw = fmaf(c, sv, -tau[gq]);
       if (raw >= band[gq])
