@@ -54,7 +54,7 @@ typedef struct {
   float scale;      /* > 0, finite; usually 1/sqrt(head_dim) */
   int32_t causal;   /* 0 or 1 */
   int32_t max_iter; /* Halley-bisection updates after the initial midpoint (Algorithm 1's T), 0..64 */
-  float tol;        /* >= 0: the solver stops on a tile of query rows (256; 128 without a mask)
+  float tol;        /* >= 0: the solver stops on a tile of query rows  (256, 128 or 64)
                        once every row has |f(tau)| <= tol */
   int32_t need_bwd; /* 1: also write o2 for a later entmax_attn_bwd */
 } ea_params;
@@ -230,9 +230,9 @@ ea_status entmax_attn_bwd_noalloc(const ea_shape* shape, const ea_params* params
 
 /*
  * No-mask ("memory-efficient") mode, Algorithm 2 as written (Sec. 3.2.1): the
- * forward solves tau and accumulates O (and, if need_bwd, o2) in one kernel
- * per 128-row query tile, visiting every valid key block; no block mask or
- * tables exist, so memory beyond the inputs and outputs is O(n) per head.
+ * forward solves tau and accumulates O (and, if need_bwd, o2), visiting every
+ * valid key block; no block mask or tables exist, so memory beyond the inputs
+ * and outputs is O(n) per head.
  *   tau  fp32 [BH, n] (written); o2 fp32 [BH, n, d] (written if need_bwd)
  *   tau_lo  fp32 [BH, n], fp32 inputs only (required then, written by the
  *        forward and read by the backward; ignored, may be NULL, for bf16):
@@ -240,8 +240,8 @@ ea_status entmax_attn_bwd_noalloc(const ea_shape* shape, const ea_params* params
  *   workspace  optional candidate cache, as for entmax_attn_fwd
  * The backward visits every valid block (no tables) and otherwise follows
  * entmax_attn_bwd: workspace >= sizes.ws_bwd bytes.  Results equal those of
- * entmax_attn_fwd / entmax_attn_bwd up to rounding.  One kernel launch
- * (forward) or three (backward) on `stream`.
+ * entmax_attn_fwd / entmax_attn_bwd up to rounding.  Launches are those of
+ * entmax_attn_fwd and entmax_attn_bwd.
  */
 ea_status entmax_attn_fwd_dense(const ea_shape* shape, const ea_params* params, const void* q,
                                 const void* k, const void* v, void* o, float* tau, float* tau_lo,
@@ -250,6 +250,21 @@ ea_status entmax_attn_bwd_dense(const ea_shape* shape, const ea_params* params, 
                                 const void* k, const void* v, const void* dout, const float* tau,
                                 const float* tau_lo, const float* o2, float* dq, float* dk,
                                 float* dv, void* workspace, size_t ws_bytes, void* stream);
+
+/*
+ * The no-mask mode with element lists (see entmax_attn_fwd_lists; lists may be
+ * NULL).  Here `lists` is scratch of each call, not a residual: the backward
+ * collects the lists again from the thresholds, in one more K pass and launch.
+ */
+ea_status entmax_attn_fwd_dense_lists(const ea_shape* shape, const ea_params* params, const void* q,
+                                      const void* k, const void* v, void* o, float* tau,
+                                      float* tau_lo, float* o2, void* lists, size_t lists_bytes,
+                                      void* workspace, size_t ws_bytes, void* stream);
+ea_status entmax_attn_bwd_dense_lists(const ea_shape* shape, const ea_params* params, const void* q,
+                                      const void* k, const void* v, const void* dout,
+                                      const float* tau, const float* tau_lo, const float* o2,
+                                      void* lists, size_t lists_bytes, float* dq, float* dk,
+                                      float* dv, void* workspace, size_t ws_bytes, void* stream);
 
 /*
  * Row-wise alpha-entmax of a materialized score matrix s, [rows, n] row-major

@@ -36,7 +36,7 @@ SYMBOLS = ("entmax_attn_default_params", "entmax_attn_sizes", "entmax_attn_fwd",
            "entmax_attn_status_string", "entmax_attn_last_hip_error", "entmax_rows_fwd",
            "entmax_rows_bwd", "entmax_attn_fwd_dense", "entmax_attn_bwd_dense",
            "entmax_attn_bwd_noalloc", "entmax_attn_lists_bytes", "entmax_attn_fwd_lists",
-           "entmax_attn_bwd_lists")
+           "entmax_attn_bwd_lists", "entmax_attn_fwd_dense_lists", "entmax_attn_bwd_dense_lists")
 EA_ALL_STAGES = -1
 NOALLOC_MAX_ROWS = 1048576  # EA_NOALLOC_MAX_ROWS of include/entmax_attn.h
 
@@ -104,6 +104,12 @@ _lib.entmax_rows_bwd.restype = ctypes.c_int
 _lib.entmax_attn_bwd_noalloc.argtypes = [_P(Shape), _P(Params), _v, _v, _v, _v, _P(ResidualPtrs),
                                          _v, _v, _v, _v]
 _lib.entmax_attn_bwd_noalloc.restype = ctypes.c_int
+_lib.entmax_attn_fwd_dense_lists.argtypes = [_P(Shape), _P(Params), _v, _v, _v, _v, _v, _v, _v, _v,
+                                             ctypes.c_size_t, _v, ctypes.c_size_t, _v]
+_lib.entmax_attn_fwd_dense_lists.restype = ctypes.c_int
+_lib.entmax_attn_bwd_dense_lists.argtypes = [_P(Shape), _P(Params), _v, _v, _v, _v, _v, _v, _v, _v,
+                                             ctypes.c_size_t, _v, _v, _v, _v, ctypes.c_size_t, _v]
+_lib.entmax_attn_bwd_dense_lists.restype = ctypes.c_int
 _lib.entmax_attn_lists_bytes.argtypes = [_P(Shape), _P(Params), _P(ctypes.c_size_t)]
 _lib.entmax_attn_lists_bytes.restype = ctypes.c_int
 _lib.entmax_attn_fwd_lists.argtypes = [ctypes.c_int, _P(Shape), _P(Params), _v, _v, _v, _v,
@@ -506,6 +512,15 @@ def rows_backward(s, tau, dp, alpha=1.5, scale=1.0):
 
 # ---------------------------------------------------------- no-mask mode
 
+def _scratch_lists(shape, params, device):
+    """Element lists for one call of the no-mask mode: (tensor or None, pointer, bytes)."""
+    nbytes = entmax_attn_lists_bytes(shape, params)
+    if not 0 < nbytes <= _lists_limit(device):
+        return None, None, 0
+    t = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    return t, t.data_ptr(), nbytes
+
+
 def forward_dense(q, k, v, alpha=1.5, scale=None, causal=False, need_bwd=True, max_iter=None,
                   tol=None, workspace=None):
     """(O, tau, O2 or None, tau_lo or None) without block mask or tables
@@ -528,11 +543,12 @@ def forward_dense(q, k, v, alpha=1.5, scale=None, causal=False, need_bwd=True, m
     _on_gpu(dev)
     ws_ptr, ws_bytes = (None, 0) if workspace is False else (workspace.data_ptr(),
                                                             workspace.numel() * workspace.element_size())
-    _check(_lib.entmax_attn_fwd_dense(ctypes.byref(shape), ctypes.byref(params), q.data_ptr(),
-                                      k.data_ptr(), v.data_ptr(), o.data_ptr(), tau.data_ptr(),
-                                      tau_lo.data_ptr() if tau_lo is not None else None,
-                                      o2.data_ptr() if o2 is not None else None, ws_ptr, ws_bytes,
-                                      _stream_handle(q.device)), "entmax_attn_fwd_dense")
+    _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device)
+    _check(_lib.entmax_attn_fwd_dense_lists(
+        ctypes.byref(shape), ctypes.byref(params), q.data_ptr(), k.data_ptr(), v.data_ptr(),
+        o.data_ptr(), tau.data_ptr(), tau_lo.data_ptr() if tau_lo is not None else None,
+        o2.data_ptr() if o2 is not None else None, lists_ptr, lists_bytes, ws_ptr, ws_bytes,
+        _stream_handle(q.device)), "entmax_attn_fwd_dense")
     return o, tau, o2, tau_lo
 
 
@@ -554,10 +570,10 @@ def backward_dense(q, k, v, dout, tau, o2, alpha=1.5, scale=None, causal=False, 
     mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
     dq, dk, dv = mk(), mk(), mk()
     ws = torch.empty(max(z.ws_bwd, 16) // 4 + 4, dtype=torch.float32, device=q.device)
-    _check(_lib.entmax_attn_bwd_dense(ctypes.byref(shape), ctypes.byref(params), q.data_ptr(),
-                                      k.data_ptr(), v.data_ptr(), dout.data_ptr(), tau.data_ptr(),
-                                      tau_lo.data_ptr() if q.dtype == torch.float32 else None,
-                                      o2.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
-                                      ws.data_ptr(), ws.numel() * 4, _stream_handle(q.device)),
-           "entmax_attn_bwd_dense")
+    _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device)
+    _check(_lib.entmax_attn_bwd_dense_lists(
+        ctypes.byref(shape), ctypes.byref(params), q.data_ptr(), k.data_ptr(), v.data_ptr(),
+        dout.data_ptr(), tau.data_ptr(), tau_lo.data_ptr() if q.dtype == torch.float32 else None,
+        o2.data_ptr(), lists_ptr, lists_bytes, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
+        ws.data_ptr(), ws.numel() * 4, _stream_handle(q.device)), "entmax_attn_bwd_dense")
     return dq, dk, dv

@@ -33,14 +33,11 @@ constexpr float DEFAULT_TOL = 1e-5f;
 constexpr int MAX_ITER_CAP = 64;
 // Candidate-cache entries per list (see entmax_attn_sizes); a slot holds
 // two lists per row of a workgroup.
-constexpr int TAU_CACHE_CAP = 192;
-static_assert(TAU_CACHE_CAP % 16 == 0, "the solver reads lists in batches of 16 entries");
 constexpr int SOLVE_QUAD_CAP = 96;
 static_assert(SOLVE_QUAD_CAP % 8 == 0, "the solver reads lists in batches of 8 quads");
 constexpr size_t SOLVE_SLOT_BYTES = solve_slot_bytes(SOLVE_QUAD_CAP);
 static_assert(SOLVE_SLOT_BYTES % (2 * SOLVE_THREADS * sizeof(CandEntry) * 8) == 0,
               "a refilled slot holds a multiple of 8 single entries per list");
-constexpr size_t TAU_SLOT_BYTES = (size_t)TAU_CACHE_CAP * 2 * TAU_ROWS * sizeof(CandEntry);
 
 bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
@@ -94,12 +91,9 @@ size_t bwd_ws_bytes(const Dims& d) { return (size_t)(d.BH * d.n) * 4; }
 // path's sizing covers both.
 constexpr int64_t MAX_SOLVE_SLOTS = 512;
 int64_t solve_tiles(const Dims& d) { return d.BH * ((d.n + SOLVE_ROWS - 1) / SOLVE_ROWS); }
-int64_t cache_tiles(const Dims& d) { return d.BH * ((d.n + TAU_ROWS - 1) / TAU_ROWS); }
 int64_t solve_slots(const Dims& d) {
   return solve_tiles(d) < MAX_SOLVE_SLOTS ? solve_tiles(d) : MAX_SOLVE_SLOTS;
 }
-static_assert(SOLVE_ROWS == 2 * TAU_ROWS && SOLVE_SLOT_BYTES >= 2 * TAU_SLOT_BYTES,
-              "a masked-path slot covers two fused-forward slots");
 
 void fill_sizes(const Dims& d, ea_sizes* z) {
   z->tau = (size_t)(d.BH * d.n) * 4;
@@ -274,7 +268,7 @@ ea_status run_fwd_stage(int stage, const Dims& d, const ea_params* params, const
     const int64_t most = solve_tiles(d);
     if (slots > most) slots = most;
     void* cand = slots > 0 ? workspace : nullptr;
-    TauArgs ta{q, k, res->tau, res->block_mask, res->stats, nullptr, nullptr, nullptr, cand,
+    TauArgs ta{q, k, res->tau, res->block_mask, res->stats, cand,
                SOLVE_QUAD_CAP, (int)slots, /*tile0=*/0,
                (int)d.BH, (int)d.n, (int)d.T, c, params->alpha, gamma, params->causal,
                params->max_iter, params->tol, gk,
@@ -502,9 +496,11 @@ ea_status entmax_rows_bwd(int64_t rows, int32_t n, ea_dtype dtype, const ea_para
   return from_hip(launch_rows_bwd(ra, dtype, static_cast<hipStream_t>(stream)));
 }
 
-ea_status entmax_attn_fwd_dense(const ea_shape* shape, const ea_params* params, const void* q,
-                                const void* k, const void* v, void* o, float* tau, float* tau_lo,
-                                float* o2, void* workspace, size_t ws_bytes, void* stream) {
+// The no-mask mode: the same stages without a mask or tables.
+ea_status entmax_attn_fwd_dense_lists(const ea_shape* shape, const ea_params* params, const void* q,
+                                      const void* k, const void* v, void* o, float* tau, float* tau_lo,
+                                      float* o2, void* lists, size_t lists_bytes, void* workspace,
+                                      size_t ws_bytes, void* stream) {
   Dims d;
   ea_status st = check_shape(shape, params, &d);
   if (st != EA_OK) return st;
@@ -513,23 +509,30 @@ ea_status entmax_attn_fwd_dense(const ea_shape* shape, const ea_params* params, 
   if (d.dtype == EA_F32 && !small_ok(tau_lo)) return EA_ERR_INVALID_ARG;
   if (params->need_bwd && !tensor_ok(o2)) return EA_ERR_INVALID_ARG;
   if (workspace && !aligned(workspace, 16)) return EA_ERR_INVALID_ARG;
-  int64_t slots = workspace ? (int64_t)(ws_bytes / TAU_SLOT_BYTES) : 0;
-  if (slots > cache_tiles(d)) slots = cache_tiles(d);
-  void* cand = slots > 0 ? workspace : nullptr;
-  const float c = (params->alpha - 1.0f) * params->scale;
-  const float gamma = 1.0f / (params->alpha - 1.0f);
-  TauArgs ta{q, k, tau, nullptr, nullptr, v, o, params->need_bwd ? o2 : nullptr, cand,
-             TAU_CACHE_CAP, (int)slots, /*tile0=*/0, (int)d.BH, (int)d.n, (int)d.T, c,
-             params->alpha, gamma,
-             params->causal, params->max_iter, params->tol, gamma_kind(params->alpha),
-             d.dtype == EA_F32 ? tau_lo : nullptr, c64_of(params), g64_of(params)};
-  return from_hip(launch_tau_fused(ta, d.dtype, (int)d.d, static_cast<hipStream_t>(stream)));
+  if ((st = check_lists(d, lists, lists_bytes)) != EA_OK) return st;
+  ea_residuals res{};
+  res.tau = tau;
+  res.tau_lo = tau_lo;
+  res.o2 = o2;
+  for (int stage = 0; stage < 2; ++stage)
+    if ((st = run_fwd_stage(stage, d, params, q, k, v, o, &res, workspace, ws_bytes,
+                            static_cast<ListBlock*>(lists), static_cast<hipStream_t>(stream))) != EA_OK)
+      return st;
+  return EA_OK;
 }
 
-ea_status entmax_attn_bwd_dense(const ea_shape* shape, const ea_params* params, const void* q,
-                                const void* k, const void* v, const void* dout, const float* tau,
-                                const float* tau_lo, const float* o2, float* dq, float* dk,
-                                float* dv, void* workspace, size_t ws_bytes, void* stream) {
+ea_status entmax_attn_fwd_dense(const ea_shape* shape, const ea_params* params, const void* q,
+                                const void* k, const void* v, void* o, float* tau, float* tau_lo,
+                                float* o2, void* workspace, size_t ws_bytes, void* stream) {
+  return entmax_attn_fwd_dense_lists(shape, params, q, k, v, o, tau, tau_lo, o2, nullptr, 0, workspace,
+                                     ws_bytes, stream);
+}
+
+ea_status entmax_attn_bwd_dense_lists(const ea_shape* shape, const ea_params* params, const void* q,
+                                      const void* k, const void* v, const void* dout, const float* tau,
+                                      const float* tau_lo, const float* o2, void* lists, size_t lists_bytes,
+                                      float* dq, float* dk, float* dv, void* workspace, size_t ws_bytes,
+                                      void* stream) {
   Dims d;
   ea_status st = check_shape(shape, params, &d);
   if (st != EA_OK) return st;
@@ -539,16 +542,31 @@ ea_status entmax_attn_bwd_dense(const ea_shape* shape, const ea_params* params, 
   if (d.dtype == EA_F32 && !small_ok(tau_lo)) return EA_ERR_INVALID_ARG;
   if (!workspace || !aligned(workspace, 16)) return EA_ERR_INVALID_ARG;
   if (ws_bytes < bwd_ws_bytes(d)) return EA_ERR_WORKSPACE;
-  // no tables: the kernels visit every valid block
+  if ((st = check_lists(d, lists, lists_bytes)) != EA_OK) return st;
+  // no tables: the kernels visit every valid block that has no lists
   ea_residuals res{};
   res.tau = const_cast<float*>(tau);
   res.tau_lo = const_cast<float*>(tau_lo);
   res.o2 = const_cast<float*>(o2);
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (lists) {
+    CollectArgs ca{q, k, tau, tau_lo_of(&res, d), static_cast<ListBlock*>(lists), (int)d.BH, (int)d.n,
+                   (int)d.T, (params->alpha - 1.0f) * params->scale, params->causal,
+                   gamma_kind(params->alpha), c64_of(params)};
+    if ((st = from_hip(launch_collect(ca, d.dtype, (int)d.d, s))) != EA_OK) return st;
+  }
   for (int stage = 0; stage < 3; ++stage)
-    if ((st = run_bwd_stage(stage, d, params, q, k, v, dout, &res, dq, dk, dv, workspace, nullptr, s)) != EA_OK)
+    if ((st = run_bwd_stage(stage, d, params, q, k, v, dout, &res, dq, dk, dv, workspace, lists, s)) != EA_OK)
       return st;
   return EA_OK;
+}
+
+ea_status entmax_attn_bwd_dense(const ea_shape* shape, const ea_params* params, const void* q,
+                                const void* k, const void* v, const void* dout, const float* tau,
+                                const float* tau_lo, const float* o2, float* dq, float* dk,
+                                float* dv, void* workspace, size_t ws_bytes, void* stream) {
+  return entmax_attn_bwd_dense_lists(shape, params, q, k, v, dout, tau, tau_lo, o2, nullptr, 0, dq, dk, dv,
+                                     workspace, ws_bytes, stream);
 }
 
 const char* entmax_attn_status_string(ea_status s) {

@@ -227,6 +227,125 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
   }
 }
 
+// ------------------------------- element lists from the thresholds alone
+
+// The element lists of the no-mask mode's backward, which is given thresholds
+// but no lists: one K pass at tau (one of the three products a block of dQ
+// and dK/dV each costs otherwise), every z > 0 appended to its row's lists.
+// Workgroup = 128 rows, wave = 32 rows against both halves of every key block,
+// as the solver's one-group form.  A wave whose lists overflow stops scoring,
+// and the workgroup stops when all have.
+constexpr int COL_NT = 256;
+
+template <typename E, int D, int GK>
+__global__ __launch_bounds__(COL_NT, sizeof(E) == 4 && D == 128 ? 1 : 3) void collect_kernel(CollectArgs a) {
+  using TL = PadTile<E, D>;
+  using M = Mma<E>;
+  constexpr int KS = D / M::KW;
+  constexpr bool PRECISE = precise_path<E, GK>();
+  __shared__ __attribute__((aligned(16))) E kbuf[2][TL::ELEMS];
+  __shared__ uint32_t bits[2][PREP_T / 32];  // key blocks in use, per query block
+  __shared__ int entries[2];
+  const int t = threadIdx.x, lane = lane_id(), w = wave_id(), half = lane >> 5;
+  const int n = a.n, T = a.T;
+  int bh, qt;
+  head_major(blockIdx.x, a.BH, (T + 1) / 2, bh, qt);
+  if (a.causal) qt = (T + 1) / 2 - 1 - qt;
+  const int q0 = qt * 128 + 32 * w, i = q0 + (lane & 31), qbl = w >> 1, qb = 2 * qt + qbl;
+  const bool row_ok = i < n;
+  const E* Q = static_cast<const E*>(a.q) + (size_t)bh * n * D;
+  const E* K = static_cast<const E*>(a.k) + (size_t)bh * n * D;
+  const int last = min(n, q0 + 32) - 1;  // last row of the wave
+  const int nkb = a.causal ? (min(n, qt * 128 + 128) - 1) / BLK + 1 : T;
+  const float c = a.c, tau = row_ok ? a.tau[(size_t)bh * n + i] : INFINITY;
+  [[maybe_unused]] const double tau64 =
+      (double)tau + (PRECISE && a.tau_lo && row_ok ? (double)a.tau_lo[(size_t)bh * n + i] : 0.0);
+  [[maybe_unused]] const float band = PRECISE_BAND * fmaxf(1.f, fabsf(tau));
+  for (int x = t; x < 2 * (PREP_T / 32); x += COL_NT) (&bits[0][0])[x] = 0;
+  if (t < 2) entries[t] = 0;
+
+  typename M::frag qf[KS];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) qf[kk] = load_row_frag_global<E, D>(Q, i, n, kk);
+  ListBlock* const lb = qb < T ? a.lists + ((size_t)bh * T + qb) : nullptr;
+  const int row = i - qb * BLK, id = 64 * half + row;
+  int cnt = 0;
+  bool dead = q0 >= n;
+
+  TileDma<TL, D, COL_NT> dma;
+  dma.init();
+  dma.issue(kbuf[0], K, 0, n);
+  for (int kb = 0; kb < nkb; ++kb) {
+    dma_wait();
+    if ((kb & 7) == 7) {
+      if (__syncthreads_and(dead)) break;
+    } else {
+      __syncthreads();
+    }
+    if (kb + 1 < nkb) dma.issue(kbuf[(kb + 1) & 1], K, (kb + 1) * BLK, n);
+    if (dead) continue;
+    bool any = false;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int j0 = kb * BLK + 32 * h;
+      if (j0 >= n || (a.causal && j0 > last)) continue;
+      f32x16 s = zero16();
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk)
+        s = M::mma(lds_row_frag_pad<E, D>(kbuf[kb & 1], 32 * h + (lane & 31), kk), qf[kk], s);
+      if (j0 + 31 >= n || (a.causal && j0 + 31 > q0)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int j = j0 + crow(r);
+          if (!(j < n && (!a.causal || j <= i))) s[r] = -INFINITY;
+        }
+      }
+      float z[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if constexpr (PRECISE)
+          z[r] = precise_relu_z<D>(row_ok, c, s[r], tau, band, tau64,
+                                   reinterpret_cast<const float*>(Q) + (size_t)i * D,
+                                   reinterpret_cast<const float*>(K) + (size_t)(j0 + crow(r)) * D, a.c64);
+        else
+          z[r] = relu_z(c, s[r], tau);
+      }
+#pragma unroll
+      for (int r0 = 0; r0 < 16; r0 += 4) {
+        if (fmaxf(max3f(z[r0], z[r0 + 1], z[r0 + 2]), z[r0 + 3]) > 0.f) {
+#pragma unroll
+          for (int r = r0; r < r0 + 4; ++r)
+            if (z[r] > 0.f) {
+              any = true;
+              if (cnt < LIST_CAP) {
+                lb->z[LIST_IDS * cnt + id] = z[r];
+                lb->key[LIST_IDS * cnt + id] = (uint16_t)(j0 + crow(r));
+              }
+              ++cnt;
+            }
+        }
+      }
+    }
+    if (__ballot(any) != 0ull && lane == 0) atomicOr(&bits[qbl][kb >> 5], 1u << (kb & 31));
+    dead = __ballot(cnt > LIST_CAP) != 0ull;
+  }
+  dma_wait();  // a copy may be in flight when the loop was left
+  int total = cnt > LIST_CAP ? LIST_ENTRIES + 1 : cnt;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
+  if (lane == 0) atomicAdd(&entries[qbl], total);
+  if (lb) {
+    lb->count[id] = (uint8_t)min(cnt, LIST_CAP);
+    if (half == 0 && row_ok) lb->tau[row] = tau;
+  }
+  __syncthreads();
+  if (lb && (w & 1) == 0 && lane == 0) {
+    int blocks = 0;
+    for (int x = 0; x < (T + 31) / 32; ++x) blocks += __popc(bits[qbl][x]);
+    lb->used = list_use(entries[qbl], blocks, T, sizeof(E) == 4);
+  }
+}
+
 // ------------------------------------------------------------------ dK dV
 
 // The number of a head's T query blocks that are sorted for the list kernel.
@@ -241,15 +360,16 @@ __device__ __forceinline__ int sorted_blocks(const int32_t* used, int T) {
   return __builtin_amdgcn_readfirstlane(sorted);
 }
 
-// The query blocks of list[0 .. cnt) that have no element lists, in order, in
-// out (in LDS); returns their number.  Every thread of the workgroup.
+// The query blocks of list[0 .. cnt) (without tables: first, first + 1, ...)
+// that have no element lists, in order, in out (in LDS); returns their number.
+// Every thread of the workgroup.
 template <int NT>
-__device__ int unlisted_blocks(const int32_t* list, int cnt, const int32_t* used, uint16_t* out) {
+__device__ int unlisted_blocks(const int32_t* list, int first, int cnt, const int32_t* used, uint16_t* out) {
   __shared__ int wcount[NT / 64];
   int total = 0;
   for (int e0 = 0; e0 < cnt; e0 += NT) {
     const int e = e0 + (int)threadIdx.x;
-    const int qb = e < cnt ? list[e] : 0;
+    const int qb = e < cnt ? (list ? list[e] : first + e) : 0;
     const bool b = e < cnt && !(used[qb] & SORTED);
     const unsigned long long m = __ballot(b);
     __syncthreads();  // wcount of the round before has been read
@@ -308,7 +428,7 @@ __global__ __launch_bounds__(BWD_NT) void dkdv_kernel(BwdArgs a) {
   if (a.lists && sorted == T) return;
   const bool some = sorted > 0;
   if (some) {
-    cnt = unlisted_blocks<BWD_NT>(list, cnt, a.buckets.used + (size_t)bh * T, unlisted);
+    cnt = unlisted_blocks<BWD_NT>(list, a.causal ? kb : 0, cnt, a.buckets.used + (size_t)bh * T, unlisted);
     if (cnt == 0) return;
   }
   auto qb_of = [&](int e) { return dense ? (a.causal ? kb + e : e) : some ? (int)unlisted[e] : list[e]; };
@@ -525,8 +645,10 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
   // With element lists, only the query blocks without them (see dkdv_kernel).
   if (some) {
     const int32_t* used = a.buckets.used + (size_t)bh * T;
-    nA = unlisted_blocks<BWD2_NT>(a.k_index + ((size_t)bh * T + kbA) * T, nA, used, unlisted[0]);
-    nB = unlisted_blocks<BWD2_NT>(a.k_index + ((size_t)bh * T + min(kbB, T - 1)) * T, nB, used, unlisted[1]);
+    const int32_t* lA = dense ? nullptr : a.k_index + ((size_t)bh * T + kbA) * T;
+    const int32_t* lB = dense ? nullptr : a.k_index + ((size_t)bh * T + min(kbB, T - 1)) * T;
+    nA = unlisted_blocks<BWD2_NT>(lA, a.causal ? kbA : 0, nA, used, unlisted[0]);
+    nB = unlisted_blocks<BWD2_NT>(lB, a.causal ? kbB : 0, nB, used, unlisted[1]);
     if (nA == 0 && nB == 0) return;
     // (scalar registers: they steer the loop below)
     nA = __builtin_amdgcn_readfirstlane(nA);
@@ -774,8 +896,10 @@ __global__ __launch_bounds__(LK_NT, 2) void dkdv_lists_kernel(BwdArgs a) {
   const E* dO = static_cast<const E*>(a.dout) + head;
   const float* del = a.delta + (size_t)bh * n;
   const int k0 = kb * BLK;
-  const int32_t* list = a.k_index + ((size_t)bh * T + kb) * T;
-  const int cnt = a.k_count[(size_t)bh * T + kb];
+  const bool dense = a.k_index == nullptr;  // no tables: every valid query block
+  const int32_t* list = dense ? nullptr : a.k_index + ((size_t)bh * T + kb) * T;
+  const int cnt = dense ? (a.causal ? T - kb : T) : a.k_count[(size_t)bh * T + kb];
+  auto qb_of = [&](int e) { return dense ? (a.causal ? kb + e : e) : list[e]; };
   const int32_t* used = a.buckets.used + (size_t)bh * T;
 
   const int sorted = sorted_blocks<LK_NT>(used, T);
@@ -786,7 +910,7 @@ __global__ __launch_bounds__(LK_NT, 2) void dkdv_lists_kernel(BwdArgs a) {
   bool add = false;
   if (sorted < T) {
     bool other = false;
-    for (int e = t; e < cnt; e += LK_NT) other |= !(used[list[e]] & SORTED);
+    for (int e = t; e < cnt; e += LK_NT) other |= !(used[qb_of(e)] & SORTED);
     add = __syncthreads_or(other);
   }
 #pragma unroll
@@ -816,7 +940,7 @@ __global__ __launch_bounds__(LK_NT, 2) void dkdv_lists_kernel(BwdArgs a) {
     const int e = e0 + t;
     int qb = 0, from = 0, num = 0;
     if (e < cnt) {
-      qb = list[e];
+      qb = qb_of(e);
       if (used[qb] & SORTED) {
         const uint16_t* off = a.buckets.off + ((size_t)bh * T + qb) * (size_t)(T + 1) + kb;
         from = off[0];
@@ -1287,6 +1411,14 @@ hipError_t launch_dq_d(const BwdArgs& a, hipStream_t s) {
 }
 
 template <typename E, int D>
+hipError_t launch_collect_d(const CollectArgs& a, hipStream_t s) {
+  dim3 grid((unsigned)(a.BH * ((a.T + 1) / 2))), block(COL_NT);
+  auto kernel = collect_kernel<E, D, 1>;  // the kinds but fp32's general alpha differ in nothing here
+  if (sizeof(E) == 4 && a.gk == 0) kernel = collect_kernel<E, D, 0>;
+  return launch_kernel(kernel, grid, block, s, a);
+}
+
+template <typename E, int D>
 hipError_t launch_dkdv_lists_d(const BwdArgs& a, hipStream_t s) {
   dim3 grid((unsigned)(a.BH * a.T)), block(LK_NT);
   auto kernel = dkdv_lists_kernel<E, D, 0>;
@@ -1313,6 +1445,11 @@ hipError_t launch_delta(const DeltaArgs& a, int dtype, int head_dim, hipStream_t
 hipError_t launch_bwd_dkdv(const BwdArgs& a, int dtype, int head_dim, hipStream_t s) {
   if (dtype == 0) return head_dim == 64 ? launch_dkdv_d<__bf16, 64>(a, s) : launch_dkdv_d<__bf16, 128>(a, s);
   return head_dim == 64 ? launch_dkdv_d<float, 64>(a, s) : launch_dkdv_d<float, 128>(a, s);
+}
+
+hipError_t launch_collect(const CollectArgs& a, int dtype, int head_dim, hipStream_t s) {
+  if (dtype == 0) return head_dim == 64 ? launch_collect_d<__bf16, 64>(a, s) : launch_collect_d<__bf16, 128>(a, s);
+  return head_dim == 64 ? launch_collect_d<float, 64>(a, s) : launch_collect_d<float, 128>(a, s);
 }
 
 hipError_t launch_bwd_dkdv_lists(const BwdArgs& a, int dtype, int head_dim, hipStream_t s) {

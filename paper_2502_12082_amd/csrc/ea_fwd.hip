@@ -209,8 +209,11 @@ __global__ __launch_bounds__(FWD_NT, !TRAIN && D == 64 && sizeof(E) == 2 ? 4 : 2
   constexpr bool PRIO_PV = GK == 2;
   constexpr bool PRIO_S = PRIO_PV && D == 64;
 
-  const int32_t* list = a.q_index + ((size_t)bh * T + qb) * T;
-  const int cnt = a.q_count[(size_t)bh * T + qb];
+  // Without tables (the no-mask mode) every valid key block is visited.
+  const bool dense = a.q_index == nullptr;
+  const int32_t* list = dense ? nullptr : a.q_index + ((size_t)bh * T + qb) * T;
+  const int cnt = dense ? (a.causal ? qb + 1 : T) : a.q_count[(size_t)bh * T + qb];
+  auto kb_of = [&](int e) { return dense ? e : list[e]; };
 
   f32x16 o[NTD], o2[NTD];
 #pragma unroll
@@ -230,7 +233,7 @@ __global__ __launch_bounds__(FWD_NT, !TRAIN && D == 64 && sizeof(E) == 2 ? 4 : 2
   DmaPlan<E, D, FWD_NT> dma;
   dma.init();
   auto issue = [&](int e) {
-    const int kb = list[e];
+    const int kb = kb_of(e);
     dma.issue(kbuf[e & 1], K, kb * BLK, n);
     dma.issue(vbuf[e & 1], V, kb * BLK, n);
   };
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(FWD_NT, !TRAIN && D == 64 && sizeof(E) == 2 ? 4 : 2
     if (e + 1 < cnt) issue(e + 1);
     const E* kt = kbuf[e & 1];
     const E* vt = vbuf[e & 1];
-    const int j0 = list[e] * BLK + 32 * kh;
+    const int j0 = kb_of(e) * BLK + 32 * kh;
     const int kind = sub_kind(j0);
     if (kind == 0) continue;
     // S^T = K Q^T for this wave's 32 keys x 32 queries
@@ -391,11 +394,11 @@ __global__ __launch_bounds__(FWD_NT, !TRAIN && D == 64 && sizeof(E) == 2 ? 4 : 2
 }
 
 // The column tables serve the backward only, so an inference forward
-// (TRAIN false) launches no workgroups for them.
+// (TRAIN false) launches no workgroups for them, nor does the no-mask mode.
 template <typename E, int D, bool TRAIN>
 hipError_t launch_fwd_dt(const FwdArgs& a, hipStream_t s) {
   const int nqb = a.BH * a.T;
-  const int ncol = TRAIN ? (nqb + FWD_COLS_PER_WG - 1) / FWD_COLS_PER_WG : 0;
+  const int ncol = TRAIN && a.k_index ? (nqb + FWD_COLS_PER_WG - 1) / FWD_COLS_PER_WG : 0;
   dim3 grid((unsigned)(nqb + ncol)), block(FWD_NT);
   auto kernel = fwd_kernel<E, D, 0, TRAIN>;
   if (a.gk == 1) kernel = fwd_kernel<E, D, 1, TRAIN>;

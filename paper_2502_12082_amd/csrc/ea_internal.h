@@ -16,7 +16,7 @@ constexpr int MAX_KEY_BLOCKS = MAX_SEQLEN / 64;
 // {1, 2, 4} run without transcendentals; 0 means general alpha.
 int gamma_kind(float alpha);
 
-// One cached score of the no-mask forward's solver: the raw score
+// One cached score of a later fill of the solver's lists: the raw score
 // s = <q_i, k_j> (the solver forms x - tau from it exactly as in a streamed
 // evaluation) and the key j.
 struct alignas(8) CandEntry {
@@ -24,15 +24,13 @@ struct alignas(8) CandEntry {
   int32_t j;  // key index; its key block is j / 64
 };
 
-// Workgroup geometry (rows and threads per workgroup) of the masked path's
-// solver and of the no-mask fused forward.  Each row has two candidate
-// lists (one per half of every key block), of `cap` entries each.
+// Workgroup geometry (rows and threads per workgroup) of the solver.  Each row
+// has two candidate lists (one per half of every key block), of `cap` entries
+// each.
 constexpr int SOLVE_ROWS = 256;
 constexpr int SOLVE_THREADS = 256;
-constexpr int TAU_ROWS = 128;
-constexpr int TAU_THREADS = 256;
 
-// The masked path's solver caches quads: the four raw scores of four
+// The solver caches quads: the four raw scores of four
 // consecutive keys 4 m .. 4 m + 3 that one lane holds for one row (16 bytes),
 // with m as a 16-bit key (2 bytes, in an array of their own).  Its first
 // evaluation copies the scores above the bracket's lower end into lists of
@@ -90,15 +88,10 @@ struct TauArgs {
   const void* q;
   const void* k;
   float* tau;         // [BH, n]
-  uint8_t* mask;      // [BH, T, T]
+  uint8_t* mask;      // [BH, T, T], or null (the no-mask mode: no tables either)
   int32_t* stats;     // [2, BH, T] K passes and evaluations for each 64-row query block, or null
-  // no-mask mode only (mask, stats null): O and, when training, O2 are
-  // accumulated by the solver kernel itself once tau is known
-  const void* v;
-  void* o;            // [BH, n, D] input dtype
-  float* o2;          // [BH, n, D] fp32, or null (inference)
-  void* cand;         // candidate cache: one slot per workgroup (quads or CandEntry lists), or null
-  int cap;            // entries (quads for the masked path) per list
+  void* cand;         // candidate cache: one slot per workgroup, or null
+  int cap;            // quads per list
   int slots;          // cache slots (workgroup b of a launch uses slot b)
   int tile0;          // first tile of this launch (workgroup b solves tile tile0 + b)
   int BH, n, T;
@@ -112,8 +105,7 @@ struct TauArgs {
   // in fp64 from the same fp32 parameters
   float* tau_lo;
   double c64, g64;
-  // masked path: the row tables of the mask (Q_i of every query block),
-  // written with it
+  // the row tables of the mask (Q_i of every query block), written with it
   int32_t* q_count;   // [BH, T]
   int32_t* q_index;   // [BH, T, T]
   ListBlock* lists;   // [BH * T] (masked path, n <= LIST_MAX_SEQLEN), or null
@@ -186,6 +178,19 @@ struct DeltaArgs {
   int BH, n, T;
 };
 
+// The element lists of given thresholds (no-mask mode's backward).
+struct CollectArgs {
+  const void* q;
+  const void* k;
+  const float* tau;
+  const float* tau_lo;  // as in BwdArgs
+  ListBlock* lists;
+  int BH, n, T;
+  float c;
+  int causal, gk;
+  double c64;
+};
+
 // Row-wise alpha-entmax of a materialized [rows, n] score matrix.
 struct RowsArgs {
   const void* s;      // [rows, n] scores, input dtype
@@ -222,14 +227,13 @@ hipError_t launch_tau_bf16_64(const TauArgs& a, hipStream_t s);
 hipError_t launch_tau_bf16_128(const TauArgs& a, hipStream_t s);
 hipError_t launch_tau_f32_64(const TauArgs& a, hipStream_t s);
 hipError_t launch_tau_f32_128(const TauArgs& a, hipStream_t s);
-// The no-mask forward: tau, then O (and O2 if a.o2) in the same kernel.
-hipError_t launch_tau_fused(const TauArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_fwd(const FwdArgs& a, int dtype, int head_dim, bool train, hipStream_t s);
 hipError_t launch_delta(const DeltaArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dkdv(const BwdArgs& a, int dtype, int head_dim, hipStream_t s);
 // dK and dV of the listed query blocks, added to what launch_bwd_dkdv (given
 // the same lists) wrote for the others.
 hipError_t launch_bwd_dkdv_lists(const BwdArgs& a, int dtype, int head_dim, hipStream_t s);
+hipError_t launch_collect(const CollectArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dq(const BwdArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_rows_fwd(const RowsArgs& a, int dtype, hipStream_t s);
 hipError_t launch_rows_bwd(const RowsArgs& a, int dtype, hipStream_t s);

@@ -348,12 +348,12 @@ __global__ __launch_bounds__(SM_NT, KT <= 4 ? 4 : 2) void solve_small_kernel(Tau
   }
   if (w != 0) return;
   // mask row and row table (at most 16 key blocks)
-  const bool b = lane < T && (mask >> lane & 1u);
-  if (lane < T) a.mask[((size_t)bh * T + qb) * T + lane] = b ? 1 : 0;
+  const bool b = lane < T && (mask >> lane & 1u), tables = a.mask != nullptr;
+  if (tables && lane < T) a.mask[((size_t)bh * T + qb) * T + lane] = b ? 1 : 0;
   const unsigned long long m = __ballot(b);
-  if (b) a.q_index[((size_t)bh * T + qb) * T + __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)] = lane;
+  if (tables && b) a.q_index[((size_t)bh * T + qb) * T + __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)] = lane;
   if (lane == 0) {
-    a.q_count[(size_t)bh * T + qb] = blocks;
+    if (tables) a.q_count[(size_t)bh * T + qb] = blocks;
     if (a.stats) {
       a.stats[(size_t)bh * T + qb] = 1;
       a.stats[((size_t)a.BH + bh) * T + qb] = evals;

@@ -36,573 +36,6 @@ namespace ea {
 
 namespace {
 
-constexpr int TAU_WAVES = 4;
-constexpr int TAU_NT = 64 * TAU_WAVES;
-constexpr int TAU_ROWS = 32 * TAU_WAVES;
-
-// MODE: FUSED_O (inference) and FUSED_O2 (training) are the no-mask forward
-// of Algorithm 2: once tau is known, the same workgroup streams K and V once
-// more and writes O (and O2), with no mask or tables.
-constexpr int FUSED_O = 1, FUSED_O2 = 2;
-
-template <typename E, int D, int GK, int MODE>
-__global__ __launch_bounds__(TAU_NT, 2) void tau_solve_kernel(TauArgs a) {
-  using TL = PadTile<E, D>;
-  using TV = Tile<E, D>;
-  using M = Mma<E>;
-  constexpr int KS = D / M::KW;
-  constexpr int NTD = D / 32;
-  constexpr int PS = perm_steps<E>();
-  constexpr bool TRAIN = MODE == FUSED_O2;
-  __shared__ __attribute__((aligned(16))) E kbuf[2][TL::ELEMS];
-  __shared__ __attribute__((aligned(16))) E vbuf[2][TV::ELEMS];
-
-  const int lane = lane_id(), w = wave_id();
-  const int n = a.n, T = a.T;
-  const int nqt = (n + TAU_ROWS - 1) / TAU_ROWS;
-  const float c = a.c, g = a.gamma;
-  // The Newton step from any tau is a lower bound of the root when f is
-  // convex, i.e. gamma >= 1 (alpha <= 2).
-  const bool newton_bound = g >= 1.f;
-  // Tile a.tile0 + blockIdx.x, and this workgroup's slot of the candidate
-  // cache (entry e of thread t at [e * TAU_NT + t]), or null when the
-  // workspace has no slot for it.  A launch covers at most one tile per slot
-  // (see launch_tiles).
-  const int tile = a.tile0 + (int)blockIdx.x;
-  CandEntry* const cache = a.cand && (int)blockIdx.x < a.slots
-                               ? static_cast<CandEntry*>(a.cand) + (size_t)blockIdx.x * a.cap * TAU_NT
-                               : nullptr;
-
-  TileDma<TL, D, TAU_NT> dma;
-  dma.init();
-
-  {
-    const int bh = tile % a.BH;
-    int qt = tile / a.BH;
-    if (a.causal) qt = nqt - 1 - qt;  // longest rows first
-    const int q0 = qt * TAU_ROWS + 32 * w;
-    const int i = q0 + (lane & 31);
-    const bool row_ok = i < n;
-    const int ni = a.causal ? i + 1 : n;
-    const E* Q = static_cast<const E*>(a.q) + (size_t)bh * n * D;
-    const E* K = static_cast<const E*>(a.k) + (size_t)bh * n * D;
-
-    const int wg_last = min(n, (qt + 1) * TAU_ROWS) - 1;
-    const int nkb = a.causal ? wg_last / BLK + 1 : T;
-    const int wave_last = min(n - 1, q0 + 31);
-    const bool wave_ok = q0 < n;
-
-    typename M::frag qf[KS];
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) qf[kk] = load_row_frag_global<E, D>(Q, i, n, kk);
-
-    // Streams every key block the tile needs, double-buffered: block kb + 1
-    // is copied into LDS while `body(kb, tile)` works on block kb.
-    auto stream = [&](auto&& body) {
-      dma.issue(kbuf[0], K, 0, n);
-      for (int kb = 0; kb < nkb; ++kb) {
-        dma_wait();
-        __syncthreads();
-        if (kb + 1 < nkb) dma.issue(kbuf[(kb + 1) & 1], K, (kb + 1) * BLK, n);
-        body(kb, kbuf[kb & 1]);
-      }
-      __syncthreads();  // the next pass refills buffer 0
-    };
-
-    // S^T sub-tiles of the staged block: keys [0, 32) and [32, 64) x this
-    // wave's 32 queries; value r of lane l is key 32 sub + crow(r), query
-    // l%32.  The two accumulation chains are interleaved so neither waits on
-    // the other.
-    auto scores = [&](const E* kt, f32x16& s0, f32x16& s1) {
-      s0 = zero16();
-      s1 = zero16();
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        const typename M::frag a0 = lds_row_frag_pad<E, D>(kt, (lane & 31), kk);
-        const typename M::frag a1 = lds_row_frag_pad<E, D>(kt, 32 + (lane & 31), kk);
-        s0 = M::mma(a0, qf[kk], s0);
-        s1 = M::mma(a1, qf[kk], s1);
-      }
-    };
-    // Sub-tile state for the calling wave: 0 = nothing valid, 1 = all valid,
-    // 2 = needs per-element masking (ragged tail or causal diagonal).
-    auto sub_kind = [&](int j0) {
-      if (!wave_ok || j0 >= n || (a.causal && j0 > wave_last)) return 0;
-      if (j0 + 31 >= n || (a.causal && j0 + 31 > q0)) return 2;
-      return 1;
-    };
-    auto valid = [&](int j) { return j < n && (!a.causal || j <= i); };
-    // Invalid keys of a masked sub-tile become -inf: they cannot be the
-    // maximum, and the clamp of [x - tau]_+ turns them into exactly 0.
-    auto mask_tile = [&](f32x16& s, int j0) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (!valid(j0 + crow(r))) s[r] = -INFINITY;
-    };
-
-    // ---- pass 0: row maximum of the raw scores (scale > 0, so the maximum
-    // of x = c s is c times the maximum of s), and a tighter lower end of
-    // the bracket: if j distinct keys score at least v, each of their terms
-    // of f is at least (c v - tau)^gamma at any tau below c v, so at the root
-    // j (c v - tau)^gamma <= 1 and tau >= c v - j^(-1/gamma).  j = 1 with v
-    // the maximum is Algorithm 1's tau >= max - 1.  Each lane keeps the four
-    // largest maxima of its 16-score sub-tile columns (each over keys of its
-    // own); the two lanes of a row merge theirs into the row's eight largest,
-    // and v_j is the j-th of those.
-    float t4[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};  // descending
-    auto tile_max = [&](const f32x16& s) {
-      float v = fmaxf(s[0], s[1]);
-#pragma unroll
-      for (int r = 2; r < 16; r += 2) v = fmaxf(v, fmaxf(s[r], s[r + 1]));
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float h = fmaxf(t4[j], v);
-        v = fminf(t4[j], v);
-        t4[j] = h;
-      }
-    };
-    stream([&](int kb, const E* kt) {
-      const int j0 = kb * BLK;
-      const int k0 = sub_kind(j0), k1 = sub_kind(j0 + 32);
-      if (k0 == 0 && k1 == 0) return;
-      f32x16 s0, s1;
-      scores(kt, s0, s1);
-      if (k0 == 2) mask_tile(s0, j0);
-      if (k1 == 2) mask_tile(s1, j0 + 32);
-      if (k0) tile_max(s0);
-      if (k1) tile_max(s1);
-    });
-
-    float lo = 0.f, hi = 0.f, tau = 0.f;
-    {
-      // the row's eight largest sub-tile maxima, descending: the two lanes'
-      // sorted lists merged by Batcher's odd-even network
-      float u[8];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        u[j] = t4[j];
-        u[4 + j] = __shfl_xor(t4[j], 32);
-      }
-      auto cx = [&](int x, int y) {
-        const float h = fmaxf(u[x], u[y]);
-        u[y] = fminf(u[x], u[y]);
-        u[x] = h;
-      };
-      cx(0, 4); cx(1, 5); cx(2, 6); cx(3, 7);
-      cx(2, 4); cx(3, 5);
-      cx(1, 2); cx(3, 4); cx(5, 6);
-      if (row_ok) {
-        const float m = c * u[0];
-        hi = m - powf((float)ni, 1.f - a.alpha);
-        float b = m - 1.f;
-#pragma unroll
-        for (int j = 1; j < 8; ++j) b = fmaxf(b, fmaf(c, u[j], -exp2f(-__log2f((float)(j + 1)) / g)));
-        // For gamma >= 1, two Newton steps on f restricted to these eight
-        // scores: that f is convex and decreasing, so the steps stay below
-        // its root, which is below tau (the dropped terms are >= 0).  Every z
-        // is at most 1 and z_1 > 0, so the derivative is nonzero.
-        if (g >= 1.f) {
-#pragma unroll
-          for (int it = 0; it < 2; ++it) {
-            float f = -1.f, fp = 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const float z = fmaf(c, u[j], -b);
-              if (z > 0.f) {
-                float pj, uj;
-                Gamma<GK>::pu(z, g, pj, uj);
-                f += pj;
-                fp += uj;
-              }
-            }
-            b += f / (g * fp);
-          }
-        }
-        // the bound may round above the root by a few ulps (rows whose whole
-        // support is among the eight reach it)
-        lo = fminf(b - 4e-6f * fmaxf(1.f, fabsf(b)), hi);
-        tau = 0.5f * (lo + hi);
-      }
-    }
-
-    bool cached = false; // evaluations run on the candidate cache
-    int attempts = 0;    // cache fills tried
-    int cc = 0;          // candidates this thread found in the last fill
-    int cmax = 0;        // wave maximum of cc once the cache is in use
-    __shared__ int fill_full;  // some list of the current fill overflowed
-    CandEntry* const mine = cache ? cache + threadIdx.x : nullptr;
-    // Reads this thread's list in batches of eight independent loads and
-    // calls `use` on each entry; the trip count is the wave's longest list.
-    auto scan = [&](auto&& use) {
-      for (int e0 = 0; e0 < cmax; e0 += 8) {
-        CandEntry ce[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (e0 + u < cc) ce[u] = mine[(size_t)(e0 + u) * TAU_NT];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (e0 + u < cc) use(ce[u]);
-      }
-    };
-    bool small_support = false;  // every thread's support count <= cap / 2
-    float f_prev = INFINITY;     // |f| at the previous evaluation
-    float usum = 0.f;            // sum of u = z^(gamma-1) over the row at the last tau
-    for (int it = 0;; ++it) {
-      // ---- evaluation at tau: m0 = sum z^gamma, m1 = sum z^(gamma-1),
-      // m2 = sum z^(gamma-2) over the strict support z > 0, and mc = the size
-      // of the support (for gamma = 1, 2 that is the last sum, counted exactly
-      // as an integer).
-      float m0 = 0.f, m1 = 0.f, m2 = 0.f;
-      int mc = 0;
-      // Adds the terms of one value z = [x - tau]_+ (clamped to [0, 1]) to
-      // (t0, t1, t2, tc).
-      auto add_z = [&](float zp, float& t0, float& t1, float& t2, int& tc) {
-        if constexpr (GK == 1) {
-          t0 += zp;
-          tc += in_support(zp);
-        } else if constexpr (GK == 2) {
-          t0 = fmaf(zp, zp, t0);
-          t1 += zp;
-          tc += in_support(zp);
-        } else if constexpr (GK == 4) {
-          const float z2 = zp * zp;
-          t0 = fmaf(z2, z2, t0);
-          t1 = fmaf(z2, zp, t1);
-          t2 += z2;
-          tc += in_support(zp);
-        } else {
-          if (zp > 0.f) {
-            const float l = __log2f(zp);
-            t0 += exp2f(g * l);
-            t1 += exp2f((g - 1.f) * l);
-            t2 += exp2f((g - 2.f) * l);
-            ++tc;
-          }
-        }
-      };
-      // Adds one sub-tile to the sums.
-      auto eval_tile = [&](const f32x16& s) {
-        if constexpr (GK == 1 || GK == 2) {
-          int cnt = 0;
-#pragma unroll
-          for (int r = 0; r < 16; r += 2) {
-            const float za = relu_z(c, s[r], tau), zb = relu_z(c, s[r + 1], tau);
-            if constexpr (GK == 1) {
-              m0 += za;
-              m0 += zb;
-            } else {
-              m0 = fmaf(za, za, m0);
-              m0 = fmaf(zb, zb, m0);
-              m1 += za;
-              m1 += zb;
-            }
-            cnt += in_support(za) + in_support(zb);
-          }
-          mc += cnt;
-        } else {
-          float t0 = 0.f;  // summed per tile, then added to the row sum
-#pragma unroll
-          for (int r = 0; r < 16; ++r) add_z(relu_z(c, s[r], tau), t0, m1, m2, mc);
-          m0 += t0;
-        }
-      };
-      // Appends the entries x > lo of a sub-tile to this thread's cache list.
-      // Every later tau stays >= lo, so the entries left out are 0 there.
-      // The threshold in score units carries a margin for the rounding of
-      // lo / c (a superset of the entries is harmless).
-      const float s_lo0 = lo / c;
-      const float s_lo = row_ok ? s_lo0 - 1e-6f * fmaxf(fabsf(s_lo0), 1.f / c) : INFINITY;
-      auto fill_tile = [&](const f32x16& s, int jb) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          if (s[r] > s_lo) {
-            if (cc < a.cap) mine[(size_t)cc * TAU_NT] = CandEntry{s[r], jb + crow(r)};
-            ++cc;
-          }
-        }
-      };
-      // Decides, after a fill, whether every list fit.
-      auto fill_done = [&]() {
-        if (!__syncthreads_or(cc > a.cap)) {
-          cached = true;
-          cmax = cc;
-#pragma unroll
-          for (int o = 32; o >= 1; o >>= 1) cmax = max(cmax, __shfl_xor(cmax, o));
-        }
-      };
-
-      // A tile with a cache slot collects its candidates x > lo during the
-      // first evaluation; if a list overflows, it tries (once more) later in
-      // a K pass of its own, when the last streamed evaluation suggests that
-      // they fit, and that evaluation then runs on the cache.  Otherwise the
-      // evaluation streams K.
-      if (!cached && cache && it >= 1 && attempts < 2 && small_support) {
-        ++attempts;
-        cc = 0;
-        stream([&](int kb, const E* kt) {
-          const int j0 = kb * BLK;
-          const int k0 = sub_kind(j0), k1 = sub_kind(j0 + 32);
-          if (k0 == 0 && k1 == 0) return;
-          f32x16 s0, s1;
-          scores(kt, s0, s1);
-          if (k0 == 2) mask_tile(s0, j0);
-          if (k1 == 2) mask_tile(s1, j0 + 32);
-          if (k0) fill_tile(s0, j0);
-          if (k1) fill_tile(s1, j0 + 32);
-        });
-        fill_done();
-      }
-      if (!cached) {
-        // streamed evaluation
-        const bool fill = cache && it == 0;
-        if (fill) {
-          ++attempts;
-          cc = 0;
-          if (threadIdx.x == 0) fill_full = 0;  // read after the first block's barrier
-        }
-        stream([&](int kb, const E* kt) {
-          const int j0 = kb * BLK;
-          const int k0 = sub_kind(j0), k1 = sub_kind(j0 + 32);
-          // once a list of this fill has overflowed, no thread stores more
-          const bool fill_now = fill && !fill_full;
-          if (k0 == 1 && k1 == 1) {  // every key valid: one straight-line block
-            f32x16 s0, s1;
-            scores(kt, s0, s1);
-            eval_tile(s0);
-            eval_tile(s1);
-            if (fill_now) {
-              fill_tile(s0, j0);
-              fill_tile(s1, j0 + 32);
-            }
-          } else if (k0 != 0 || k1 != 0) {
-            f32x16 s0, s1;
-            scores(kt, s0, s1);
-            if (k0 == 2) mask_tile(s0, j0);
-            if (k1 == 2) mask_tile(s1, j0 + 32);
-            if (k0) eval_tile(s0);
-            if (k1) eval_tile(s1);
-            if (fill_now) {
-              if (k0) fill_tile(s0, j0);
-              if (k1) fill_tile(s1, j0 + 32);
-            }
-          }
-          if (fill_now && cc > a.cap) fill_full = 1;
-        });
-        // support sizes at this tau, a guide to the size of the candidate lists
-        small_support = !__syncthreads_or(mc > a.cap / 2);
-        if (fill) {
-          if (fill_full) cc = a.cap + 1;  // the fill stopped early: its lists are incomplete
-          fill_done();
-        }
-      } else {
-        // cached evaluation: the same sums over this thread's list
-        scan([&](const CandEntry& ce) {
-          add_z(relu_z(c, ce.s, tau), m0, m1, m2, mc);
-        });
-      }
-      if constexpr (GK == 1) m1 = (float)mc;
-      if constexpr (GK == 2) m2 = (float)mc;
-      m0 += __shfl_xor(m0, 32);
-      m1 += __shfl_xor(m1, 32);
-      m2 += __shfl_xor(m2, 32);
-      usum = m1;
-
-      const float f = m0 - 1.f;                        // Eq. 3
-      float f1, f2;                                    // Eq. 6, 7
-      if constexpr (GK == 1) {
-        f1 = -m1;
-        f2 = 0.f;
-      } else if constexpr (GK == 2) {
-        f1 = -2.f * m1;
-        f2 = 2.f * m2;
-      } else if constexpr (GK == 4) {
-        f1 = -4.f * m1;
-        f2 = 12.f * m2;
-      } else {
-        f1 = -g * m1;
-        f2 = g * (g - 1.f) * m2;
-      }
-      const bool conv = !row_ok || fabsf(f) <= a.tol;
-      if (__syncthreads_and(conv) || it >= a.max_iter) break;
-      if (row_ok) {
-        if (f < 0.f)  // B_f, Eq. 4 ("otherwise" branch when f == 0)
-          hi = tau;
-        else
-          lo = tau;
-        // Bracket test of Algorithm 1 with fp32 rounding: when the root sits
-        // on an end of the bracket (one-hot rows: tau = max - 1; constant
-        // rows: tau = max - n^(1-alpha)) the Halley value lands within a few
-        // ulps on either side of it, so values within `slack` are accepted
-        // and clamped into [lo, hi].  NaN and inf fail the test and take the
-        // midpoint.
-        const float slack = 1e-6f * fmaxf(1.f, fmaxf(fabsf(lo), fabsf(hi)));
-        if (newton_bound && f1 < 0.f) {
-          // convexity: the tangent at tau meets zero at or below the root;
-          // a margin of 10 slacks covers the rounding of that point
-          const float tn = tau - f / f1 - 10.f * slack;
-          lo = fminf(fmaxf(lo, tn), hi);
-        }
-        const float th = tau - 2.f * f * f1 / (2.f * f1 * f1 - f * f2);  // H_f, Eq. 5
-        bool take = th >= lo - slack && th <= hi + slack;
-        // For gamma < 1 (alpha > 2) f' diverges at every kink x_j, and H_f can
-        // creep towards a kink in ever smaller steps that all stay inside
-        // the bracket, so the fail-safe above never fires.  There the
-        // midpoint is also taken whenever |f| has not halved since the last
-        // evaluation, which bounds the bracket's shrinkage from below.
-        if (!newton_bound && fabsf(f) > 0.5f * f_prev) take = false;
-        f_prev = fabsf(f);
-        tau = take ? fminf(fmaxf(th, lo), hi) : 0.5f * (lo + hi);
-      }
-    }
-
-    // fp32 inputs, general alpha (ea_common.h): tau refined in fp64 by Newton
-    // steps on f (Eq. 3, 6) over every entry above the lower edge of the band
-    // around the support edge, each with its fp64 score, as in solve_kernel.
-    constexpr bool PRECISE = precise_path<E, GK>();
-    double tau64 = tau;
-    [[maybe_unused]] const float band = PRECISE_BAND * fmaxf(1.f, fabsf(tau));
-    [[maybe_unused]] const float* Qf = reinterpret_cast<const float*>(Q);
-    [[maybe_unused]] const float* Kf = reinterpret_cast<const float*>(K);
-    if constexpr (PRECISE) {
-      // use(fp32 score, key) for every valid entry of this lane's row
-      auto visit = [&](auto&& use) {
-        if (cached) {
-          scan([&](const CandEntry& ce) { use(ce.s, ce.j); });
-        } else {
-          stream([&](int kb, const E* kt) {
-            const int j0 = kb * BLK;
-            const int k0 = sub_kind(j0), k1 = sub_kind(j0 + 32);
-            if (k0 == 0 && k1 == 0) return;
-            f32x16 s0, s1;
-            scores(kt, s0, s1);
-            if (k0 == 2) mask_tile(s0, j0);
-            if (k1 == 2) mask_tile(s1, j0 + 32);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              if (k0) use(s0[r], j0 + crow(r));
-              if (k1) use(s1[r], j0 + 32 + crow(r));
-            }
-          });
-        }
-      };
-      for (int it = 0; it < 3; ++it) {
-        double t0 = 0.0, t1 = 0.0;
-        visit([&](float sv, int jv) {
-          if (!row_ok || !(fmaf(c, sv, -tau) > -band)) return;
-          const double z = exact_x<D>(Qf + (size_t)i * D, Kf + (size_t)jv * D, a.c64) - tau64;
-          if (z > 0.0) {
-            t0 += pow(z, a.g64);
-            t1 += pow(z, a.g64 - 1.0);
-          }
-        });
-        t0 += __shfl_xor(t0, 32);
-        t1 += __shfl_xor(t1, 32);
-        if (row_ok && t1 > 0.0) {
-          const double slack = 1e-5 * fmax(1.0, fmax(fabs((double)lo), fabs((double)hi)));
-          const double tn = tau64 + (t0 - 1.0) / (a.g64 * t1);
-          tau64 = fmin(fmax(tn, (double)lo - slack), (double)hi + slack);
-        }
-      }
-    }
-    if (row_ok && lane < 32) {
-      const float th = (float)tau64;
-      a.tau[(size_t)bh * n + i] = th;
-      if (a.tau_lo) a.tau_lo[(size_t)bh * n + i] = PRECISE ? (float)(tau64 - (double)th) : 0.f;
-    }
-
-    {
-      // ---- Algorithm 2 at the returned tau: O = sum_j P_ij V_j, and in
-      // training O2 = sum_j u_ij V_j / sum_j u_ij (sum u is the solver's last
-      // S1 sum, or, on the fp64 path, the sum of the u this pass forms), over
-      // every valid key block.
-      f32x16 o[NTD], o2[NTD];
-#pragma unroll
-      for (int t = 0; t < NTD; ++t) {
-        o[t] = zero16();
-        if constexpr (TRAIN) o2[t] = zero16();
-      }
-      const E* V = static_cast<const E*>(a.v) + (size_t)bh * n * D;
-      TileDma<TV, D, TAU_NT> vdma;
-      vdma.init();
-      [[maybe_unused]] float usum_pv = 0.f;  // the fp64 path's sum of u
-      auto pv_tile = [&](const f32x16& s, const E* vt, int sub, int j0) {
-        float p[16], u[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float zp;
-          if constexpr (PRECISE) {
-            zp = precise_relu_z<D>(row_ok, c, s[r], tau, band, tau64, Qf + (size_t)i * D,
-                                   Kf + (size_t)(j0 + 32 * sub + crow(r)) * D, a.c64);
-          } else {
-            zp = relu_z(c, s[r], tau);
-          }
-          if constexpr (TRAIN) {
-            Gamma<GK>::pu(zp, g, p[r], u[r]);
-            if constexpr (PRECISE) usum_pv += u[r];
-          } else {
-            p[r] = Gamma<GK>::p_only(zp, g);
-          }
-        }
-#pragma unroll
-        for (int t = 0; t < PS; ++t) {
-          typename M::frag ph, pl, uh, ul;
-          M::pack_split(p, t, ph, pl);
-          if constexpr (TRAIN) M::pack_split(u, t, uh, ul);
-#pragma unroll
-          for (int nt = 0; nt < NTD; ++nt) {
-            const typename M::frag vb = lds_perm_frag<E, D>(vt, 32 * nt, 32 * sub, t);
-            o[nt] = M::mma(ph, vb, o[nt]);
-            if constexpr (!M::exact_operands) o[nt] = M::mma(pl, vb, o[nt]);
-            if constexpr (TRAIN) {
-              o2[nt] = M::mma(uh, vb, o2[nt]);
-              if constexpr (!M::exact_operands) o2[nt] = M::mma(ul, vb, o2[nt]);
-            }
-          }
-        }
-      };
-      dma.issue(kbuf[0], K, 0, n);
-      vdma.issue(vbuf[0], V, 0, n);
-      for (int kb = 0; kb < nkb; ++kb) {
-        dma_wait();
-        __syncthreads();
-        if (kb + 1 < nkb) {
-          dma.issue(kbuf[(kb + 1) & 1], K, (kb + 1) * BLK, n);
-          vdma.issue(vbuf[(kb + 1) & 1], V, (kb + 1) * BLK, n);
-        }
-        const int j0 = kb * BLK;
-        const int k0 = sub_kind(j0), k1 = sub_kind(j0 + 32);
-        if (k0 == 0 && k1 == 0) continue;
-        f32x16 s0, s1;
-        scores(kbuf[kb & 1], s0, s1);
-        if (k0 == 2) mask_tile(s0, j0);
-        if (k1 == 2) mask_tile(s1, j0 + 32);
-        if (k0) pv_tile(s0, vbuf[kb & 1], 0, j0);
-        if (k1) pv_tile(s1, vbuf[kb & 1], 1, j0);
-      }
-      if constexpr (PRECISE && TRAIN) usum = usum_pv + __shfl_xor(usum_pv, 32);
-      if (!wave_ok) return;
-      // accumulator value r of lane l: query q0 + crow(r), column 32 nt + l % 32
-      E* O = static_cast<E*>(a.o) + (size_t)bh * n * D;
-      float* O2 = TRAIN ? a.o2 + (size_t)bh * n * D : nullptr;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = crow(r);
-        const int ir = q0 + row;
-        float us = 0.f;
-        if constexpr (TRAIN) us = __shfl(usum, row);
-        if (ir < n) {
-#pragma unroll
-          for (int nt = 0; nt < NTD; ++nt) {
-            const size_t off = (size_t)ir * D + 32 * nt + (lane & 31);
-            O[off] = (E)o[nt][r];
-            if constexpr (TRAIN) O2[off] = us > 0.f ? o2[nt][r] / us : 0.f;
-          }
-        }
-      }
-    }
-  }
-}
-
 // ----------------------------------------------------------- masked solver
 //
 // The solver of the masked path (tau, the block mask and stats).  One
@@ -1784,17 +1217,19 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   if (!wave_ok || !writer) return;
   // The block's mask row and its row table (Sec. 3.2.1): Q_i ascending, by
   // a ballot and a prefix count per 64 key blocks.
+  // (The no-mask mode takes neither.)
+  const bool tables = a.mask != nullptr;
   int32_t* const row = a.q_index + ((size_t)bh * T + qb) * T;
   int listed = 0;
   for (int k0 = 0; k0 < T; k0 += 64) {
     const int kb = k0 + lane;
     const bool b = kb < T && ((bits[qbl * BW + (kb >> 5)] >> (kb & 31)) & 1u);
-    if (kb < T) a.mask[((size_t)bh * T + qb) * T + kb] = b ? 1 : 0;
+    if (tables && kb < T) a.mask[((size_t)bh * T + qb) * T + kb] = b ? 1 : 0;
     const unsigned long long m = __ballot(b);
-    if (b) row[listed + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = kb;
+    if (tables && b) row[listed + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = kb;
     listed += __popcll(m);
   }
-  if (lane == 0) a.q_count[(size_t)bh * T + qb] = listed;
+  if (tables && lane == 0) a.q_count[(size_t)bh * T + qb] = listed;
   if (a.lists && lane == 0)
     a.lists[(size_t)bh * T + qb].used = cached ? list_use(lsum[qbl], listed, T, sizeof(E) == 4) : LIST_NONE;
   if (a.stats && lane == 0) {
@@ -1819,15 +1254,6 @@ hipError_t launch_tiles(K kernel, TauArgs a, int rows, int threads, hipStream_t 
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-template <typename E, int D, int MODE>
-hipError_t launch_tau_d(const TauArgs& a, hipStream_t s) {
-  auto kernel = tau_solve_kernel<E, D, 0, MODE>;
-  if (a.gk == 1) kernel = tau_solve_kernel<E, D, 1, MODE>;
-  if (a.gk == 2) kernel = tau_solve_kernel<E, D, 2, MODE>;
-  if (a.gk == 4) kernel = tau_solve_kernel<E, D, 4, MODE>;
-  return launch_tiles(kernel, a, TAU_ROWS, TAU_NT, s);
 }
 
 template <typename E, int D, int G>
@@ -1891,21 +1317,6 @@ hipError_t launch_tau(const TauArgs& a, int dtype, int head_dim, hipStream_t s) 
   if (small_solver(a, dtype, head_dim)) return launch_tau_small(a, dtype, head_dim, s);
   if (dtype == 0) return head_dim == 64 ? launch_tau_bf16_64(a, s) : launch_tau_bf16_128(a, s);
   return head_dim == 64 ? launch_tau_f32_64(a, s) : launch_tau_f32_128(a, s);
-}
-
-namespace {
-template <int MODE>
-hipError_t launch_tau_mode(const TauArgs& a, int dtype, int head_dim, hipStream_t s) {
-  if (dtype == 0)
-    return head_dim == 64 ? launch_tau_d<__bf16, 64, MODE>(a, s) : launch_tau_d<__bf16, 128, MODE>(a, s);
-  return head_dim == 64 ? launch_tau_d<float, 64, MODE>(a, s) : launch_tau_d<float, 128, MODE>(a, s);
-}
-
-}  // namespace
-
-hipError_t launch_tau_fused(const TauArgs& a, int dtype, int head_dim, hipStream_t s) {
-  return a.o2 ? launch_tau_mode<FUSED_O2>(a, dtype, head_dim, s)
-              : launch_tau_mode<FUSED_O>(a, dtype, head_dim, s);
 }
 #else
 #error "EA_TAU_PART must be 0 .. 4"
