@@ -57,7 +57,7 @@ class ResidualPtrs(ctypes.Structure):
     """The ABI's ea_residuals.  `lists` and `lists_bytes`, set by
     Residuals.ptrs(), name the element lists that belong to them; the calls
     below then pass those on."""
-    lists, lists_bytes = None, 0
+    lists, lists_bytes, lists_shape = None, 0, None
     _fields_ = [(f, ctypes.c_void_p) for f in
                 ("tau", "o2", "block_mask", "q_count", "q_index", "k_count", "k_index", "stats",
                  "tau_lo")]
@@ -161,10 +161,16 @@ def entmax_attn_lists_bytes(shape: Shape, params: Params) -> int:
     return n.value
 
 
+def _dims(shape):
+    return shape.batch, shape.heads, shape.seqlen, shape.head_dim
+
+
 def _lists_of(res: ResidualPtrs, shape, params):
     """The lists of res, as (pointer, bytes), if they serve this shape."""
     if res.lists is None:
         return None, 0
+    if res.lists_shape == _dims(shape):
+        return res.lists, res.lists_bytes
     n = ctypes.c_size_t()
     st = _lib.entmax_attn_lists_bytes(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(n))
     return (res.lists, res.lists_bytes) if st == EA_OK and 0 < n.value <= res.lists_bytes else (None, 0)
@@ -263,55 +269,104 @@ def make_params(alpha=1.5, scale=None, causal=False, need_bwd=True, max_iter=Non
     return p
 
 
+_memory = {}  # total memory of each device, a constant of the device
+
+
 def _lists_limit(device) -> int:
     """Largest element lists that Residuals allocates: a sixteenth of the
     device's memory."""
     device = torch.device(device)
     if device.type != "cuda":
         return 1 << 30
-    return torch.cuda.get_device_properties(device).total_memory // 16
+    if device.index not in _memory:
+        _memory[device.index] = torch.cuda.get_device_properties(device).total_memory
+    return _memory[device.index] // 16
+
+
+def _lists_size(shape, params, device, least) -> int:
+    """Bytes of the element lists to allocate, or 0: from `least` keys on (a
+    quarter of that for fp32, whose products take longer), since the sort and
+    the list kernel of the backward are launches of their own, and few blocks
+    of a short sequence are listed."""
+    if shape.seqlen <= (least if shape.dtype == EA_BF16 else least // 4):
+        return 0
+    nbytes = entmax_attn_lists_bytes(shape, params)
+    return nbytes if nbytes <= _lists_limit(device) else 0
+
+
+# Measured, in us, with lists against without: B64 H16 n128 d64 alpha 1.5
+# c = 1 150 against 140 (no block listed), B1 H1 n256 fp32 inference 26 against
+# 38; the no-mask mode collects its lists in a K pass more: B1 H2 n128 56
+# against 44, B1 H16 n4096 d128 670 against 1040.
+LISTS_FROM, DENSE_LISTS_FROM = 256, 1024
 
 
 class Residuals:
     """Device buffers (torch tensors) that the forward fills and the backward
-    reads, sized by entmax_attn_sizes."""
+    reads, sized by entmax_attn_sizes: tau, o2, tau_lo (fp32 inputs: the low
+    part of tau), lists (the element lists, see entmax_attn_fwd_lists), and
+    block_mask, q_count, q_index, k_count, k_index and stats ([0]: K passes the
+    solver streamed, [1]: its evaluations, per query block).
+
+    The last six are parts of one allocation, made into tensors where they are
+    asked for: ten allocations and views per forward took longer on the host
+    than the kernels of a short sequence on the GPU (a training step at B1 H2
+    n128: 79 us of host time with them, most of them never looked at)."""
 
     def __init__(self, shape: Shape, params: Params, device, with_stats: bool = True):
         z = entmax_attn_sizes(shape, params)
         BH, n, d = shape.batch * shape.heads, shape.seqlen, shape.head_dim
         T = (n + 63) // 64
         self.shape, self.params, self.sizes = shape, params, z
-        self.tau = torch.empty(z.tau // 4, dtype=torch.float32, device=device).view(BH, n)
-        self.o2 = (torch.empty(z.o2 // 4, dtype=torch.float32, device=device).view(BH, n, d)
+        self.tau = torch.empty((BH, n), dtype=torch.float32, device=device)
+        self.o2 = (torch.empty((BH, n, d), dtype=torch.float32, device=device)
                    if params.need_bwd else None)
-        self.block_mask = torch.empty(z.block_mask, dtype=torch.uint8, device=device).view(BH, T, T)
-        self.q_count = torch.empty(BH * T, dtype=torch.int32, device=device).view(BH, T)
-        self.q_index = torch.empty(BH * T * T, dtype=torch.int32, device=device).view(BH, T, T)
-        self.k_count = torch.empty(BH * T, dtype=torch.int32, device=device).view(BH, T)
-        self.k_index = torch.empty(BH * T * T, dtype=torch.int32, device=device).view(BH, T, T)
-        # [0]: K passes the solver streamed, [1]: its evaluations, per query block
-        self.stats = (torch.empty(z.stats // 4, dtype=torch.int32, device=device).view(2, BH, T)
-                      if with_stats else None)
-        # fp32 inputs: the low part of tau (tau + tau_lo to ~fp64 precision)
-        self.tau_lo = (torch.empty(z.tau_lo // 4, dtype=torch.float32, device=device).view(BH, n)
+        self.tau_lo = (torch.empty((BH, n), dtype=torch.float32, device=device)
                        if z.tau_lo else None)
-        # the forward's element lists (see entmax_attn_fwd_lists), or None
-        nbytes = entmax_attn_lists_bytes(shape, params)
-        self.lists = (torch.empty(nbytes, dtype=torch.uint8, device=device)
-                      if 0 < nbytes <= _lists_limit(device) else None)
+        nbytes = _lists_size(shape, params, device, LISTS_FROM)
+        self.lists = torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
+        at, parts = 0, {}
+        for name, nbytes, dims in (
+                ("q_index", z.q_index, (BH, T, T)), ("k_index", z.k_index, (BH, T, T)),
+                ("q_count", z.q_count, (BH, T)), ("k_count", z.k_count, (BH, T)),
+                ("stats", z.stats, (2, BH, T)), ("block_mask", z.block_mask, (BH, T, T))):
+            parts[name] = (at, nbytes, dims)
+            at += (nbytes + 255) // 256 * 256
+        self._parts = parts
+        self._tables = torch.empty(at, dtype=torch.uint8, device=device)
+        if not with_stats:
+            self.stats = None
+
+    def __getattr__(self, name):  # a part that is not a tensor yet
+        part = self.__dict__.get("_parts", {}).get(name)
+        if part is None:
+            raise AttributeError("Residuals has no attribute %r" % name)
+        at, nbytes, dims = part
+        t = self._tables[at:at + nbytes]
+        if name != "block_mask":
+            t = t.view(torch.int32)
+        t = t.view(dims)
+        self.__dict__[name] = t
+        return t
 
     def ptrs(self) -> ResidualPtrs:
-        f = lambda t: None if t is None else t.data_ptr()
-        p = ResidualPtrs(f(self.tau), f(self.o2), f(self.block_mask), f(self.q_count),
-                         f(self.q_index), f(self.k_count), f(self.k_index), f(self.stats),
-                         f(self.tau_lo))
+        own, base = self.__dict__, self._tables.data_ptr()
+
+        def f(name):
+            if name in own:
+                return None if own[name] is None else own[name].data_ptr()
+            return base + self._parts[name][0]
+
+        p = ResidualPtrs(*map(f, ("tau", "o2", "block_mask", "q_count", "q_index", "k_count",
+                                  "k_index", "stats", "tau_lo")))
         if self.lists is not None:
             p.lists, p.lists_bytes = self.lists.data_ptr(), self.lists.numel()
+            p.lists_shape = _dims(self.shape)
         return p
 
 
 def _stream_handle(device):
-    return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index)  # current_stream without its object
 
 
 # ------------------------------------------------------ argument checks
@@ -371,13 +426,14 @@ def _check_residuals(res, shape: Shape, device, need_o2: bool):
         if res.o2 is None:
             raise ValueError("res has no o2 (forward ran with need_bwd=False)")
         _need(res.o2, "res.o2", (BH, n, d), torch.float32, device)
-    _need(res.block_mask, "res.block_mask", (BH, T, T), torch.uint8, device)
-    _need(res.q_count, "res.q_count", (BH, T), torch.int32, device)
-    _need(res.q_index, "res.q_index", (BH, T, T), torch.int32, device)
-    _need(res.k_count, "res.k_count", (BH, T), torch.int32, device)
-    _need(res.k_index, "res.k_index", (BH, T, T), torch.int32, device)
-    if res.stats is not None:
-        _need(res.stats, "res.stats", (2, BH, T), torch.int32, device)
+    # the tables that are still parts of one buffer have their sizes from it
+    _need(res._tables, "res", res._tables.shape, torch.uint8, device)
+    own = res.__dict__
+    for name, dims, dtype in (("block_mask", (BH, T, T), torch.uint8), ("q_count", (BH, T), torch.int32),
+                              ("q_index", (BH, T, T), torch.int32), ("k_count", (BH, T), torch.int32),
+                              ("k_index", (BH, T, T), torch.int32), ("stats", (2, BH, T), torch.int32)):
+        if name in own and not (name == "stats" and own[name] is None):
+            _need(own[name], "res." + name, dims, dtype, device)
     if shape.dtype == EA_F32:
         _need(res.tau_lo, "res.tau_lo", (BH, n), torch.float32, device)
     if res.lists is not None:
@@ -514,8 +570,8 @@ def rows_backward(s, tau, dp, alpha=1.5, scale=1.0):
 
 def _scratch_lists(shape, params, device):
     """Element lists for one call of the no-mask mode: (tensor or None, pointer, bytes)."""
-    nbytes = entmax_attn_lists_bytes(shape, params)
-    if not 0 < nbytes <= _lists_limit(device):
+    nbytes = _lists_size(shape, params, device, DENSE_LISTS_FROM)
+    if not nbytes:
         return None, None, 0
     t = torch.empty(nbytes, dtype=torch.uint8, device=device)
     return t, t.data_ptr(), nbytes
