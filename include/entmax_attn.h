@@ -181,7 +181,9 @@ ea_status entmax_attn_bwd_stage(int stage, const ea_shape* shape, const ea_param
  * lists of (z = x - tau, key) per row, into `lists`; the later stages then work
  * on the listed entries of that block instead of recomputing the scores of its
  * key blocks.  The results are those of entmax_attn_fwd / entmax_attn_bwd up
- * to rounding, and the residuals are the same; `lists` is one more buffer that
+ * to rounding, and the residuals are the same (as in a skipped block, a key of
+ * zero probability adds nothing, also where its K or V row is not finite; a
+ * block of matrix products adds 0 times that row); `lists` is one more buffer that
  * the forward writes and the backward reads (and sorts into parts of its own,
  * the same ones on every call).  A backward may be given lists only with the
  * residuals of the forward that wrote them; if another forward has written

@@ -313,6 +313,8 @@ class Residuals:
     than the kernels of a short sequence on the GPU (a training step at B1 H2
     n128: 79 us of host time with them, most of them never looked at)."""
 
+    lists, _tables, _parts = None, None, {}  # objects that were saved with a tensor per table
+
     def __init__(self, shape: Shape, params: Params, device, with_stats: bool = True):
         z = entmax_attn_sizes(shape, params)
         BH, n, d = shape.batch * shape.heads, shape.seqlen, shape.head_dim
@@ -338,7 +340,7 @@ class Residuals:
             self.stats = None
 
     def __getattr__(self, name):  # a part that is not a tensor yet
-        part = self.__dict__.get("_parts", {}).get(name)
+        part = self._parts.get(name)
         if part is None:
             raise AttributeError("Residuals has no attribute %r" % name)
         at, nbytes, dims = part
@@ -350,7 +352,8 @@ class Residuals:
         return t
 
     def ptrs(self) -> ResidualPtrs:
-        own, base = self.__dict__, self._tables.data_ptr()
+        own = self.__dict__
+        base = self._tables.data_ptr() if self._parts else 0
 
         def f(name):
             if name in own:
@@ -427,7 +430,8 @@ def _check_residuals(res, shape: Shape, device, need_o2: bool):
             raise ValueError("res has no o2 (forward ran with need_bwd=False)")
         _need(res.o2, "res.o2", (BH, n, d), torch.float32, device)
     # the tables that are still parts of one buffer have their sizes from it
-    _need(res._tables, "res", res._tables.shape, torch.uint8, device)
+    if res._parts:
+        _need(res._tables, "res", res._tables.shape, torch.uint8, device)
     own = res.__dict__
     for name, dims, dtype in (("block_mask", (BH, T, T), torch.uint8), ("q_count", (BH, T), torch.int32),
                               ("q_index", (BH, T, T), torch.int32), ("k_count", (BH, T), torch.int32),
