@@ -12,8 +12,9 @@ on the current stream.
 Prints ONE JSON line.  `value` is dense-equivalent TFLOP/s (14 n^2 d per head
 for forward + backward, the FlashAttention convention) at the headline
 temperature c; `executed_tflops` counts the MFMA work the method actually
-performs (solver passes over every valid block, 10 block products per listed
-block).  `roofline` is for the kernel with the largest share of the step,
+performs (solver passes over every valid block, 10 block products per active
+block of the query blocks without element lists, the listed entries of the
+others).  `roofline` is for the kernel with the largest share of the step,
 timed with HIP events over the timed region; `cpu_baseline` is the fp64
 oracle on a bounded sample (four heads by default), on this host's cores.
 """
@@ -278,6 +279,14 @@ def parse():
     return ap.parse_args()
 
 
+# ListBlock of csrc/ea_internal.h: bytes of a record, of its counts and of its
+# use; the least use at which a stage reads the lists instead of its blocks.
+LIST_COUNTS = 48 * 128 * 6
+LIST_USE = LIST_COUNTS + 128 + 64 * 4
+LIST_RECORD = LIST_USE + 4 + 31 * 4
+LIST_LEVEL = {"fwd_sparse": 1, "bwd_dq": 2, "bwd_dkdv": 3}
+
+
 class Runner:
     """Device buffers and the six stage launches of one configuration."""
 
@@ -389,16 +398,31 @@ class Runner:
         # choice, not work of the method, and is left out.
         solver_blocks = float((stats * per_qb[None, :]).sum())
         flops = {"tau_solve": solver_blocks * f_blk, "bwd_delta": 0.0}
+        counts = self.res.q_count.cpu().numpy().reshape(-1)
+        use, entries = self.listed(BH * T)
         for k_, m in PRODUCTS_PER_ACTIVE.items():
             # the forward without a backward to follow forms S and P V only
             if k_ == "fwd_sparse" and not self.bwd:
                 m = 2
-            flops[k_] = m * n_act * f_blk
+            # a listed entry takes the same products without S, 2 d each
+            listed = use >= LIST_LEVEL[k_]
+            flops[k_] = (m * float(counts[~listed].sum()) * f_blk
+                         + (m - 1) * float(entries[listed].sum()) * 2.0 * d)
         dense = 14.0 * n * n * d * BH * (0.5 if self.params.causal else 1.0)
         return {"n_valid": n_valid, "n_act": n_act, "block_density": n_act / n_valid,
                 "passes_mean": float(stats.mean()), "passes_max": int(stats.max()),
                 "evals_mean": float(evals.mean()), "evals_max": int(evals.max()),
+                "listed": float((use > 0).mean()),
                 "flops": flops, "dense_flops": dense, "mask_nnz": int(mask.sum())}
+
+    def listed(self, blocks):
+        """(use, entries) of each 64-row query block's element lists: what they
+        serve (LIST_LEVEL) and how many nonzero probabilities they hold."""
+        if self.res.lists is None:
+            return np.zeros(blocks, np.int32), np.zeros(blocks, np.int64)
+        rec = self.res.lists[:blocks * LIST_RECORD].view(blocks, LIST_RECORD)
+        use = rec[:, LIST_USE:LIST_USE + 4].cpu().numpy().copy().view(np.int32)[:, 0]
+        return use, rec[:, LIST_COUNTS:LIST_COUNTS + 128].cpu().numpy().astype(np.int64).sum(1)
 
     def _sampled_z(self, rows):
         """x - tau (fp64, from the input values and the returned tau) on
@@ -718,6 +742,7 @@ def main():
         "step_ms": kern["_steps"],
         "kernels": kernels,
         "sparsity": {"block_density": round(work["block_density"], 4),
+                     "listed_query_blocks": round(work["listed"], 4),
                      "zero_fraction_sampled": round(run.zero_fraction(), 5),
                      "solver_passes_mean": round(work["passes_mean"], 3),
                      "solver_passes_max": work["passes_max"],
