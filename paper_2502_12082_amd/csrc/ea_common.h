@@ -525,17 +525,27 @@ struct RowGroup {
 
 // Block of a grid over B * H heads of T blocks each, workgroups being handed
 // to the eight XCDs in turn: with a multiple of eight heads, each XCD works
-// through its heads one after another, so that its L2 holds the operands of
-// one head; otherwise head by head over the whole chip.
-__device__ __forceinline__ void head_major(int b, int BH, int T, int& bh, int& blk) {
-  if (BH % 8 == 0) {
-    const int s = b >> 3;
-    bh = (b & 7) + 8 * (s / T);
-    blk = s % T;
-  } else {
-    bh = b / T;
-    blk = b % T;
-  }
+// through its heads `group` at a time, so that its L2 holds the operands of
+// those; otherwise the whole chip does.  Block t of every head of a group
+// comes before block t + 1 of any.
+__device__ __forceinline__ void head_major(int b, int BH, int T, int& bh, int& blk, int group = 1) {
+  const bool xcd = BH % 8 == 0;
+  const int heads = xcd ? BH / 8 : BH, s = xcd ? b >> 3 : b;
+  const int h0 = s / (T * group) * group, r = s - h0 * T;
+  const int g = min(group, heads - h0);
+  const int h = h0 + r % g;
+  blk = r / g;
+  bh = xcd ? (b & 7) + 8 * h : h;
+}
+
+// Heads of a group where blocks come longest first (causal): as many as have
+// one operand each in half of an XCD's 4 MiB L2.  One at a time, the long
+// blocks of the last head start when the others have drained: where few
+// blocks are listed (B1 H16 n4096 d128 alpha 1.25 c = 2) the forward took 174
+// against 168 us and dQ 144 against 140.
+template <typename E, int D>
+__device__ __forceinline__ int head_group(int causal, int n) {
+  return causal ? max(1, (2 << 20) / (n * D * (int)sizeof(E))) : 1;
 }
 
 }  // namespace ea
