@@ -431,7 +431,7 @@ __global__ __launch_bounds__(BWD_NT) void dkdv_kernel(BwdArgs a) {
     cnt = unlisted_blocks<BWD_NT>(list, a.causal ? kb : 0, cnt, a.buckets.used + (size_t)bh * T, unlisted);
     if (cnt == 0) return;
   }
-  auto qb_of = [&](int e) { return dense ? (a.causal ? kb + e : e) : some ? (int)unlisted[e] : list[e]; };
+  auto qb_of = [&](int e) { return some ? (int)unlisted[e] : dense ? (a.causal ? kb + e : e) : list[e]; };
 
   typename M::frag kf[KS], vf[KS];
 #pragma unroll
