@@ -630,11 +630,7 @@ def backward_dense(q, k, v, dout, tau, o2, alpha=1.5, scale=None, causal=False, 
     mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
     dq, dk, dv = mk(), mk(), mk()
     ws = torch.empty(max(z.ws_bwd, 16) // 4 + 4, dtype=torch.float32, device=q.device)
-    # Causal: without lists.  With them dK and dV came out wrong at B4 H2 n1920
-    # d64 alpha 1.5 c = 1.125 (relative error 0.65), where only part of a
-    # head's blocks is listed; the matrix kernels alone are right there.
-    _lists, lists_ptr, lists_bytes = ((None, None, 0) if causal else
-                                      _scratch_lists(shape, params, q.device))
+    _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device)
     _check(_lib.entmax_attn_bwd_dense_lists(
         ctypes.byref(shape), ctypes.byref(params), q.data_ptr(), k.data_ptr(), v.data_ptr(),
         dout.data_ptr(), tau.data_ptr(), tau_lo.data_ptr() if q.dtype == torch.float32 else None,
