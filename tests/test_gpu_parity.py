@@ -299,3 +299,22 @@ def test_element_lists(dtype, d, alpha, causal):
         # fp32, differ by the rounding of their sums of up to n terms
         rel = 4e-3 if dtype == "bf16" else 2e-5
         assert (a - b).norm().item() <= rel * b.norm().item()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,causal,c", [(1920, 64, True, 1.125), (1920, 64, False, 1.125),
+                                          (1920, 128, True, 1.125), (1153, 64, True, 1.0)])
+def test_dense_partly_listed(n, d, causal, c):
+    """No-mask mode where part of a head's query blocks has element lists:
+    the gradients are the masked path's (bf16 rounding of P: 2^-8 relative)."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v, do = (torch.randn(2, 2, n, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
+    q = (q.float() * c).to(torch.bfloat16)
+    _, res = ea.forward(q, k, v, alpha=1.5, causal=causal)
+    res.lists = None
+    ref = ea.backward(q, k, v, do, res)
+    _, tau, o2, lo = ea.forward_dense(q, k, v, alpha=1.5, causal=causal)
+    got = ea.backward_dense(q, k, v, do, tau, o2, alpha=1.5, causal=causal, tau_lo=lo)
+    for x, y in zip(got, ref):
+        assert (x - y).norm() <= 2 ** -8 * y.norm()
