@@ -308,6 +308,7 @@ def test_dense_partly_listed(n, d, causal, c):
     """No-mask mode where part of a head's query blocks has element lists:
     the gradients are the masked path's (bf16 rounding of P: 2^-8 relative)."""
     import torch
+    import paper_2502_12082_amd as ea
     g = torch.Generator(device="cuda").manual_seed(5)
     q, k, v, do = (torch.randn(2, 2, n, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
     q = (q.float() * c).to(torch.bfloat16)
