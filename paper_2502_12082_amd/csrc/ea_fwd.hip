@@ -73,9 +73,21 @@ __device__ __forceinline__ void gather_fwd(const FwdArgs& a, const ListBlock& lb
   const int n = a.n;
   const size_t head = (size_t)bh * n * D;
   const E* V = static_cast<const E*>(a.v) + head;
-  for (int r0 = w * R::GROUPS; r0 < BLK; r0 += 4 * R::GROUPS) {
+  // the lengths of all the rows' lists first, 16 bits a row: one wait for
+  // them instead of one a row
+  constexpr int STEP = 4 * R::GROUPS;
+  static_assert(BLK / STEP <= 8, "two registers of four rows");
+  uint64_t counts[2] = {};
+#pragma unroll
+  for (int x = 0; x < BLK / STEP; ++x) {
+    const int row = x * STEP + w * R::GROUPS + lane / LPR;
+    counts[x / 4] |= (uint64_t)(lb.count[row] | lb.count[64 + row] << 8) << (16 * (x % 4));
+  }
+  for (int r0 = w * R::GROUPS; r0 < BLK; r0 += STEP) {
     const int row = r0 + lane / LPR, i = qb * BLK + row;
-    const int c0 = lb.count[row], cnt = c0 + lb.count[64 + row];
+    const int c0 = (int)(counts[0] & 0xff), cnt = c0 + (int)(counts[0] >> 8 & 0xff);
+    counts[0] = counts[0] >> 16 | counts[1] << 48;
+    counts[1] >>= 16;
     float o[VPL] = {}, o2[VPL] = {}, usum = 0.f;
     for (int base = 0; __ballot(base < cnt) != 0ull; base += LPR) {
       // lane `sub` of a group fetches the row's entry base + sub; past the

@@ -27,6 +27,21 @@ constexpr int SM_NT = 512;
 constexpr int SM_KG = 4;      // key groups (waves per row group)
 constexpr int SM_LIST = 16;   // entries of a lane's list
 
+// Columns 8 m .. 8 m + 7 of a fp32 row, held as 8 m + 4 h + e by the row's two
+// lanes (h = lane half), as the operands of the four products that take them:
+// step e has columns 8 m + 2 e + h (see load_row_frag_global).  The products
+// are then added up in the order of every other kernel, so that the scores,
+// and with them the mask and the support at tau, are theirs bit for bit.
+__device__ __forceinline__ f32x4 step_operands(const f32x4& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[1]), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[2]), __float_as_uint(v[3]), false, false);
+  return f32x4{__uint_as_float(a[0]), __uint_as_float(b[0]), __uint_as_float(a[1]), __uint_as_float(b[1])};
+#else
+  return v;
+#endif
+}
+
 template <typename E, int D, int GK, int KT>
 __global__ __launch_bounds__(SM_NT, KT <= 4 ? 4 : 2) void solve_small_kernel(TauArgs a) {
   using M = Mma<E>;
@@ -70,8 +85,8 @@ __global__ __launch_bounds__(SM_NT, KT <= 4 ? 4 : 2) void solve_small_kernel(Tau
       }
     }
   } else {
-    // fp32: 16-byte loads; lane half h holds columns 8 m + 4 h + e, so that
-    // product e of step m takes columns 8 m + e and 8 m + 4 + e
+    // fp32: 16-byte loads, then four operands (Q's in the first tile, so that
+    // its keys are on the way meanwhile; a wave without that tile has no other)
     f32x4 qf[D / 8];
     const float* qr = reinterpret_cast<const float*>(Q) + (size_t)min(i, n - 1) * D + 4 * half;
 #pragma unroll
@@ -84,7 +99,8 @@ __global__ __launch_bounds__(SM_NT, KT <= 4 ? 4 : 2) void solve_small_kernel(Tau
         const float* kr = reinterpret_cast<const float*>(K) + (size_t)min(j0 + (lane & 31), n - 1) * D + 4 * half;
 #pragma unroll
         for (int m = 0; m < D / 8; ++m) {
-          const f32x4 kf = *reinterpret_cast<const f32x4*>(kr + 8 * m);
+          const f32x4 kf = step_operands(*reinterpret_cast<const f32x4*>(kr + 8 * m));
+          if (k == 0) qf[m] = step_operands(qf[m]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) s[k] = M::mma(kf[e], qf[m][e], s[k]);
         }

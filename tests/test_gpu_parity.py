@@ -319,3 +319,28 @@ def test_dense_partly_listed(n, d, causal, c):
     got = ea.backward_dense(q, k, v, do, tau, o2, alpha=1.5, causal=causal, tau_lo=lo)
     for x, y in zip(got, ref):
         assert (x - y).norm() <= 2 ** -8 * y.norm()
+
+
+@pytest.mark.parametrize("d,n", [(128, 128), (128, 100), (64, 70), (64, 512)])
+@pytest.mark.parametrize("alpha", [1.25, 1.5, 2.0])
+def test_short_fp32_scores_are_the_recomputed_ones(d, n, alpha):
+    """fp32 on the short-sequence solver: the probabilities that it lists and
+    those that the forward recomputes from tau come from the same scores, bit
+    for bit (at alpha = 2 u jumps from 0 to 1 at the support's edge, and one
+    stage may read the lists where another recomputes).  With V's first d rows
+    the unit matrix O is P itself, exactly."""
+    import paper_2502_12082_amd as ea
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q, k = (torch.randn(1, 8, n, d, generator=g, device="cuda") for _ in range(2))
+    v = torch.zeros_like(q)
+    m = min(n, d)
+    v[:, :, range(m), range(m)] = 1.0
+    shape, params = ea.make_shape(q), ea.make_params(alpha, head_dim=d)
+    res = ea.Residuals(shape, params, q.device)
+    assert res.lists is not None
+    p_listed, _ = ea.forward(q, k, v, alpha=alpha, res=res)
+    tau = res.tau.clone()
+    res.lists = None
+    p, _ = ea.forward(q, k, v, alpha=alpha, res=res)
+    assert torch.equal(tau, res.tau)
+    assert (p > 0).any() and torch.equal(p_listed, p)
