@@ -171,6 +171,17 @@ __global__ __launch_bounds__(SM_NT, KT <= 4 ? 4 : 2) void solve_small_kernel(Tau
           }
           if (f > 0.f) b += f / (g * fp);
         }
+      } else {
+        // f is not convex: one term of f at a time (solve_kernel's bound):
+        // with j scores at or above u_x, j (c u_x - tau)^gamma <= 1
+#pragma unroll 1
+        for (int x = 0; x < 16; ++x) {
+          const float ux = part[x >> 2][row][x & 3];
+          int j = 0;
+#pragma unroll
+          for (int y = 0; y < 16; ++y) j += u[y] >= ux ? 1 : 0;
+          if (ux > -INFINITY) b = fmaxf(b, fmaf(c, ux, -exp2f(-__log2f((float)j) / g)));
+        }
       }
       lo = fminf(b - 4e-6f * fmaxf(1.f, fabsf(b)), hi);
       tau = newton_bound ? fminf(b, hi) : 0.5f * (lo + hi);

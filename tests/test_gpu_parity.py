@@ -344,3 +344,25 @@ def test_short_fp32_scores_are_the_recomputed_ones(d, n, alpha):
     p, _ = ea.forward(q, k, v, alpha=alpha, res=res)
     assert torch.equal(tau, res.tau)
     assert (p > 0).any() and torch.equal(p_listed, p)
+
+
+@pytest.mark.parametrize("alpha", [2.5, 3.0])
+@pytest.mark.parametrize("n", [300, 1000])
+def test_short_sequence_bracket_above_two(alpha, n):
+    """alpha > 2 (f is not convex, and the iteration may halve the bracket at
+    every step): the short-sequence solver's bracket is as narrow as that of
+    the longer ones, which takes 8 equal scores into account.  With all keys
+    the same row, tau = x - n^(1 - alpha), the upper end, and the bracket is
+    8^(1 - alpha) wide at most: k updates after its midpoint leave at most
+    2^-(k+2) of it, and the rounding of x and tau."""
+    import paper_2502_12082_amd as ea
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q = torch.randn(1, 2, n, 64, generator=g, device="cuda").bfloat16()
+    k = torch.randn(1, 2, 1, 64, generator=g, device="cuda").bfloat16().expand(1, 2, n, 64).contiguous()
+    x = (alpha - 1) * 0.125 * (q.double() @ k[:, :, 0].double()[..., None])[..., 0]
+    tau = x.reshape(2, n) - float(n) ** (1 - alpha)
+    for it in (0, 4, 12):
+        _, res = ea.forward(q, k, k, alpha=alpha, max_iter=it, need_bwd=False)
+        err = (res.tau.double() - tau).abs().max().item()
+        log("alpha %g n %d, %d updates: dtau %.2e" % (alpha, n, it, err))
+        assert err <= 8.0 ** (1 - alpha) / 2 ** (it + 2) + 1e-6 * max(5.0, x.abs().max().item())
