@@ -634,6 +634,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   // in, and takes them last, at the bound of all the others: fewer of their
   // scores pass than at the bound of the first stream alone.
   const int first = W < nkb ? W : 0;
+  int seen = 0;  // key blocks searched for the lists
   auto nth = [&](int kb) { return kb >= first ? kb - first : kb - first + nkb; };  // its place in the stream
   stream_from(first, [&](int kb, const E* kt) {
     // once the lists have overflowed, the first stream's blocks need nothing
@@ -652,6 +653,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
         if (kb >= W && k[h][gq]) insert_max(v, gq);
       }
     if (!cache || fill_dead) return;
+    seen = nth(kb) + 1;
     // Every 4 blocks the running bound takes the one-term bound of the
     // current maxima, every 32 blocks the Newton-refined one (any valid
     // lower bound serves; the first stream already left a close one).  The
@@ -741,18 +743,24 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
 #pragma unroll
     for (int gq = 0; gq < G; ++gq) cmax[gq] = wave_max(cc[gq]);
   }
-  // First tau: the lower bound where f is convex, which is within a few
-  // percent of the bracket from the root, so that the steps from there
-  // converge in 3 evaluations instead of 5 or 6 (12 at alpha = 2, where the
-  // midpoint's steps come from the kinks right of the root); streamed
-  // evaluations at alpha >= 1.5 take the midpoint, since lists that do not
-  // fit mean a wide support, far from the bound of its largest scores
-  // (alpha 1.5, c = 1/4: 4.4 evaluations against 5).  The bound itself, not
-  // the bracket's end below it: where one key takes the whole row, z is
+  // First tau: on the lists, the lower bound where f is convex, which is
+  // within a few percent of the bracket from the root, so that the steps from
+  // there converge in 3 evaluations instead of 5 or 6 (12 at alpha = 2, where
+  // the midpoint's steps come from the kinks right of the root).  Streamed
+  // evaluations take the midpoint: lists that do not fit mean a wide support,
+  // far from the bound of its largest scores (alpha 1.5, c = 1/4: 4.4
+  // evaluations against 5); but below alpha = 1.5 also the bound, unless more
+  // than 7 in 8 of a row's quads so far hold a score above it (alpha
+  // 1.25, B1 H4 n8192 d128, bound against midpoint: c = 0.3 1003 against 729
+  // us, c = 0.8 879 against 871, c = 1.3 737 against 862).  The bound itself,
+  // not the bracket's end below it: where one key takes the whole row, z is
   // clamped to 1 there and f reads 0 all the way to the root.
 #pragma unroll
-  for (int gq = 0; gq < G; ++gq)
-    if (!newton_bound || !(cached || g > 2.f)) tau[gq] = 0.5f * (lo[gq] + hi[gq]);
+  for (int gq = 0; gq < G; ++gq) {
+    const int quads = cc[gq] + __shfl_xor(cc[gq], 32);  // of 16 a key block
+    const bool near = g > 2.f && seen > 0 && quads <= 14 * seen;
+    if (!newton_bound || !(cached || near)) tau[gq] = 0.5f * (lo[gq] + hi[gq]);
+  }
   int attempts = cache ? 1 : 0;  // cache fills tried (pass 0 is the first)
   // form of the lists: 0 quads, 1 compacted singles, 2 singles of a later fill
   int lists = 0;

@@ -184,3 +184,19 @@ def test_cache_wide_rows_among_narrow(alpha, wide):
     assert (o1.float() - o0.float()).abs().max().item() <= BF16_TOL
     assert torch.equal(r0.block_mask, r1.block_mask) or \
         (r0.block_mask != r1.block_mask).float().mean().item() < 1e-3
+
+
+@pytest.mark.parametrize("c,evals", [(0.273, 4), (2.0, 3.5)])
+def test_streamed_start(c, evals):
+    """alpha 1.25 where the lists do not fit: the first streamed evaluation
+    starts at the bracket's midpoint where nearly all keys are in the support
+    (c = 0.273: 4 evaluations, 5 from the bracket's lower end), and at the
+    lower end where fewer are (c = 2)."""
+    inp = synth.attention_inputs(4, 2, 1686, 64, c=c, dtype="bf16", seed=17)
+    (o0, r0), (o1, r1) = _both(inp, 1.25, False)
+    log("c %g: evaluations %.2f, K passes %.2f" % (c, r1.stats[1].float().mean().item(),
+                                                   r1.stats[0].float().mean().item()))
+    assert r1.stats[0].max().item() > 2  # streamed
+    assert r1.stats[1].float().mean().item() <= evals + 0.1
+    dt = ((r1.tau.double() - r0.tau.double()).abs() / r0.tau.double().abs().clamp(min=1.0)).max().item()
+    assert dt <= 1e-4
