@@ -623,9 +623,6 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
   // Query-block lists of the two key blocks (without tables, in the no-mask
   // mode, every valid query block), merged in ascending order.
   const bool dense = a.k_index == nullptr;
-  // The tables are read through the constant address space (scalar loads),
-  // so that reading them does not wait on the tile copies in flight.
-  typedef const __attribute__((address_space(4))) int32_t ci32;
   const ci32* kcount = (const ci32*)a.k_count;
   const ci32* kindex = (const ci32*)a.k_index;
   __shared__ uint16_t unlisted[2][LIST_MAX_SEQLEN / BLK];
@@ -1279,8 +1276,8 @@ __global__ __launch_bounds__(DQ_NT, 2) void dq_kernel(BwdArgs a) {
 
   // Without tables (the no-mask mode) every valid key block is visited.
   const bool dense = a.q_index == nullptr;
-  const int32_t* list = dense ? nullptr : a.q_index + ((size_t)bh * T + qb) * T;
-  const int cnt = dense ? (a.causal ? qb + 1 : T) : a.q_count[(size_t)bh * T + qb];
+  const ci32* list = (const ci32*)(dense ? nullptr : a.q_index + ((size_t)bh * T + qb) * T);
+  const int cnt = dense ? (a.causal ? qb + 1 : T) : ((const ci32*)a.q_count)[(size_t)bh * T + qb];
   auto kb_of = [&](int e) { return dense ? e : list[e]; };
 
   f32x16 dq[NTD];
@@ -1296,19 +1293,22 @@ __global__ __launch_bounds__(DQ_NT, 2) void dq_kernel(BwdArgs a) {
 
   DmaPlan<E, D, DQ_NT> dma;
   dma.init();
-  auto issue = [&](int e) {
-    const int kb = kb_of(e);
+  auto issue = [&](int kb, int e) {
     dma.issue(kbuf[e & 1], Kg, kb * BLK, n);
     dma.issue(vbuf[e & 1], Vg, kb * BLK, n);
   };
-  if (cnt > 0) issue(0);
+  // key block of this step, and of the next, read a step ahead
+  int kb = cnt > 0 ? kb_of(0) : 0, kb_next = cnt > 1 ? kb_of(1) : 0;
+  if (cnt > 0) issue(kb, 0);
   for (int e = 0; e < cnt; ++e) {
+    const int j0 = kb * BLK + 32 * kh;
+    kb = kb_next;
     dma_wait();
     __syncthreads();
-    if (e + 1 < cnt) issue(e + 1);
+    if (e + 1 < cnt) issue(kb, e + 1);
+    if (e + 2 < cnt) kb_next = kb_of(e + 2);
     const E* kt = kbuf[e & 1];
     const E* vt = vbuf[e & 1];
-    const int j0 = kb_of(e) * BLK + 32 * kh;
     const int kind = sub_kind(j0);
     if (kind == 0) continue;
     // S^T = K Q^T and dP^T = V dO^T for this wave's 32 keys x 32 queries

@@ -39,6 +39,11 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
+// Wave-uniform values that an earlier launch wrote (tables, flags), read
+// through the constant address space: scalar loads, which wait for no copy in
+// flight and need no proof that the kernel's own stores leave them alone.
+typedef const __attribute__((address_space(4))) int32_t ci32;
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 // Wave index within the workgroup, as a wave-uniform (scalar) value.
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }

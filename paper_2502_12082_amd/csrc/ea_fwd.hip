@@ -223,8 +223,8 @@ __global__ __launch_bounds__(FWD_NT, !TRAIN && D == 64 && sizeof(E) == 2 ? 4 : 2
 
   // Without tables (the no-mask mode) every valid key block is visited.
   const bool dense = a.q_index == nullptr;
-  const int32_t* list = dense ? nullptr : a.q_index + ((size_t)bh * T + qb) * T;
-  const int cnt = dense ? (a.causal ? qb + 1 : T) : a.q_count[(size_t)bh * T + qb];
+  const ci32* list = (const ci32*)(dense ? nullptr : a.q_index + ((size_t)bh * T + qb) * T);
+  const int cnt = dense ? (a.causal ? qb + 1 : T) : ((const ci32*)a.q_count)[(size_t)bh * T + qb];
   auto kb_of = [&](int e) { return dense ? e : list[e]; };
 
   f32x16 o[NTD], o2[NTD];
@@ -244,19 +244,22 @@ __global__ __launch_bounds__(FWD_NT, !TRAIN && D == 64 && sizeof(E) == 2 ? 4 : 2
 
   DmaPlan<E, D, FWD_NT> dma;
   dma.init();
-  auto issue = [&](int e) {
-    const int kb = kb_of(e);
+  auto issue = [&](int kb, int e) {
     dma.issue(kbuf[e & 1], K, kb * BLK, n);
     dma.issue(vbuf[e & 1], V, kb * BLK, n);
   };
-  if (cnt > 0) issue(0);
+  // key block of this step, and of the next, read a step ahead
+  int kb = cnt > 0 ? kb_of(0) : 0, kb_next = cnt > 1 ? kb_of(1) : 0;
+  if (cnt > 0) issue(kb, 0);
   for (int e = 0; e < cnt; ++e) {
+    const int j0 = kb * BLK + 32 * kh;
+    kb = kb_next;
     dma_wait();
     __syncthreads();
-    if (e + 1 < cnt) issue(e + 1);
+    if (e + 1 < cnt) issue(kb, e + 1);
+    if (e + 2 < cnt) kb_next = kb_of(e + 2);
     const E* kt = kbuf[e & 1];
     const E* vt = vbuf[e & 1];
-    const int j0 = kb_of(e) * BLK + 32 * kh;
     const int kind = sub_kind(j0);
     if (kind == 0) continue;
     // S^T = K Q^T for this wave's 32 keys x 32 queries
