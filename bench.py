@@ -279,11 +279,11 @@ def parse():
     return ap.parse_args()
 
 
-# ListBlock of csrc/ea_internal.h: bytes of a record, of its counts and of its
-# use; the least use at which a stage reads the lists instead of its blocks.
+# ListBlock of csrc/ea_internal.h: place of its counts and bytes of a record
+# (after the records: 4 bytes of use per block); the least use at which a stage
+# reads the lists instead of its blocks.
 LIST_COUNTS = 48 * 128 * 6
-LIST_USE = LIST_COUNTS + 128 + 64 * 4
-LIST_RECORD = LIST_USE + 4 + 31 * 4
+LIST_RECORD = LIST_COUNTS + 128 + 64 * 4
 LIST_LEVEL = {"fwd_sparse": 1, "bwd_dq": 2, "bwd_dkdv": 3}
 
 
@@ -312,8 +312,7 @@ class Runner:
         self.o = torch.empty_like(self.q)
         f32 = lambda: torch.empty(self.q.shape, dtype=torch.float32, device=self.q.device)
         self.dq, self.dk, self.dv = f32(), f32(), f32()
-        self.ws = torch.empty(self.res.sizes.ws_bwd // 4 + 4, dtype=torch.float32,
-                              device=self.q.device)
+        self.ws = ea.backward_workspace(self.res, self.q.device)
         self.ws_fwd = ea.forward_workspace(self.res, self.q.device)
         self.events = [[torch.cuda.Event(enable_timing=True) for _ in range(len(KERNELS) + 1)]
                        for _ in range(max(1, args.steps))]
@@ -335,7 +334,7 @@ class Runner:
             ea._check(ea.entmax_attn_bwd_stage(st, self.shape, self.params, q, k, v, do, self.rp,
                                                self.dq.data_ptr(), self.dk.data_ptr(),
                                                self.dv.data_ptr(), self.ws.data_ptr(),
-                                               self.ws.numel() * 4, s), "bwd stage")
+                                               self.ws.numel(), s), "bwd stage")
             if ev:
                 ev[3 + st].record()
 
@@ -420,8 +419,10 @@ class Runner:
         serve (LIST_LEVEL) and how many nonzero probabilities they hold."""
         if self.res.lists is None:
             return np.zeros(blocks, np.int32), np.zeros(blocks, np.int64)
-        rec = self.res.lists[:blocks * LIST_RECORD].view(blocks, LIST_RECORD)
-        use = rec[:, LIST_USE:LIST_USE + 4].cpu().numpy().copy().view(np.int32)[:, 0]
+        end = blocks * LIST_RECORD
+        rec = self.res.lists[:end].view(blocks, LIST_RECORD)
+        at = (end + 255) // 256 * 256
+        use = self.res.lists[at:at + 4 * blocks].cpu().numpy().view(np.int32)
         return use, rec[:, LIST_COUNTS:LIST_COUNTS + 128].cpu().numpy().astype(np.int64).sum(1)
 
     def _sampled_z(self, rows):

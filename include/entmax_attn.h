@@ -183,23 +183,27 @@ ea_status entmax_attn_bwd_stage(int stage, const ea_shape* shape, const ea_param
  * key blocks.  The results are those of entmax_attn_fwd / entmax_attn_bwd up
  * to rounding, and the residuals are the same (as in a skipped block, a key of
  * zero probability adds nothing, also where its K or V row is not finite; a
- * block of matrix products adds 0 times that row); `lists` is one more buffer that
- * the forward writes and the backward reads (and sorts into parts of its own,
- * the same ones on every call).  A backward may be given lists only with the
- * residuals of the forward that wrote them; if another forward has written
+ * block of matrix products adds 0 times that row); `lists` is one more buffer
+ * that the forward writes and the backward only reads (it sorts them into its
+ * workspace).  A backward may be given lists only with the residuals of the forward that wrote them; if another forward has written
  * new thresholds to those residuals since, its blocks are computed without
  * the lists.
  *   stage      as for the *_stage functions, or EA_ALL_STAGES
- *   lists      16-byte aligned, entmax_attn_lists_bytes bytes, or NULL: then
- *              the functions without lists
- *   workspace  as for those (a forward without one lists no block); NULL in a
- *              backward of all stages: as entmax_attn_bwd_noalloc
+ *   lists      16-byte aligned, entmax_attn_lists_bytes bytes (582 a row), or
+ *              NULL: then the functions without lists
+ *   workspace  of a forward as for those (without one only the solver for
+ *              short sequences lists blocks); of a backward at least
+ *              sizes.ws_bwd bytes, and the lists are used where it has
+ *              entmax_attn_bwd_lists_workspace bytes (up to 0.6 KB a row
+ *              more); NULL in a backward of all stages: as
+ *              entmax_attn_bwd_noalloc, without the lists
  * Sequences of more than 65536 keys have no lists: entmax_attn_lists_bytes
  * gives 0, and a call with lists returns EA_ERR_UNSUPPORTED.  A backward with
  * lists launches 4 kernels.
  */
 #define EA_ALL_STAGES (-1)
 ea_status entmax_attn_lists_bytes(const ea_shape* shape, const ea_params* params, size_t* bytes);
+ea_status entmax_attn_bwd_lists_workspace(const ea_shape* shape, const ea_params* params, size_t* bytes);
 ea_status entmax_attn_fwd_lists(int stage, const ea_shape* shape, const ea_params* params,
                                 const void* q, const void* k, const void* v, void* o,
                                 const ea_residuals* res, void* lists, size_t lists_bytes,
@@ -256,7 +260,9 @@ ea_status entmax_attn_bwd_dense(const ea_shape* shape, const ea_params* params, 
 /*
  * The no-mask mode with element lists (see entmax_attn_fwd_lists; lists may be
  * NULL).  Here `lists` is scratch of each call, not a residual: the backward
- * collects the lists again from the thresholds, in one more K pass and launch.
+ * collects the lists again from the thresholds, in one more K pass and launch,
+ * where its workspace has room to sort them.  Memory stays O(n) per head: 582
+ * bytes a row for the lists, and up to 0.6 KB a row to sort them.
  */
 ea_status entmax_attn_fwd_dense_lists(const ea_shape* shape, const ea_params* params, const void* q,
                                       const void* k, const void* v, void* o, float* tau,

@@ -36,7 +36,8 @@ SYMBOLS = ("entmax_attn_default_params", "entmax_attn_sizes", "entmax_attn_fwd",
            "entmax_attn_status_string", "entmax_attn_last_hip_error", "entmax_rows_fwd",
            "entmax_rows_bwd", "entmax_attn_fwd_dense", "entmax_attn_bwd_dense",
            "entmax_attn_bwd_noalloc", "entmax_attn_lists_bytes", "entmax_attn_fwd_lists",
-           "entmax_attn_bwd_lists", "entmax_attn_fwd_dense_lists", "entmax_attn_bwd_dense_lists")
+           "entmax_attn_bwd_lists", "entmax_attn_fwd_dense_lists", "entmax_attn_bwd_dense_lists",
+           "entmax_attn_bwd_lists_workspace")
 EA_ALL_STAGES = -1
 NOALLOC_MAX_ROWS = 1048576  # EA_NOALLOC_MAX_ROWS of include/entmax_attn.h
 
@@ -55,9 +56,9 @@ class Params(ctypes.Structure):
 
 class ResidualPtrs(ctypes.Structure):
     """The ABI's ea_residuals.  `lists` and `lists_bytes`, set by
-    Residuals.ptrs(), name the element lists that belong to them; the calls
-    below then pass those on."""
-    lists, lists_bytes, lists_shape = None, 0, None
+    Residuals.ptrs(), name the element lists that belong to them, and `owner`
+    the Residuals itself; the calls below then pass those on."""
+    lists, lists_bytes, lists_shape, owner = None, 0, None, None
     _fields_ = [(f, ctypes.c_void_p) for f in
                 ("tau", "o2", "block_mask", "q_count", "q_index", "k_count", "k_index", "stats",
                  "tau_lo")]
@@ -112,6 +113,8 @@ _lib.entmax_attn_bwd_dense_lists.argtypes = [_P(Shape), _P(Params), _v, _v, _v, 
 _lib.entmax_attn_bwd_dense_lists.restype = ctypes.c_int
 _lib.entmax_attn_lists_bytes.argtypes = [_P(Shape), _P(Params), _P(ctypes.c_size_t)]
 _lib.entmax_attn_lists_bytes.restype = ctypes.c_int
+_lib.entmax_attn_bwd_lists_workspace.argtypes = [_P(Shape), _P(Params), _P(ctypes.c_size_t)]
+_lib.entmax_attn_bwd_lists_workspace.restype = ctypes.c_int
 _lib.entmax_attn_fwd_lists.argtypes = [ctypes.c_int, _P(Shape), _P(Params), _v, _v, _v, _v,
                                        _P(ResidualPtrs), _v, ctypes.c_size_t, _v, ctypes.c_size_t,
                                        _v]
@@ -158,6 +161,13 @@ def entmax_attn_lists_bytes(shape: Shape, params: Params) -> int:
     n = ctypes.c_size_t()
     _check(_lib.entmax_attn_lists_bytes(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(n)),
            "entmax_attn_lists_bytes")
+    return n.value
+
+
+def entmax_attn_bwd_lists_workspace(shape: Shape, params: Params) -> int:
+    n = ctypes.c_size_t()
+    _check(_lib.entmax_attn_bwd_lists_workspace(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(n)),
+           "entmax_attn_bwd_lists_workspace")
     return n.value
 
 
@@ -211,10 +221,16 @@ def entmax_attn_bwd(shape, params, q, k, v, dout, res: ResidualPtrs, dq, dk, dv,
 
 
 def entmax_attn_bwd_noalloc(shape, params, q, k, v, dout, res: ResidualPtrs, dq, dk, dv, stream):
+    """As the C function.  The lists of a Residuals are sorted in a buffer that
+    it holds (Residuals.keep_workspace; the first call makes it unless the
+    stream is being captured, and without it the lists are not used)."""
     lists = _lists_of(res, shape, params)
-    if lists[0]:
-        return entmax_attn_bwd_lists(EA_ALL_STAGES, shape, params, q, k, v, dout, res, *lists, dq, dk,
-                                     dv, None, 0, stream)
+    rows = shape.batch * shape.heads * shape.seqlen
+    if lists[0] and res.owner is not None and rows <= NOALLOC_MAX_ROWS:
+        ws = res.owner.keep_workspace(make=not torch.cuda.is_current_stream_capturing())
+        if ws is not None and ws.numel() >= entmax_attn_bwd_lists_workspace(shape, params):
+            return entmax_attn_bwd_lists(EA_ALL_STAGES, shape, params, q, k, v, dout, res, *lists, dq,
+                                         dk, dv, ws.data_ptr(), ws.numel(), stream)
     return _lib.entmax_attn_bwd_noalloc(ctypes.byref(shape), ctypes.byref(params), q, k, v, dout,
                                         ctypes.byref(res), dq, dk, dv, stream)
 
@@ -304,7 +320,8 @@ LISTS_FROM, DENSE_LISTS_FROM = 256, 1024
 class Residuals:
     """Device buffers (torch tensors) that the forward fills and the backward
     reads, sized by entmax_attn_sizes: tau, o2, tau_lo (fp32 inputs: the low
-    part of tau), lists (the element lists, see entmax_attn_fwd_lists), and
+    part of tau), lists (the element lists, see entmax_attn_fwd_lists; 582 bytes
+    a row, which the backward reads), and
     block_mask, q_count, q_index, k_count, k_index and stats ([0]: K passes the
     solver streamed, [1]: its evaluations, per query block).
 
@@ -313,7 +330,7 @@ class Residuals:
     than the kernels of a short sequence on the GPU (a training step at B1 H2
     n128: 79 us of host time with them, most of them never looked at)."""
 
-    lists, _tables, _parts = None, None, {}  # objects that were saved with a tensor per table
+    lists, _tables, _parts, _kept = None, None, {}, None  # objects that were saved with a tensor per table
 
     def __init__(self, shape: Shape, params: Params, device, with_stats: bool = True):
         z = entmax_attn_sizes(shape, params)
@@ -365,7 +382,17 @@ class Residuals:
         if self.lists is not None:
             p.lists, p.lists_bytes = self.lists.data_ptr(), self.lists.numel()
             p.lists_shape = _dims(self.shape)
+            p.owner = self
         return p
+
+    def keep_workspace(self, make=True):
+        """The buffer that entmax_attn_bwd_noalloc sorts the lists in, held from
+        the first call on; None where there is none and `make` is false, or no
+        memory for it."""
+        if self._kept is None and make and self.lists is not None:
+            self._kept = _bytes_or_none(entmax_attn_bwd_lists_workspace(self.shape, self.params),
+                                        self.lists.device)
+        return self._kept
 
 
 def _stream_handle(device):
@@ -454,6 +481,24 @@ def _check_bytes(ws, name, need_bytes, device):
         raise ValueError("%s must be on %s" % (name, device))
 
 
+def _bytes_or_none(nbytes, device):
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
+def backward_workspace(res: Residuals, device):
+    """A device buffer for the workspace of backward: delta, and room to sort
+    the element lists where res has them (without that room, as in a buffer of
+    sizes.ws_bwd bytes, the backward does not use them)."""
+    if res.lists is not None:
+        ws = _bytes_or_none(entmax_attn_bwd_lists_workspace(res.shape, res.params), device)
+        if ws is not None:
+            return ws
+    return torch.empty(max(res.sizes.ws_bwd, 16), dtype=torch.uint8, device=device)
+
+
 def forward_workspace(res: Residuals, device):
     """A device buffer of sizes.ws_fwd bytes for the solver's candidate cache."""
     return torch.empty(max(res.sizes.ws_fwd, 16), dtype=torch.uint8, device=device)
@@ -492,7 +537,10 @@ def forward(q, k, v, alpha=1.5, scale=None, causal=False, need_bwd=True, max_ite
 
 
 def backward(q, k, v, dout, res: Residuals, dq=None, dk=None, dv=None, workspace=None):
-    """(dQ, dK, dV) in fp32 for the loss sum(dO * O) of the forward that filled res."""
+    """(dQ, dK, dV) in fp32 for the loss sum(dO * O) of the forward that filled res.
+
+    workspace: a device tensor of at least sizes.ws_bwd bytes; to keep one from
+    call to call, take it from backward_workspace."""
     shape = make_shape(q)
     dev = _check_qkv([("q", q), ("k", k), ("v", v), ("dout", dout)], shape)
     _check_residuals(res, shape, dev, True)
@@ -503,8 +551,7 @@ def backward(q, k, v, dout, res: Residuals, dq=None, dk=None, dv=None, workspace
     for name, t in (("dq", dq), ("dk", dk), ("dv", dv)):
         _need(t, name, q.shape, torch.float32, dev)
     if workspace is None:
-        workspace = torch.empty(max(res.sizes.ws_bwd, 16) // 4 + 4, dtype=torch.float32,
-                                device=q.device)
+        workspace = backward_workspace(res, q.device)
     else:
         _check_bytes(workspace, "workspace", res.sizes.ws_bwd, dev)
     _on_gpu(dev)
@@ -626,14 +673,15 @@ def backward_dense(q, k, v, dout, tau, o2, alpha=1.5, scale=None, causal=False, 
         _need(tau_lo, "tau_lo", (B * H, n), torch.float32, dev)
     _on_gpu(dev)
     params = make_params(alpha, scale, causal, True, None, None, head_dim=q.shape[-1])
-    z = entmax_attn_sizes(shape, params)
     mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
     dq, dk, dv = mk(), mk(), mk()
-    ws = torch.empty(max(z.ws_bwd, 16) // 4 + 4, dtype=torch.float32, device=q.device)
     _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device)
+    ws = _bytes_or_none(entmax_attn_bwd_lists_workspace(shape, params), q.device) if lists_ptr else None
+    if ws is None:
+        ws = torch.empty(max(entmax_attn_sizes(shape, params).ws_bwd, 16), dtype=torch.uint8, device=q.device)
     _check(_lib.entmax_attn_bwd_dense_lists(
         ctypes.byref(shape), ctypes.byref(params), q.data_ptr(), k.data_ptr(), v.data_ptr(),
         dout.data_ptr(), tau.data_ptr(), tau_lo.data_ptr() if q.dtype == torch.float32 else None,
         o2.data_ptr(), lists_ptr, lists_bytes, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
-        ws.data_ptr(), ws.numel() * 4, _stream_handle(q.device)), "entmax_attn_bwd_dense")
+        ws.data_ptr(), ws.numel(), _stream_handle(q.device)), "entmax_attn_bwd_dense")
     return dq, dk, dv

@@ -109,16 +109,28 @@ void fill_sizes(const Dims& d, ea_sizes* z) {
   z->tau_lo = d.dtype == EA_F32 ? (size_t)(d.BH * d.n) * 4 : 0;
 }
 
-// Element lists: one ListBlock per query block, written by the forward, then
-// the buckets that each backward sorts them into (always the same ones), each
-// part 256-byte aligned.  Fills *b (if given) from the buffer `lists`.
+// Element lists: one ListBlock per query block, then what each serves.
 size_t up256(size_t b) { return (b + 255) / 256 * 256; }
-size_t lists_layout(const Dims& d, char* lists, Buckets* b) {
+size_t lists_bytes_of(const Dims& d) {
   if (d.n > LIST_MAX_SEQLEN) return 0;
   const size_t blocks = (size_t)(d.BH * d.T);
-  size_t at = up256(blocks * sizeof(ListBlock));
+  return up256(blocks * sizeof(ListBlock)) + blocks * 4;
+}
+int32_t* lists_use(const Dims& d, void* lists) {
+  return lists ? reinterpret_cast<int32_t*>(static_cast<char*>(lists) +
+                                            up256((size_t)(d.BH * d.T) * sizeof(ListBlock)))
+               : nullptr;
+}
+
+// A backward's workspace with element lists: delta, then the buckets that it
+// sorts the lists into, each part 256-byte aligned.  Returns its size (that of
+// delta alone where there are no lists); fills *b, if given, from `ws`.
+size_t bwd_lists_ws(const Dims& d, char* ws, Buckets* b) {
+  if (d.n > LIST_MAX_SEQLEN) return bwd_ws_bytes(d);
+  const size_t blocks = (size_t)(d.BH * d.T);
+  size_t at = up256(bwd_ws_bytes(d));
   auto part = [&](size_t bytes) {
-    char* p = lists ? lists + at : nullptr;
+    char* p = ws ? ws + at : nullptr;
     at += up256(bytes);
     return p;
   };
@@ -273,13 +285,13 @@ ea_status run_fwd_stage(int stage, const Dims& d, const ea_params* params, const
                (int)d.BH, (int)d.n, (int)d.T, c, params->alpha, gamma, params->causal,
                params->max_iter, params->tol, gk,
                const_cast<float*>(tau_lo_of(res, d)), c64_of(params), g64_of(params),
-               res->q_count, res->q_index, lists};
+               res->q_count, res->q_index, lists, lists_use(d, lists)};
     return from_hip(launch_tau(ta, d.dtype, (int)d.d, s));
   }
   FwdArgs fa{q, k, v, o, params->need_bwd ? res->o2 : nullptr, res->tau, res->q_count,
              res->q_index, (int)d.BH, (int)d.n, (int)d.T, c, gamma, params->causal, gk,
              tau_lo_of(res, d), c64_of(params), g64_of(params),
-             res->block_mask, res->k_count, res->k_index, lists};
+             res->block_mask, res->k_count, res->k_index, lists, lists_use(d, lists)};
   return from_hip(launch_fwd(fa, d.dtype, (int)d.d, params->need_bwd != 0, s));
 }
 
@@ -311,12 +323,14 @@ ea_status run_bwd_stage(int stage, const Dims& d, const ea_params* params, const
                         const void* k, const void* v, const void* dout, const ea_residuals* res,
                         float* dq, float* dk, float* dv, void* workspace, void* lists_buf,
                         hipStream_t s) {
+  // (with lists, the workspace has room for their buckets)
   float* delta = static_cast<float*>(workspace);
   const ListBlock* lists = static_cast<const ListBlock*>(lists_buf);
   Buckets buckets{};
-  if (lists) lists_layout(d, static_cast<char*>(lists_buf), &buckets);
+  if (lists) bwd_lists_ws(d, static_cast<char*>(workspace), &buckets);
   if (stage == 0) {
-    DeltaArgs da{dout, res->o2, delta, d.BH * d.n, lists, res->tau, buckets, (int)d.BH, (int)d.n, (int)d.T};
+    DeltaArgs da{dout, res->o2, delta, d.BH * d.n, lists, lists_use(d, lists_buf), res->tau, buckets,
+                 (int)d.BH, (int)d.n, (int)d.T};
     return from_hip(launch_delta(da, d.dtype, (int)d.d, s));
   }
   const float c = (params->alpha - 1.0f) * params->scale;
@@ -391,7 +405,16 @@ ea_status entmax_attn_lists_bytes(const ea_shape* shape, const ea_params* params
   const ea_status st = check_shape(shape, params, &d);
   if (st != EA_OK) return st;
   if (!bytes) return EA_ERR_INVALID_ARG;
-  *bytes = lists_layout(d, nullptr, nullptr);
+  *bytes = lists_bytes_of(d);
+  return EA_OK;
+}
+
+ea_status entmax_attn_bwd_lists_workspace(const ea_shape* shape, const ea_params* params, size_t* bytes) {
+  Dims d;
+  const ea_status st = check_shape(shape, params, &d);
+  if (st != EA_OK) return st;
+  if (!bytes) return EA_ERR_INVALID_ARG;
+  *bytes = bwd_lists_ws(d, nullptr, nullptr);
   return EA_OK;
 }
 
@@ -400,7 +423,7 @@ namespace {
 // Checks of a lists buffer (null: no lists).
 ea_status check_lists(const Dims& d, const void* lists, size_t lists_bytes) {
   if (!lists) return EA_OK;
-  const size_t need = lists_layout(d, nullptr, nullptr);
+  const size_t need = lists_bytes_of(d);
   if (need == 0) return EA_ERR_UNSUPPORTED;
   if (!aligned(lists, 16)) return EA_ERR_INVALID_ARG;
   return lists_bytes < need ? EA_ERR_WORKSPACE : EA_OK;
@@ -446,7 +469,9 @@ ea_status entmax_attn_bwd_lists(int stage, const ea_shape* shape, const ea_param
     hipError_t e = hipSuccess;
     workspace = scratch_for(s, &e);
     if (!workspace) return from_hip(e);
+    ws_bytes = 0;
   }
+  if (ws_bytes < bwd_lists_ws(d, nullptr, nullptr)) lists = nullptr;  // no room to sort them
   for (int x = first_stage(stage); x <= last_stage(stage, 2); ++x)
     if ((st = run_bwd_stage(x, d, params, q, k, v, dout, res, dq, dk, dv, workspace, lists, s)) != EA_OK)
       return st;
@@ -543,6 +568,7 @@ ea_status entmax_attn_bwd_dense_lists(const ea_shape* shape, const ea_params* pa
   if (!workspace || !aligned(workspace, 16)) return EA_ERR_INVALID_ARG;
   if (ws_bytes < bwd_ws_bytes(d)) return EA_ERR_WORKSPACE;
   if ((st = check_lists(d, lists, lists_bytes)) != EA_OK) return st;
+  if (ws_bytes < bwd_lists_ws(d, nullptr, nullptr)) lists = nullptr;  // no room to sort them
   // no tables: the kernels visit every valid block that has no lists
   ea_residuals res{};
   res.tau = const_cast<float*>(tau);
@@ -550,8 +576,8 @@ ea_status entmax_attn_bwd_dense_lists(const ea_shape* shape, const ea_params* pa
   res.o2 = const_cast<float*>(o2);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (lists) {
-    CollectArgs ca{q, k, tau, tau_lo_of(&res, d), static_cast<ListBlock*>(lists), (int)d.BH, (int)d.n,
-                   (int)d.T, (params->alpha - 1.0f) * params->scale, params->causal,
+    CollectArgs ca{q, k, tau, tau_lo_of(&res, d), static_cast<ListBlock*>(lists), lists_use(d, lists),
+                   (int)d.BH, (int)d.n, (int)d.T, (params->alpha - 1.0f) * params->scale, params->causal,
                    gamma_kind(params->alpha), c64_of(params)};
     if ((st = from_hip(launch_collect(ca, d.dtype, (int)d.d, s))) != EA_OK) return st;
   }

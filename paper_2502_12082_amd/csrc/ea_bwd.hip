@@ -117,13 +117,14 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
   const int T = a.T;
   bool same = true;
   if (t < nr) same = __float_as_uint(lb.tau[t]) == __float_as_uint(a.tau[row0 + t]);
-  const bool used = __syncthreads_and(same && lb.used >= LIST_DQ);
+  const int use = a.use[blk];
+  const bool used = __syncthreads_and(same && use >= LIST_DQ);
   // The dK/dV work of a head is split only if most of its blocks are listed:
   // its other blocks cost a pass of their own over every key block.
   int listed = 0;
   for (int x0 = 0; x0 < T; x0 += PREP_NT)
-    listed += __syncthreads_count(x0 + t < T && a.lists[(size_t)bh * T + min(x0 + t, T - 1)].used == LIST_DKDV);
-  const bool sorted = used && lb.used == LIST_DKDV && 4 * listed >= 3 * T;
+    listed += __syncthreads_count(x0 + t < T && a.use[(size_t)bh * T + min(x0 + t, T - 1)] == LIST_DKDV);
+  const bool sorted = used && use == LIST_DKDV && 4 * listed >= 3 * T;
   if (t == 0) a.buckets.used[blk] = sorted ? LISTED | SORTED : used ? LISTED : 0;
   if (!sorted) return;
 
@@ -342,7 +343,7 @@ __global__ __launch_bounds__(COL_NT, sizeof(E) == 4 && D == 128 ? 1 : 3) void co
   if (lb && (w & 1) == 0 && lane == 0) {
     int blocks = 0;
     for (int x = 0; x < (T + 31) / 32; ++x) blocks += __popc(bits[qbl][x]);
-    lb->used = list_use(entries[qbl], blocks, T, sizeof(E) == 4);
+    a.use[(size_t)bh * T + qb] = list_use(entries[qbl], blocks, T, sizeof(E) == 4);
   }
 }
 

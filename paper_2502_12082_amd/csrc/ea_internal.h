@@ -45,12 +45,14 @@ constexpr size_t solve_slot_bytes(int cap) {
 static_assert(MAX_SEQLEN / 4 <= 65536, "a quad's key fits 16 bits");
 
 // Element lists: the nonzero probabilities of every row of a 64-row query
-// block, written by the masked path's solver where they are few, and read by
-// the forward and backward instead of recomputing the scores of whole blocks.
+// block, written by the solver (or, in the no-mask mode's backward, by
+// collect_kernel) where they are few, and read by the forward and backward
+// instead of recomputing the scores of whole blocks.
 // Each row has two lists of up to LIST_CAP entries (the keys that each half
 // of the solver's wave held for it): z = [x - tau]_+ and the 16-bit key, entry
 // e of list id = 64 * half + row at index LIST_IDS * e + id.  One record per
-// query block:
+// query block, sized for the most it can hold (the host cannot know the counts
+// without waiting for the solver): 37248 bytes, 582 a row.
 constexpr int LIST_CAP = 48;
 constexpr int LIST_IDS = 2 * 64;
 constexpr int LIST_ENTRIES = LIST_CAP * LIST_IDS;  // at most, per query block
@@ -60,8 +62,6 @@ struct ListBlock {
   uint16_t key[LIST_ENTRIES];
   uint8_t count[LIST_IDS];
   float tau[64];  // the thresholds the z belong to
-  int32_t used;   // ListUse: 0, or the lists hold every nonzero probability of the block
-  int32_t pad[31];
 };
 static_assert(sizeof(ListBlock) % 128 == 0, "records keep their alignment");
 // What a block's lists serve, by its entries per listed key block (64 x 64
@@ -74,6 +74,7 @@ static_assert(sizeof(ListBlock) % 128 == 0, "records keep their alignment");
 // against 124, dQ 41 against 127).  Among many key blocks a few entries are always
 // listed (the first rows of a causal head), since one block that is not makes
 // the whole head take both ways.
+// (An array of their own beside the records: kernels read one of many blocks.)
 enum ListUse { LIST_NONE = 0, LIST_FWD = 1, LIST_DQ = 2, LIST_DKDV = 3 };
 #if defined(__HIPCC__)
 __host__ __device__ inline int list_use(int entries, int blocks, int T, bool f32) {
@@ -108,7 +109,8 @@ struct TauArgs {
   // the row tables of the mask (Q_i of every query block), written with it
   int32_t* q_count;   // [BH, T]
   int32_t* q_index;   // [BH, T, T]
-  ListBlock* lists;   // [BH * T] (masked path, n <= LIST_MAX_SEQLEN), or null
+  ListBlock* lists;   // [BH * T] (n <= LIST_MAX_SEQLEN), or null
+  int32_t* use;       // [BH * T] ListUse: 0, or the lists hold every nonzero probability
 };
 
 struct FwdArgs {
@@ -132,11 +134,12 @@ struct FwdArgs {
   int32_t* k_count;     // [BH, T]
   int32_t* k_index;     // [BH, T, T]
   const ListBlock* lists;  // [BH * T], or null
+  const int32_t* use;      // as in TauArgs
 };
 
-// The element lists of a query block in the backward, sorted by key block:
-// entry p of bucket J at off[J] + p (off: [T + 1] per query block), with its
-// row and key within their blocks (row * 64 + key).
+// The element lists of a query block in the backward, sorted by key block
+// into the call's workspace: entry p of bucket J at off[J] + p (off: [T + 1]
+// per query block), with its row and key within their blocks (row * 64 + key).
 struct Buckets {
   int32_t* used;   // [BH * T]: whether the block's lists serve dQ, and its buckets dK and dV
   uint16_t* off;   // [BH * T, T + 1]
@@ -173,6 +176,7 @@ struct DeltaArgs {
   int64_t rows;
   // with element lists: their buckets are written too
   const ListBlock* lists;  // [BH * T], or null
+  const int32_t* use;      // as in TauArgs
   const float* tau;
   Buckets buckets;
   int BH, n, T;
@@ -185,6 +189,7 @@ struct CollectArgs {
   const float* tau;
   const float* tau_lo;  // as in BwdArgs
   ListBlock* lists;
+  int32_t* use;  // as in TauArgs
   int BH, n, T;
   float c;
   int causal, gk;

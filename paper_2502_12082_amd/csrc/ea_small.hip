@@ -371,7 +371,7 @@ __global__ __launch_bounds__(SM_NT, KT <= 4 ? 4 : 2) void solve_small_kernel(Tau
         if (half == 0 && row_ok) lb->tau[row] = tau;
       }
     }
-    if (t == 0) lb->used = fit ? use : LIST_NONE;
+    if (t == 0) a.use[(size_t)bh * T + qb] = fit ? use : LIST_NONE;
   }
   if (w != 0) return;
   // mask row and row table (at most 16 key blocks)

@@ -1239,7 +1239,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   }
   if (tables && lane == 0) a.q_count[(size_t)bh * T + qb] = listed;
   if (a.lists && lane == 0)
-    a.lists[(size_t)bh * T + qb].used = cached ? list_use(lsum[qbl], listed, T, sizeof(E) == 4) : LIST_NONE;
+    a.use[(size_t)bh * T + qb] = cached ? list_use(lsum[qbl], listed, T, sizeof(E) == 4) : LIST_NONE;
   if (a.stats && lane == 0) {
     a.stats[(size_t)bh * T + qb] = passes;
     a.stats[((size_t)a.BH + bh) * T + qb] = evals;

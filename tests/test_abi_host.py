@@ -277,3 +277,29 @@ def test_binding_refuses_mismatched_dense_and_rows():
         ea.rows_backward(s, torch.zeros(4), torch.zeros(4, 100, dtype=torch.float64))
     with pytest.raises(ValueError, match="GPU"):
         ea.rows_backward(s, torch.zeros(4), torch.zeros(4, 100))
+
+
+def test_lists_sizes_and_refusals():
+    """Element lists: 37248 bytes and 4 of use per 64-row block, and nothing of
+    the backward's; the sorted part is workspace of the call.  (Refused before
+    anything is launched.)"""
+    s, p = shape(), ea.default_params()  # 6 heads of 16 blocks
+    z = ea.entmax_attn_sizes(s, p)
+    lists = ea.entmax_attn_lists_bytes(s, p)
+    assert lists == 96 * 37248 + 96 * 4
+    ws = ea.entmax_attn_bwd_lists_workspace(s, p)
+    assert z.ws_bwd + 96 * (6144 * 6 + 17 * 2) < ws < z.ws_bwd + 96 * (6144 * 6 + 17 * 2 + 4) + 5 * 256
+    r = ea.ResidualPtrs(*[_fake() for _ in range(7)], None)
+    args = [_fake()] * 4
+    f = ea.entmax_attn_bwd_lists
+    assert f(-1, s, p, *args, r, _fake(), lists - 1, _fake(), _fake(), _fake(), _fake(), ws,
+             None) == ea.EA_ERR_WORKSPACE
+    assert f(-1, s, p, *args, r, _fake() + 4, lists, _fake(), _fake(), _fake(), _fake(), ws,
+             None) == ea.EA_ERR_INVALID_ARG
+    assert f(-1, s, p, *args, r, _fake(), lists, _fake(), _fake(), _fake(), _fake(), z.ws_bwd - 4,
+             None) == ea.EA_ERR_WORKSPACE
+    big = shape(1, 1, 65537)
+    assert ea.entmax_attn_lists_bytes(big, p) == 0
+    assert ea.entmax_attn_bwd_lists_workspace(big, p) == ea.entmax_attn_sizes(big, p).ws_bwd
+    assert f(-1, big, p, *args, r, _fake(), lists, _fake(), _fake(), _fake(), _fake(), 1 << 40,
+             None) == ea.EA_ERR_UNSUPPORTED

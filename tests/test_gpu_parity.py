@@ -366,3 +366,38 @@ def test_short_sequence_bracket_above_two(alpha, n):
         err = (res.tau.double() - tau).abs().max().item()
         log("alpha %g n %d, %d updates: dtau %.2e" % (alpha, n, it, err))
         assert err <= 8.0 ** (1 - alpha) / 2 ** (it + 2) + 1e-6 * max(5.0, x.abs().max().item())
+
+
+@pytest.mark.parametrize("dtype,n", [("bf16", 1500), ("f32", 300)])
+def test_backward_leaves_the_lists_alone(dtype, n):
+    """The backward only reads the residuals' element lists: they are the same
+    bytes afterwards, and two backwards of one forward, on two streams and of
+    different output gradients, are each what they are alone.  A workspace
+    without room to sort the lists gives the backward without them."""
+    import paper_2502_12082_amd as ea
+    inp = synth.attention_inputs(2, 3, n, 64, c=4.0, dtype=dtype, with_dout=True, seed=6)
+    q, k, v, do = (to_device(inp[x]) for x in ("q", "k", "v", "dout"))
+    do2 = (2.0 * do.flip(2)).contiguous()
+    _, res = ea.forward(q, k, v, alpha=1.5)
+    before = res.lists.clone()
+    ref, ref2 = ea.backward(q, k, v, do, res), ea.backward(q, k, v, do2, res)
+    torch.cuda.synchronize()
+    assert torch.equal(res.lists, before)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for _ in range(3):
+        got = []
+        for st, d in zip(streams, (do, do2)):
+            with torch.cuda.stream(st):
+                got.append(ea.backward(q, k, v, d, res))
+        torch.cuda.synchronize()
+        for a, b in zip(ref + ref2, got[0] + got[1]):
+            assert torch.equal(a, b)
+    small = torch.empty(res.sizes.ws_bwd, dtype=torch.uint8, device=q.device)
+    got = ea.backward(q, k, v, do, res, workspace=small)
+    lists, res.lists = res.lists, None
+    plain = ea.backward(q, k, v, do, res)
+    res.lists = lists
+    torch.cuda.synchronize()
+    assert not all(torch.equal(a, b) for a, b in zip(ref, plain))  # the lists were in use above
+    for a, b in zip(plain, got):
+        assert torch.equal(a, b)
