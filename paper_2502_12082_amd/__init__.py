@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libentmax_attn.so")
@@ -286,12 +287,13 @@ def make_params(alpha=1.5, scale=None, causal=False, need_bwd=True, max_iter=Non
 
 
 _memory = {}  # total memory of each device, a constant of the device
+_held = {}    # bytes of the element lists that live Residuals hold on each device
+_held_lock = threading.RLock()
 
 
 def _lists_limit(device) -> int:
-    """Largest element lists that Residuals allocates: a sixteenth of the
-    device's memory."""
-    device = torch.device(device)
+    """The most that the element lists of all Residuals of a device take
+    together: a sixteenth of its memory."""
     if device.type != "cuda":
         return 1 << 30
     if device.index not in _memory:
@@ -299,15 +301,46 @@ def _lists_limit(device) -> int:
     return _memory[device.index] // 16
 
 
-def _lists_size(shape, params, device, least) -> int:
-    """Bytes of the element lists to allocate, or 0: from `least` keys on (a
-    quarter of that for fp32, whose products take longer), since the sort and
-    the list kernel of the backward are launches of their own, and few blocks
-    of a short sequence are listed."""
+class _Claim:
+    """`nbytes` of a device's share for element lists, given back when this
+    object goes.  Saved and copied objects hold none."""
+
+    def __init__(self, index, nbytes):
+        self.index, self.nbytes = index, nbytes
+
+    def __del__(self):
+        with _held_lock:
+            _held[self.index] -= self.nbytes
+
+    def __reduce__(self):
+        return type(None), ()
+
+
+def _claim(device, nbytes):
+    """A _Claim, or None where the limit would be passed."""
+    limit = _lists_limit(device)
+    with _held_lock:
+        if _held.get(device.index, 0) + nbytes > limit:
+            return None
+        _held[device.index] = _held.get(device.index, 0) + nbytes
+    return _Claim(device.index, nbytes)
+
+
+def _lists_size(shape, params, least) -> int:
+    """Bytes of the element lists, or 0: from `least` keys on (a quarter of
+    that for fp32, whose products take longer), since the sort and the list
+    kernel of the backward are launches of their own, and few blocks of a short
+    sequence are listed."""
     if shape.seqlen <= (least if shape.dtype == EA_BF16 else least // 4):
         return 0
-    nbytes = entmax_attn_lists_bytes(shape, params)
-    return nbytes if nbytes <= _lists_limit(device) else 0
+    return entmax_attn_lists_bytes(shape, params)
+
+
+def _bytes_or_none(nbytes, device):
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
 
 
 # Measured, in us, with lists against without: B64 H16 n128 d64 alpha 1.5
@@ -321,7 +354,10 @@ class Residuals:
     """Device buffers (torch tensors) that the forward fills and the backward
     reads, sized by entmax_attn_sizes: tau, o2, tau_lo (fp32 inputs: the low
     part of tau), lists (the element lists, see entmax_attn_fwd_lists; 582 bytes
-    a row, which the backward reads), and
+    a row, which the backward reads; None with lists=False, where they would
+    pass a sixteenth of the device's memory together with those of every other
+    live Residuals, or where there is no memory for them: forward and backward
+    then run without them), and
     block_mask, q_count, q_index, k_count, k_index and stats ([0]: K passes the
     solver streamed, [1]: its evaluations, per query block).
 
@@ -332,7 +368,7 @@ class Residuals:
 
     lists, _tables, _parts, _kept = None, None, {}, None  # objects that were saved with a tensor per table
 
-    def __init__(self, shape: Shape, params: Params, device, with_stats: bool = True):
+    def __init__(self, shape: Shape, params: Params, device, with_stats: bool = True, lists: bool = True):
         z = entmax_attn_sizes(shape, params)
         BH, n, d = shape.batch * shape.heads, shape.seqlen, shape.head_dim
         T = (n + 63) // 64
@@ -342,8 +378,9 @@ class Residuals:
                    if params.need_bwd else None)
         self.tau_lo = (torch.empty((BH, n), dtype=torch.float32, device=device)
                        if z.tau_lo else None)
-        nbytes = _lists_size(shape, params, device, LISTS_FROM)
-        self.lists = torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
+        nbytes = _lists_size(shape, params, LISTS_FROM) if lists else 0
+        self._share = _claim(self.tau.device, nbytes) if nbytes else None
+        self.lists = _bytes_or_none(nbytes, device) if self._share else None
         at, parts = 0, {}
         for name, nbytes, dims in (
                 ("q_index", z.q_index, (BH, T, T)), ("k_index", z.k_index, (BH, T, T)),
@@ -481,13 +518,6 @@ def _check_bytes(ws, name, need_bytes, device):
         raise ValueError("%s must be on %s" % (name, device))
 
 
-def _bytes_or_none(nbytes, device):
-    try:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
-    except torch.OutOfMemoryError:
-        return None
-
-
 def backward_workspace(res: Residuals, device):
     """A device buffer for the workspace of backward: delta, and room to sort
     the element lists where res has them (without that room, as in a buffer of
@@ -505,16 +535,17 @@ def forward_workspace(res: Residuals, device):
 
 
 def forward(q, k, v, alpha=1.5, scale=None, causal=False, need_bwd=True, max_iter=None,
-            tol=None, out=None, res: Residuals | None = None, workspace=None):
+            tol=None, out=None, res: Residuals | None = None, workspace=None, lists=True):
     """O and the residuals for Q, K, V ([B, H, n, d] bf16/fp32 CUDA tensors).
 
     workspace: a uint8 device tensor for the solver's candidate cache (None
-    allocates sizes.ws_fwd bytes; False runs the solver without the cache)."""
+    allocates sizes.ws_fwd bytes; False runs the solver without the cache).
+    lists: whether new residuals hold element lists (see Residuals)."""
     shape = make_shape(q)
     dev = _check_qkv([("q", q), ("k", k), ("v", v)], shape)
     params = make_params(alpha, scale, causal, need_bwd, max_iter, tol, head_dim=q.shape[-1])
     if res is None:
-        res = Residuals(shape, params, q.device)
+        res = Residuals(shape, params, q.device, lists=lists)
     else:
         _check_residuals(res, shape, dev, bool(need_bwd))
     if out is None:
@@ -619,20 +650,19 @@ def rows_backward(s, tau, dp, alpha=1.5, scale=1.0):
 
 # ---------------------------------------------------------- no-mask mode
 
-def _scratch_lists(shape, params, device):
+def _scratch_lists(shape, params, device, lists):
     """Element lists for one call of the no-mask mode: (tensor or None, pointer, bytes)."""
-    nbytes = _lists_size(shape, params, device, DENSE_LISTS_FROM)
-    if not nbytes:
-        return None, None, 0
-    t = torch.empty(nbytes, dtype=torch.uint8, device=device)
-    return t, t.data_ptr(), nbytes
+    nbytes = _lists_size(shape, params, DENSE_LISTS_FROM) if lists else 0
+    t = _bytes_or_none(nbytes, device) if 0 < nbytes <= _lists_limit(device) else None
+    return (None, None, 0) if t is None else (t, t.data_ptr(), nbytes)
 
 
 def forward_dense(q, k, v, alpha=1.5, scale=None, causal=False, need_bwd=True, max_iter=None,
-                  tol=None, workspace=None):
+                  tol=None, workspace=None, lists=True):
     """(O, tau, O2 or None, tau_lo or None) without block mask or tables
     (Algorithm 2 as written); tau_lo, the threshold's low part, exists for fp32
-    inputs and goes back into backward_dense."""
+    inputs and goes back into backward_dense.  lists: whether the call may take
+    scratch for element lists (582 bytes a row; backward_dense 1.2 KB)."""
     shape = make_shape(q)
     dev = _check_qkv([("q", q), ("k", k), ("v", v)], shape)
     _on_gpu(dev)
@@ -650,7 +680,7 @@ def forward_dense(q, k, v, alpha=1.5, scale=None, causal=False, need_bwd=True, m
     _on_gpu(dev)
     ws_ptr, ws_bytes = (None, 0) if workspace is False else (workspace.data_ptr(),
                                                             workspace.numel() * workspace.element_size())
-    _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device)
+    _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device, lists)
     _check(_lib.entmax_attn_fwd_dense_lists(
         ctypes.byref(shape), ctypes.byref(params), q.data_ptr(), k.data_ptr(), v.data_ptr(),
         o.data_ptr(), tau.data_ptr(), tau_lo.data_ptr() if tau_lo is not None else None,
@@ -659,9 +689,10 @@ def forward_dense(q, k, v, alpha=1.5, scale=None, causal=False, need_bwd=True, m
     return o, tau, o2, tau_lo
 
 
-def backward_dense(q, k, v, dout, tau, o2, alpha=1.5, scale=None, causal=False, tau_lo=None):
+def backward_dense(q, k, v, dout, tau, o2, alpha=1.5, scale=None, causal=False, tau_lo=None,
+                   lists=True):
     """(dQ, dK, dV) in fp32 for the no-mask forward that produced tau, o2 and
-    (fp32 inputs) tau_lo."""
+    (fp32 inputs) tau_lo.  lists: as for forward_dense."""
     shape = make_shape(q)
     dev = _check_qkv([("q", q), ("k", k), ("v", v), ("dout", dout)], shape)
     B, H, n, d = q.shape
@@ -675,7 +706,7 @@ def backward_dense(q, k, v, dout, tau, o2, alpha=1.5, scale=None, causal=False, 
     params = make_params(alpha, scale, causal, True, None, None, head_dim=q.shape[-1])
     mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
     dq, dk, dv = mk(), mk(), mk()
-    _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device)
+    _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device, lists)
     ws = _bytes_or_none(entmax_attn_bwd_lists_workspace(shape, params), q.device) if lists_ptr else None
     if ws is None:
         ws = torch.empty(max(entmax_attn_sizes(shape, params).ws_bwd, 16), dtype=torch.uint8, device=q.device)

@@ -303,3 +303,38 @@ def test_lists_sizes_and_refusals():
     assert ea.entmax_attn_bwd_lists_workspace(big, p) == ea.entmax_attn_sizes(big, p).ws_bwd
     assert f(-1, big, p, *args, r, _fake(), lists, _fake(), _fake(), _fake(), _fake(), 1 << 40,
              None) == ea.EA_ERR_UNSUPPORTED
+
+
+def test_lists_take_a_bounded_share(monkeypatch):
+    """The element lists of all live Residuals stay within the device's share,
+    given back when they go; none where they would pass it, where there is no
+    memory for them, or where they are not wanted.  Copies hold
+    no share of their own."""
+    import copy
+    s = ea.make_shape(_bf(1, 2, 512, 64))
+    p = ea.make_params(head_dim=64)
+    nbytes = ea.entmax_attn_lists_bytes(s, p)
+    dev = torch.device("cpu")
+    held = ea._held.get(None, 0)
+    monkeypatch.setattr(ea, "_lists_limit", lambda device: held + 2 * nbytes + 1)
+    a, b = ea.Residuals(s, p, dev), ea.Residuals(s, p, dev)
+    assert a.lists.numel() == b.lists.numel() == nbytes
+    assert ea.Residuals(s, p, dev).lists is None        # the share is taken
+    assert ea.Residuals(s, p, dev, lists=False).lists is None
+    c = copy.deepcopy(a)
+    assert c.lists.numel() == nbytes and c._share is None and ea._held[None] == held + 2 * nbytes
+    del b
+    assert ea._held[None] == held + nbytes
+    assert ea.Residuals(s, p, dev).lists is not None    # given back
+    empty = torch.empty
+
+    def no_memory(*args, **kw):
+        if args and args[0] == nbytes:
+            raise torch.OutOfMemoryError("no memory")
+        return empty(*args, **kw)
+    monkeypatch.setattr(torch, "empty", no_memory)
+    d = ea.Residuals(s, p, dev)
+    assert d.lists is None and d.tau.shape == (2, 512)
+    assert ea._scratch_lists(ea.make_shape(_bf(1, 1, 2048, 64)), p, dev, False) == (None, None, 0)
+    del a, c, d
+    assert ea._held[None] == held
