@@ -537,11 +537,11 @@ struct RowGroup {
 // count but the multiples of 8 had all XCDs read every head: at B2 H2 n11378
 // d128 alpha 1.25 dQ took 613 us against 584, the forward 678 against 663.)
 __device__ __forceinline__ void head_major(int b, int BH, int T, int& bh, int& blk, int group = 1) {
-  const int x = min(BH & -BH, 8), heads = BH / x, s = b / x;
+  const int lg = min(__ffs(BH) - 1, 3), x = 1 << lg, heads = BH >> lg, s = b >> lg;
   const int h0 = s / (T * group) * group, r = s - h0 * T;
   const int g = min(group, heads - h0);
   blk = r / g;
-  bh = b % x + x * (h0 + r % g);
+  bh = (b & (x - 1)) + ((h0 + r % g) << lg);
 }
 
 // Heads of a group where blocks come longest first (causal): as many as have
