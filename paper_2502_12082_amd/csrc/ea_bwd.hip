@@ -1244,7 +1244,7 @@ __global__ __launch_bounds__(DQ_NT, 2) void dq_kernel(BwdArgs a) {
   const int n = a.n, T = a.T;
   int bh = blockIdx.x % a.BH;
   int qb = blockIdx.x / a.BH;
-  if (a.lists) head_major(blockIdx.x, a.BH, T, bh, qb, head_group<E, D>(a.causal, n));
+  if (a.lists) head_major(blockIdx.x, a.BH, T, bh, qb, head_group<E, D>(n));
   if (a.causal) qb = T - 1 - qb;  // longest lists first
   if (a.lists && (a.buckets.used[(size_t)bh * T + qb] & LISTED)) {
     gather_dq<E, D, GK>(a, a.lists[(size_t)bh * T + qb], bh, qb);
