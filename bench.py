@@ -280,11 +280,11 @@ def parse():
 
 
 # ListBlock of csrc/ea_internal.h: place of its counts and bytes of a record
-# (after the records: 4 bytes of use per block); the least use at which a stage
-# reads the lists instead of its blocks.
+# (after the records: 4 bytes of use per block); the bit of use that has a stage
+# read the lists instead of its blocks.
 LIST_COUNTS = 48 * 128 * 6
 LIST_RECORD = LIST_COUNTS + 128 + 64 * 4
-LIST_LEVEL = {"fwd_sparse": 1, "bwd_dq": 2, "bwd_dkdv": 3}
+LIST_USE = {"fwd_sparse": 1, "bwd_dq": 2, "bwd_dkdv": 4}
 
 
 class Runner:
@@ -404,7 +404,7 @@ class Runner:
             if k_ == "fwd_sparse" and not self.bwd:
                 m = 2
             # a listed entry takes the same products without S, 2 d each
-            listed = use >= LIST_LEVEL[k_]
+            listed = (use & LIST_USE[k_]) != 0
             flops[k_] = (m * float(counts[~listed].sum()) * f_blk
                          + (m - 1) * float(entries[listed].sum()) * 2.0 * d)
         dense = 14.0 * n * n * d * BH * (0.5 if self.params.causal else 1.0)
@@ -416,7 +416,7 @@ class Runner:
 
     def listed(self, blocks):
         """(use, entries) of each 64-row query block's element lists: what they
-        serve (LIST_LEVEL) and how many nonzero probabilities they hold."""
+        serve (LIST_USE) and how many nonzero probabilities they hold."""
         if self.res.lists is None:
             return np.zeros(blocks, np.int32), np.zeros(blocks, np.int64)
         end = blocks * LIST_RECORD

@@ -136,6 +136,7 @@ size_t bwd_lists_ws(const Dims& d, char* ws, Buckets* b) {
   };
   Buckets t;
   t.used = reinterpret_cast<int32_t*>(part(blocks * 4));
+  t.heads = reinterpret_cast<int32_t*>(part((size_t)d.BH * 4));
   t.off = reinterpret_cast<uint16_t*>(part(blocks * (size_t)(d.T + 1) * 2));
   t.z = reinterpret_cast<float*>(part(blocks * LIST_ENTRIES * 4));
   t.code = reinterpret_cast<uint16_t*>(part(blocks * LIST_ENTRIES * 2));

@@ -75,6 +75,8 @@ __device__ __forceinline__ int lanes_below(unsigned long long m) {
 constexpr int PREP_NT = 256;
 constexpr int PREP_T = LIST_MAX_SEQLEN / BLK;  // most key blocks
 constexpr int PREP_STAGE = 3072;               // entries that fit the staging memory
+constexpr int PREP_SMALL = 2048;               // blocks of a small grid
+static_assert(PREP_SMALL <= (PREP_NT / 64) * PREP_T && PREP_SMALL >= PREP_T, "a counter per head, and a head's blocks");
 // Buckets::used: the block's lists are good (for dQ), and sorted (for dK, dV)
 constexpr int LISTED = 1, SORTED = 2;
 
@@ -99,6 +101,15 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
   const size_t blk = blockIdx.x;
   const int nr = min(BLK, a.n - qb * BLK);
   const long long row0 = (long long)bh * a.n + (long long)qb * BLK;
+  // uses of the head's blocks, or of every head's in a small grid (see below)
+  const bool small = a.BH * a.T <= PREP_SMALL;
+  const int h0 = small ? 0 : bh, heads = small ? a.BH : 1;
+  int all_use[PREP_SMALL / PREP_NT];
+#pragma unroll
+  for (int k = 0; k < PREP_SMALL / PREP_NT; ++k) {
+    const int x = t + k * PREP_NT;
+    all_use[k] = x < heads * a.T ? a.use[(size_t)h0 * a.T + x] : 0;
+  }
 #pragma unroll
   for (int r = t >> 4; r < BLK; r += PREP_NT / 16) {
     float acc = 0.f;
@@ -117,15 +128,32 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
   const int T = a.T;
   bool same = true;
   if (t < nr) same = __float_as_uint(lb.tau[t]) == __float_as_uint(a.tau[row0 + t]);
-  const int use = a.use[blk];
-  const bool used = __syncthreads_and(same && use >= LIST_DQ);
-  // The dK/dV work of a head is split only if most of its blocks are listed:
-  // its other blocks cost a pass of their own over every key block.
-  int listed = 0;
-  for (int x0 = 0; x0 < T; x0 += PREP_NT)
-    listed += __syncthreads_count(x0 + t < T && a.use[(size_t)bh * T + min(x0 + t, T - 1)] == LIST_DKDV);
-  const bool sorted = used && use == LIST_DKDV && 4 * listed >= 3 * T;
-  if (t == 0) a.buckets.used[blk] = sorted ? LISTED | SORTED : used ? LISTED : 0;
+  const int use = __syncthreads_and(same) ? a.use[blk] : LIST_NONE;
+  // The dK/dV work of a head is split only if at least 7 of 8 of its blocks
+  // are listed: the others cost a pass of their own over every key block.  A
+  // small grid takes as long as its longest workgroup, so there every head has
+  // to be so.  (dK/dV and sort, with against without lists, in us: B1 H4
+  // n11392 d128 causal, 537 of 712 blocks listed 689 against 459, 618 of them
+  // 303 against 470; B8 H8 n3000 d64 causal, 2192 of 3008 329 against 234;
+  // B4 H12 n4096 d64 causal, 2478 of 3072 319 against 306.)
+  bool split = true;
+  if (use & LIST_DKDV || qb == 0) {
+    uint32_t* const rest = &cursor[0][0];  // unlisted blocks of each head
+    for (int h = t; h < heads; h += PREP_NT) rest[h] = 0;
+    __syncthreads();
+    const float per_head = 1.f / (float)T;
+#pragma unroll
+    for (int k = 0; k < PREP_SMALL / PREP_NT; ++k) {
+      const int x = t + k * PREP_NT;  // (its head exactly: x < 2^11)
+      if (x < heads * T && !(all_use[k] & LIST_DKDV)) atomicAdd(&rest[(int)(((float)x + 0.5f) * per_head)], 1u);
+    }
+    __syncthreads();
+    for (int h = t; h < heads; h += PREP_NT) split &= 8 * (int)rest[h] <= T;
+    split = __syncthreads_and(split);
+    if (qb == 0 && t == 0) a.buckets.heads[bh] = split;
+  }
+  const bool sorted = (use & LIST_DKDV) && split;
+  if (t == 0) a.buckets.used[blk] = (use & LIST_DQ ? LISTED : 0) | (sorted ? SORTED : 0);
   if (!sorted) return;
 
   const int bits = 32 - __clz(max(T - 1, 1));
@@ -349,10 +377,12 @@ __global__ __launch_bounds__(COL_NT, sizeof(E) == 4 && D == 128 ? 1 : 3) void co
 
 // ------------------------------------------------------------------ dK dV
 
-// The number of a head's T query blocks that are sorted for the list kernel.
-// Every thread of the workgroup.
+// The number of the T query blocks of head bh that are sorted for the list
+// kernel.  Every thread of the workgroup.
 template <int NT>
-__device__ __forceinline__ int sorted_blocks(const int32_t* used, int T) {
+__device__ __forceinline__ int sorted_blocks(const Buckets& b, int bh, int T) {
+  if (((const ci32*)b.heads)[bh] == 0) return 0;
+  const int32_t* used = b.used + (size_t)bh * T;
   int sorted = 0;
   for (int x0 = 0; x0 < T; x0 += NT) {
     const int x = x0 + (int)threadIdx.x;
@@ -425,7 +455,7 @@ __global__ __launch_bounds__(BWD_NT) void dkdv_kernel(BwdArgs a) {
   const int32_t* list = dense ? nullptr : a.k_index + ((size_t)bh * T + kb) * T;
   int cnt = dense ? (a.causal ? T - kb : T) : a.k_count[(size_t)bh * T + kb];
   __shared__ uint16_t unlisted[LIST_MAX_SEQLEN / BLK];
-  const int sorted = a.lists ? sorted_blocks<BWD_NT>(a.buckets.used + (size_t)bh * T, T) : 0;
+  const int sorted = a.lists ? sorted_blocks<BWD_NT>(a.buckets, bh, T) : 0;
   if (a.lists && sorted == T) return;
   const bool some = sorted > 0;
   if (some) {
@@ -627,7 +657,7 @@ __global__ __launch_bounds__(BWD2_NT, 2) void dkdv2_kernel(BwdArgs a) {
   const ci32* kcount = (const ci32*)a.k_count;
   const ci32* kindex = (const ci32*)a.k_index;
   __shared__ uint16_t unlisted[2][LIST_MAX_SEQLEN / BLK];
-  const int sorted = a.lists ? sorted_blocks<BWD2_NT>(a.buckets.used + (size_t)bh * T, T) : 0;
+  const int sorted = a.lists ? sorted_blocks<BWD2_NT>(a.buckets, bh, T) : 0;
   if (a.lists && sorted == T) return;
   const bool some = sorted > 0;
   auto count_of = [&](int kb) {
@@ -900,7 +930,7 @@ __global__ __launch_bounds__(LK_NT, 2) void dkdv_lists_kernel(BwdArgs a) {
   auto qb_of = [&](int e) { return dense ? (a.causal ? kb + e : e) : list[e]; };
   const int32_t* used = a.buckets.used + (size_t)bh * T;
 
-  const int sorted = sorted_blocks<LK_NT>(used, T);
+  const int sorted = sorted_blocks<LK_NT>(a.buckets, bh, T);
   if (sorted == 0) return;
   // whether the other dK/dV kernel wrote this key block (some query block of
   // its list is not sorted): the first round then adds to it as the later

@@ -66,22 +66,30 @@ struct ListBlock {
 static_assert(sizeof(ListBlock) % 128 == 0, "records keep their alignment");
 // What a block's lists serve, by its entries per listed key block (64 x 64
 // scores): beyond these limits the matrix products of whole blocks are faster
-// than a gather per entry (bf16, us at B8 H12 n1024 d64 c = 1, 76 entries per
-// block: forward 33 against 67, dQ 43 against 58, dK/dV with the sort 101
-// against 97; at 512 per block, B64 H16 n128: 34 against 33, 42 against 28, 103
-// against 42).  fp32 products take 16 times as long, but a listed entry twice
-// the bytes: four times the limits (B8 H16 n512 d64, 136 per block: forward 31
-// against 124, dQ 41 against 127).  Among many key blocks a few entries are always
-// listed (the first rows of a causal head), since one block that is not makes
-// the whole head take both ways.
+// than a gather per entry and the solver's stores of them (bf16 d64, us, with
+// the lists against without: B8 H12 n1024 at 76 entries per block solver and
+// forward 155 against 182, dQ 47 against 59; at 97 197 against 210 and 58
+// against 59; at 55 dK/dV with the sort 95 against 108; B8 H4 n1169 at 107
+// solver and forward 169 against 166.  B64 H16 n128, at 512: 34 against 33, 42
+// against 28, 103 against 42).  fp32 products take 16
+// times as long, but a listed entry twice the bytes: four times the limits (B8
+// H16 n512 d64, 136 per block: forward 31 against 124, dQ 41 against 127).
+// Among many key blocks a few entries are always listed for dK/dV (the first
+// rows of a causal head), since one block that is not makes the whole head
+// take both ways; the forward and dQ of such a block are a step or two of
+// products (B1 H16 n4096 d128 causal alpha 1.25, whose first blocks hold up to
+// 1000 entries a key block: dQ 131 us without lists, 141 with).
 // (An array of their own beside the records: kernels read one of many blocks.)
-enum ListUse { LIST_NONE = 0, LIST_FWD = 1, LIST_DQ = 2, LIST_DKDV = 3 };
+enum ListUse { LIST_NONE = 0, LIST_FWD = 1, LIST_DQ = 2, LIST_DKDV = 4 };  // bits
+constexpr int LIST_MOST = 100;  // entries per key block, for any use
 #if defined(__HIPCC__)
+__host__ __device__ inline int list_few(int T) { return 32 * T < 1024 ? 32 * T : 1024; }
 __host__ __device__ inline int list_use(int entries, int blocks, int T, bool f32) {
-  const int per = f32 ? 4 * blocks : blocks, few = 32 * T < 1024 ? 32 * T : 1024;
+  const int per = f32 ? 4 * blocks : blocks;
   if (entries > LIST_ENTRIES) return LIST_NONE;
-  if (entries <= few || entries <= 64 * per) return LIST_DKDV;
-  return entries <= 100 * per ? LIST_DQ : entries <= 150 * per ? LIST_FWD : LIST_NONE;
+  if (entries <= 64 * per) return LIST_FWD | LIST_DQ | LIST_DKDV;
+  const int few = entries <= list_few(T) ? LIST_DKDV : LIST_NONE;
+  return entries <= LIST_MOST * per ? few | LIST_FWD | LIST_DQ : few;
 }
 #endif
 
@@ -142,6 +150,7 @@ struct FwdArgs {
 // per query block), with its row and key within their blocks (row * 64 + key).
 struct Buckets {
   int32_t* used;   // [BH * T]: whether the block's lists serve dQ, and its buckets dK and dV
+  int32_t* heads;  // [BH]: whether any block of the head has buckets
   uint16_t* off;   // [BH * T, T + 1]
   float* z;        // [BH * T, LIST_ENTRIES]
   uint16_t* code;  // [BH * T, LIST_ENTRIES]

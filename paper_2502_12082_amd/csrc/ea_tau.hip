@@ -769,6 +769,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
 #pragma unroll
   for (int gq = 0; gq < G; ++gq) f_prev[gq] = INFINITY;
 
+  int last_mc[G] = {};  // support counted by the last evaluation
   for (int it = 0;; ++it) {
     // ---- evaluation at tau (per group): m0 = sum z^gamma, m1 = sum
     // z^(gamma-1), m2 = sum z^(gamma-2) over the strict support z > 0, mc =
@@ -971,6 +972,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     float f[G], f1[G], f2[G];
 #pragma unroll
     for (int gq = 0; gq < G; ++gq) {
+      last_mc[gq] = mc[gq];
       if constexpr (GK == 1) m1[gq] = (float)mc[gq];
       if constexpr (GK == 2) m2[gq] = (float)mc[gq];
       m0[gq] = sum_halves(m0[gq]);
@@ -1029,14 +1031,26 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   // An entry of row group gq with z = [x - tau]_+ at the returned tau: sets
   // its key block's mask bit and, where element lists are wanted, appends it
   // to this lane's list of the row (LIST_CAP entries; lc counts on).
-  __shared__ int lsum[SV_WAVES];
-  if (lane == 0 && writer) lsum[qbl] = 0;
+  __shared__ int lsum[SV_WAVES], ssum[SV_WAVES];
+  if (lane == 0 && writer) lsum[qbl] = ssum[qbl] = 0;
   __syncthreads();
+  int support = 0;  // of the block's rows, at the last evaluation
+#pragma unroll
+  for (int gq = 0; gq < G; ++gq) support += last_mc[gq];
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) support += __shfl_xor(support, o);
+  if (lane == 0) atomicAdd(&ssum[qbl], support);
+  __syncthreads();
+  support = ssum[qbl];
   // (not tried where many rows hold half as many candidates again as a list
   // takes; a few such rows may still fit, and one block that is not listed
-  // among many that are keeps the launches of the later kernels waiting for it)
+  // among many that are keeps the launches of the later kernels waiting for it;
+  // nor where the support is more than any use takes: B8 H12 n1024 d64 c = 0.5,
+  // 460 against 408 us)
+  const int most = LIST_MOST * 33 / 32 * (sizeof(E) == 4 ? 4 : 1) * (a.causal ? qb + 1 : T);
   const bool listable =
-      cached && __popcll(__ballot(any_over(lists == 1 ? ns : cc, LIST_CAP * 3 / 2))) <= 8;
+      cached && __popcll(__ballot(any_over(lists == 1 ? ns : cc, LIST_CAP * 3 / 2))) <= 8 &&
+      (support <= list_few(T) || support <= most);
   ListBlock* const lb = a.lists && listable && qb < T ? a.lists + ((size_t)bh * T + qb) : nullptr;
   int lc[G] = {};
   auto list_id = [&](int gq) { return 64 * (lane >> 5) + (q0 - qb * BLK) + 32 * gq + (lane & 31); };
