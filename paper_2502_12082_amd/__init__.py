@@ -650,6 +650,18 @@ def rows_backward(s, tau, dp, alpha=1.5, scale=1.0):
 
 # ---------------------------------------------------------- no-mask mode
 
+def _dense_backward_pays(shape, params) -> bool:
+    """Whether the no-mask backward takes long enough by products (120 us and
+    more; about 3.5 us per block of keys that a workgroup walks, or 215 blocks
+    of 64 x 64 x 64 a microsecond) for the launches that look for sparse heads
+    (15 us) and what those may gain: B4 H2 n1920 d64 causal, 88 us by products
+    and 75 with lists at c = 12, is left out, B1 H8 n2431 d128 (181 us, 100 with
+    lists) is not.  fp32 products take 16 times as long."""
+    T = (shape.seqlen + 63) // 64
+    blocks = shape.batch * shape.heads * T * (T + 1 if params.causal else 2 * T) // 2 * shape.head_dim // 64
+    return shape.dtype == EA_F32 or max(3.5 * T, blocks / 215) >= 120
+
+
 def _scratch_lists(shape, params, device, lists):
     """Element lists for one call of the no-mask mode: (tensor or None, pointer, bytes)."""
     nbytes = _lists_size(shape, params, DENSE_LISTS_FROM) if lists else 0
@@ -706,7 +718,8 @@ def backward_dense(q, k, v, dout, tau, o2, alpha=1.5, scale=None, causal=False, 
     params = make_params(alpha, scale, causal, True, None, None, head_dim=q.shape[-1])
     mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
     dq, dk, dv = mk(), mk(), mk()
-    _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device, lists)
+    _lists, lists_ptr, lists_bytes = _scratch_lists(shape, params, q.device,
+                                                    lists and _dense_backward_pays(shape, params))
     ws = _bytes_or_none(entmax_attn_bwd_lists_workspace(shape, params), q.device) if lists_ptr else None
     if ws is None:
         ws = torch.empty(max(entmax_attn_sizes(shape, params).ws_bwd, 16), dtype=torch.uint8, device=q.device)

@@ -577,8 +577,10 @@ ea_status entmax_attn_bwd_dense_lists(const ea_shape* shape, const ea_params* pa
   res.o2 = const_cast<float*>(o2);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (lists) {
+    Buckets buckets{};
+    bwd_lists_ws(d, static_cast<char*>(workspace), &buckets);
     CollectArgs ca{q, k, tau, tau_lo_of(&res, d), static_cast<ListBlock*>(lists), lists_use(d, lists),
-                   (int)d.BH, (int)d.n, (int)d.T, (params->alpha - 1.0f) * params->scale, params->causal,
+                   buckets.used /* (written after this) */, (int)d.BH, (int)d.n, (int)d.T, (params->alpha - 1.0f) * params->scale, params->causal,
                    gamma_kind(params->alpha), c64_of(params)};
     if ((st = from_hip(launch_collect(ca, d.dtype, (int)d.d, s))) != EA_OK) return st;
   }

@@ -264,7 +264,106 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
 // Workgroup = 128 rows, wave = 32 rows against both halves of every key block,
 // as the solver's one-group form.  A wave whose lists overflow stops scoring,
 // and the workgroup stops when all have.
+//
+// That pass costs as much as it can gain where a block holds COL_MOST entries
+// per key block (backward, us, products against lists: B1 H8 n2431 d128 at 40
+// entries 181 against 192, at 20 180 against 147; B4 H21 n3136 d64 causal at
+// 37 535 against 582, at 26 529 against 486), and more where rows are too long
+// for their lists.  So probe_kernel first counts the entries of a sample of
+// the scores, 64 rows x 128 keys of every eighth query block, and
+// collect_kernel leaves a head that looks denser than that alone (about 10 us,
+// where the whole pass was 115 us of 895 at B4 H21 n3136 d64 causal c = 0.5;
+// with every query block sampled probe_kernel took 15 us at B1 H16 n4096 d128).
 constexpr int COL_NT = 256;
+constexpr int COL_MOST = 28;          // entries per key block (four times that for fp32)
+constexpr int COL_SAMPLE = 4;         // sub-tiles of 32 keys, per sampled query block
+constexpr int COL_EVERY = 8;          // query blocks a sampled one stands for: 4, 12, 20, ...
+constexpr int COL_LONG = 2600;        // entries of a block some of whose rows (40 on average) may not fit 2 x LIST_CAP
+
+__host__ __device__ inline int sampled_blocks(int T) { return (T + COL_EVERY - 1) / COL_EVERY; }
+__host__ __device__ inline int sampled_block(int s, int T) {
+  return COL_EVERY * s + COL_EVERY / 2 < T ? COL_EVERY * s + COL_EVERY / 2 : T - 1;
+}
+
+template <typename E, int D>
+__global__ __launch_bounds__(COL_NT) void probe_kernel(CollectArgs a) {
+  using M = Mma<E>;
+  constexpr int KS = D / M::KW;
+  __shared__ int found[COL_NT / 64];
+  const int lane = lane_id(), w = wave_id();
+  const int n = a.n, per = sampled_blocks(a.T), bh = blockIdx.x / per;
+  const int qb = sampled_block(blockIdx.x % per, a.T);
+  const int q0 = qb * BLK + 32 * (w & 1), i = q0 + (lane & 31);
+  const E* Q = static_cast<const E*>(a.q) + (size_t)bh * n * D;
+  const E* K = static_cast<const E*>(a.k) + (size_t)bh * n * D;
+  const float tau = i < n ? a.tau[(size_t)bh * n + i] : INFINITY;
+  typename M::frag qf[KS];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) qf[kk] = load_row_frag_global<E, D>(Q, i, n, kk);
+  // one sub-tile of each quarter of the block's keys, another one in the next block
+  const int tiles = ((a.causal ? min(n, qb * BLK + BLK) : n) + 31) / 32;
+  int in = 0;
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int quarter = (w >> 1) + 2 * x, t0 = quarter * tiles / COL_SAMPLE;
+    const int j0 = 32 * min(t0 + (5 * qb + 3 * bh) % max(tiles / COL_SAMPLE, 1), tiles - 1);
+    f32x16 s = zero16();
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk)
+      s = M::mma(load_row_frag_global<E, D>(K, min(j0 + (lane & 31), n - 1), n, kk), qf[kk], s);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + crow(r);
+      in += j < n && (!a.causal || j <= i) ? in_support(relu_z(a.c, s[r], tau)) : 0;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) in += __shfl_xor(in, o);
+  if (lane == 0) found[w] = in;
+  __syncthreads();
+  if (threadIdx.x == 0) a.est[blockIdx.x] = found[0] + found[1] + found[2] + found[3];
+}
+
+// Whether head bh (in a small grid, which takes as long as its slowest head:
+// every head) looks sparse enough to collect.  Heads of about the same density
+// go the same way, by the density of all of them: some of them listed and some
+// not takes longest (B4 H21 n3136 d64 causal at 28 entries a key block: 733 us
+// against 565 and 575).  `sums` holds two counters per head.  Every thread of
+// the workgroup.
+template <typename E>
+__device__ bool looks_sparse(const CollectArgs& a, int bh, int* sums) {
+  __shared__ unsigned long long all;
+  const int T = a.T, per = sampled_blocks(T), t = threadIdx.x;
+  const bool small = a.BH * T <= PREP_SMALL;
+  const int h0 = small ? 0 : bh, heads = small ? a.BH : 1;
+  for (int h = t; h < 2 * heads; h += COL_NT) sums[h] = 0;
+  if (t == 0) all = 0;
+  __syncthreads();
+  unsigned long long mine = 0;
+  for (int x = t; x < a.BH * per; x += COL_NT) {
+    const int h = x / per, s = x - h * per, blocks = a.causal ? sampled_block(s, T) + 1 : T;
+    const int expected = a.est[x] * blocks;  // twice the block's entries
+    mine += (unsigned)expected;
+    if (h >= h0 && h < h0 + heads) {
+      atomicAdd(&sums[2 * (h - h0)], expected >> 6);
+      if (expected > 2 * COL_LONG) atomicAdd(&sums[2 * (h - h0) + 1], 1);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) mine += __shfl_xor(mine, o);
+  if (lane_id() == 0) atomicAdd(&all, mine);
+  __syncthreads();
+  int valid = per * T;  // key blocks of a head's sampled query blocks
+  if (a.causal) {
+    valid = 0;
+    for (int s = 0; s < per; ++s) valid += sampled_block(s, T) + 1;
+  }
+  const int most = COL_MOST * (sizeof(E) == 4 ? 4 : 1);
+  const int limit = (all <= 2ull * most * valid * a.BH ? 3 * most / 2 : most / 2) * (valid / 32 + 1);
+  bool sparse = true;
+  for (int h = t; h < heads; h += COL_NT) sparse &= sums[2 * h] <= limit && 8 * sums[2 * h + 1] <= per;
+  return __syncthreads_and(sparse);
+}
 
 template <typename E, int D, int GK>
 __global__ __launch_bounds__(COL_NT, sizeof(E) == 4 && D == 128 ? 1 : 3) void collect_kernel(CollectArgs a) {
@@ -290,6 +389,11 @@ __global__ __launch_bounds__(COL_NT, sizeof(E) == 4 && D == 128 ? 1 : 3) void co
   [[maybe_unused]] const double tau64 =
       (double)tau + (PRECISE && a.tau_lo && row_ok ? (double)a.tau_lo[(size_t)bh * n + i] : 0.0);
   [[maybe_unused]] const float band = PRECISE_BAND * fmaxf(1.f, fabsf(tau));
+  static_assert(sizeof(kbuf) >= 2 * PREP_SMALL * sizeof(int), "looks_sparse");
+  if (!looks_sparse<E>(a, bh, reinterpret_cast<int*>(&kbuf[0][0]))) {
+    if ((w & 1) == 0 && lane == 0 && qb < T) a.use[(size_t)bh * T + qb] = LIST_NONE;
+    return;
+  }
   for (int x = t; x < 2 * (PREP_T / 32); x += COL_NT) (&bits[0][0])[x] = 0;
   if (t < 2) entries[t] = 0;
 
@@ -1274,7 +1378,7 @@ __global__ __launch_bounds__(DQ_NT, 2) void dq_kernel(BwdArgs a) {
   const int n = a.n, T = a.T;
   int bh = blockIdx.x % a.BH;
   int qb = blockIdx.x / a.BH;
-  if (a.lists) head_major(blockIdx.x, a.BH, T, bh, qb, head_group<E, D>(n));
+  if (a.lists) head_major(blockIdx.x, a.BH, T, bh, qb, head_group<E, D>(n, 2));
   if (a.causal) qb = T - 1 - qb;  // longest lists first
   if (a.lists && (a.buckets.used[(size_t)bh * T + qb] & LISTED)) {
     gather_dq<E, D, GK>(a, a.lists[(size_t)bh * T + qb], bh, qb);
@@ -1443,6 +1547,8 @@ hipError_t launch_dq_d(const BwdArgs& a, hipStream_t s) {
 
 template <typename E, int D>
 hipError_t launch_collect_d(const CollectArgs& a, hipStream_t s) {
+  const hipError_t e = launch_kernel(probe_kernel<E, D>, dim3((unsigned)(a.BH * sampled_blocks(a.T))), dim3(COL_NT), s, a);
+  if (e != hipSuccess) return e;
   dim3 grid((unsigned)(a.BH * ((a.T + 1) / 2))), block(COL_NT);
   auto kernel = collect_kernel<E, D, 1>;  // the kinds but fp32's general alpha differ in nothing here
   if (sizeof(E) == 4 && a.gk == 0) kernel = collect_kernel<E, D, 0>;

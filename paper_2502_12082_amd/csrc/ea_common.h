@@ -544,15 +544,16 @@ __device__ __forceinline__ void head_major(int b, int BH, int T, int& bh, int& b
   bh = (b & (x - 1)) + ((h0 + r % g) << lg);
 }
 
-// Heads of a group: as many as have one operand each in 3 of an XCD's 4 MiB
-// of L2.  One at a time, the long blocks of a causal head start when the others
+// Heads of a group: as many as have their operands (V for the forward's
+// gather, K and V for that of dQ) in 3 of an XCD's 4 MiB of L2 (two heads of
+// B1 H16 n4096 d128, 2 MiB each, took dQ 72 us, one at a time 67).  One at a time, the long blocks of a causal head start when the others
 // have drained, and the workgroups of a head read the same tiles at the same
 // time: where no block is listed the forward of B8 H12 n1024 d64 took 83
 // against 76 us, of B4 H12 n4096 d64 causal 250 against 240 (4 of its 6 heads
 // at a time).
 template <typename E, int D>
-__device__ __forceinline__ int head_group(int n) {
-  return max(1, (3 << 20) / (n * D * (int)sizeof(E)));
+__device__ __forceinline__ int head_group(int n, int operands) {
+  return max(1, (3 << 20) / (n * D * (int)sizeof(E) * operands));
 }
 
 }  // namespace ea

@@ -180,7 +180,7 @@ __global__ __launch_bounds__(FWD_NT, !TRAIN && D == 64 && sizeof(E) == 2 ? 4 : 2
   const int n = a.n, T = a.T;
   int bh = blockIdx.x % a.BH;
   int qb = blockIdx.x / a.BH;
-  if (a.lists) head_major(blockIdx.x, a.BH, T, bh, qb, head_group<E, D>(n));
+  if (a.lists) head_major(blockIdx.x, a.BH, T, bh, qb, head_group<E, D>(n, 1));
   if (a.causal) qb = T - 1 - qb;  // longest lists first
   if (a.lists && (((const ci32*)a.use)[(size_t)bh * T + qb] & LIST_FWD)) {
     gather_fwd<E, D, GK, TRAIN>(a, a.lists[(size_t)bh * T + qb], bh, qb);

@@ -199,6 +199,7 @@ struct CollectArgs {
   const float* tau_lo;  // as in BwdArgs
   ListBlock* lists;
   int32_t* use;  // as in TauArgs
+  int32_t* est;  // scratch, at most [BH * T]: entries found in a sample of query blocks
   int BH, n, T;
   float c;
   int causal, gk;
@@ -247,6 +248,7 @@ hipError_t launch_bwd_dkdv(const BwdArgs& a, int dtype, int head_dim, hipStream_
 // dK and dV of the listed query blocks, added to what launch_bwd_dkdv (given
 // the same lists) wrote for the others.
 hipError_t launch_bwd_dkdv_lists(const BwdArgs& a, int dtype, int head_dim, hipStream_t s);
+// (a sample of the density, then the lists of heads that look sparse)
 hipError_t launch_collect(const CollectArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dq(const BwdArgs& a, int dtype, int head_dim, hipStream_t s);
 hipError_t launch_rows_fwd(const RowsArgs& a, int dtype, hipStream_t s);

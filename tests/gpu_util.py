@@ -244,3 +244,39 @@ def check_tables(gpu: dict, causal: bool, columns: bool = True):
             rows = np.nonzero(M[:, j])[0]
             assert gpu["k_count"][bh, j] == rows.size
             assert np.array_equal(gpu["k_index"][bh, j, :rows.size], rows)
+
+
+# ListUse and ListBlock of csrc/ea_internal.h: bits of what a query block's
+# element lists serve; bytes of a record, and the place of its 128 counts.
+LIST_FWD, LIST_DQ, LIST_DKDV = 1, 2, 4
+LIST_RECORD, LIST_COUNTS = 37248, 48 * 128 * 6
+
+
+def list_uses(lists, blocks):
+    """What each of `blocks` query blocks' lists serve, and their entries."""
+    at = (blocks * LIST_RECORD + 255) // 256 * 256
+    use = lists[at:at + 4 * blocks].cpu().numpy().view(np.int32)
+    rec = lists[:blocks * LIST_RECORD].view(blocks, LIST_RECORD)
+    counts = rec[:, LIST_COUNTS:LIST_COUNTS + 128].cpu().numpy().astype(np.int64)
+    return use, np.where(use != 0, counts.sum(1), 0)
+
+
+def list_entries(lists, block):
+    """(row, key) of each entry of a listed query block."""
+    rec = lists[block * LIST_RECORD:(block + 1) * LIST_RECORD].cpu().numpy()
+    key = rec[48 * 128 * 4:LIST_COUNTS].view(np.uint16).reshape(48, 128)
+    counts = rec[LIST_COUNTS:LIST_COUNTS + 128]
+    e, i = np.nonzero(np.arange(48)[:, None] < counts[None, :])
+    return i % 64, key[e, i].astype(np.int64)
+
+
+def sorted_blocks(workspace, rows, blocks, heads):
+    """(used, heads) of a backward's workspace after it ran with lists: whether
+    each query block's lists served dQ (1) and were sorted for dK, dV (2), and
+    whether a head has any of the latter.  rows: batch * heads * seqlen."""
+    T = blocks // heads
+    up = lambda x: (x + 255) // 256 * 256
+    at = up(rows * 4)
+    used = workspace[at:at + 4 * blocks].cpu().numpy().view(np.int32).reshape(heads, T)
+    at += up(4 * blocks)
+    return used, workspace[at:at + 4 * heads].cpu().numpy().view(np.int32)

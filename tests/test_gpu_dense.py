@@ -99,3 +99,37 @@ def test_dense_f32_general_alpha(n, causal, d):
             assert errs["tau"] <= TAU_REL
             for key in ("o", "o2", "dq", "dk", "dv"):
                 assert errs[key] <= F32_TOL, (key, alpha, errs)
+
+
+@pytest.mark.parametrize("dtype,n,causal,c,listed", [
+    ("bf16", 2431, False, 0.5, False), ("bf16", 2431, False, 4.0, True), ("bf16", 2200, True, 0.5, False),
+    ("bf16", 2200, True, 8.0, True), ("f32", 700, False, 0.1, False), ("f32", 700, False, 4.0, True)])
+def test_dense_backward_samples_first(dtype, n, causal, c, listed):
+    """The no-mask backward samples the density and collects the lists of
+    sparse heads alone; the gradients are the masked path's either way."""
+    import ctypes
+    import paper_2502_12082_amd as ea
+    from gpu_util import list_uses
+    inp = synth.attention_inputs(1, 3, n, 64, c=c, dtype=dtype, with_dout=True, seed=n)
+    q, k, v, do = (to_device(inp[x]) for x in ("q", "k", "v", "dout"))
+    _, res = ea.forward(q, k, v, alpha=1.5, causal=causal)
+    ref = ea.backward(q, k, v, do, res)
+    shape, params = ea.make_shape(q), ea.make_params(1.5, None, causal, head_dim=64)
+    byte = lambda size: torch.empty(size, dtype=torch.uint8, device=q.device)
+    lists = byte(ea.entmax_attn_lists_bytes(shape, params))
+    ws = byte(ea.entmax_attn_bwd_lists_workspace(shape, params))
+    got = [torch.empty(q.shape, dtype=torch.float32, device=q.device) for _ in range(3)]
+    p = lambda t: None if t is None else t.data_ptr()
+    st = ea._lib.entmax_attn_bwd_dense_lists(
+        ctypes.byref(shape), ctypes.byref(params), p(q), p(k), p(v), p(do), p(res.tau), p(res.tau_lo),
+        p(res.o2), p(lists), lists.numel(), *map(p, got), p(ws), ws.numel(),
+        torch.cuda.current_stream().cuda_stream)
+    assert st == ea.EA_OK
+    T = (n + 63) // 64
+    use, entries = list_uses(lists, 3 * T)
+    log("n %d causal %d c %g: %d of %d blocks listed, %d entries" % (n, causal, c, (use > 0).sum(), 3 * T,
+                                                                     entries.sum()))
+    assert (use > 0).mean() > 0.9 if listed else (use == 0).all()
+    for a, b in zip(got, ref):
+        # the rounding of P to bf16 in one of the two; of sums of n terms in fp32
+        assert (a - b).norm() <= (2 ** -8 if dtype == "bf16" else 2e-5) * b.norm()
