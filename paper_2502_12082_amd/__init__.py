@@ -308,9 +308,9 @@ class _Claim:
     def __init__(self, index, nbytes):
         self.index, self.nbytes = index, nbytes
 
-    def __del__(self):
-        with _held_lock:
-            _held[self.index] -= self.nbytes
+    def __del__(self, lock=_held_lock, held=_held):  # (module globals may be gone at exit)
+        with lock:
+            held[self.index] -= self.nbytes
 
     def __reduce__(self):
         return type(None), ()

@@ -338,3 +338,17 @@ def test_lists_take_a_bounded_share(monkeypatch):
     assert ea._scratch_lists(ea.make_shape(_bf(1, 1, 2048, 64)), p, dev, False) == (None, None, 0)
     del a, c, d
     assert ea._held[None] == held
+
+
+def test_residuals_at_exit():
+    """Residuals that live until the interpreter ends go quietly."""
+    import subprocess
+    import sys
+    code = ("import paper_2502_12082_amd as ea, torch\n"
+            "q = torch.zeros(1, 2, 512, 64, dtype=torch.bfloat16)\n"
+            "r = ea.Residuals(ea.make_shape(q), ea.make_params(head_dim=64), 'cpu')\n"
+            "ea.keep, r.self = r, r\n"
+            "assert r.lists is not None\n")
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True,
+                         timeout=300)
+    assert out.returncode == 0 and "Exception ignored" not in out.stderr, out.stderr

@@ -46,8 +46,11 @@ def _both(inp, alpha, causal, ws_frac=1.0, ws_bytes=None):
 @pytest.mark.parametrize("alpha", [1.5, 2.0, 1.25, 1.6, 3.0])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("c", [0.25, 1.0, 4.0])
-def test_cache_matches_streaming(alpha, causal, c):
-    inp = synth.attention_inputs(1, 2, 1000, 64, c=c, dtype="bf16", seed=1234)
+@pytest.mark.parametrize("n", [1000, 1100])
+def test_cache_matches_streaming(alpha, causal, c, n):
+    """n = 1000 runs the solver for short sequences, which takes no workspace
+    and streams K once; n = 1100 the cached solver and its streamed form."""
+    inp = synth.attention_inputs(1, 2, n, 64, c=c, dtype="bf16", seed=1234)
     log("cache vs stream alpha=%g causal=%d c=%g" % (alpha, causal, c))
     (o0, r0), (o1, r1) = _both(inp, alpha, causal)
     t0, t1 = r0.tau.double(), r1.tau.double()
@@ -59,10 +62,17 @@ def test_cache_matches_streaming(alpha, causal, c):
     assert do <= BF16_TOL
     # the cache adds at most one K pass per fill attempt (two attempts)
     assert (r1.stats[0] <= r0.stats[0] + 2).all()
+    if n <= 1024:
+        assert (r0.stats[0] == 1).all() and (r1.stats[0] == 1).all()
+    else:
+        assert (r0.stats[0] > 1).all()
+        if c == 4.0 and alpha <= 2:  # the lists fit
+            assert (r1.stats[0] == 1).all()
 
 
 @pytest.mark.parametrize("alpha", [1.5, 3.0])
-def test_cache_against_oracle(alpha):
+@pytest.mark.parametrize("n", [700, 1100])
+def test_cache_against_oracle(alpha, n):
     """Whole heads against the oracle with the cache on, ragged n, both masks.
     For alpha > 2 the safeguarded iteration converges linearly at worst, so
     that case runs with a larger iteration budget than the default 12, and it
@@ -72,8 +82,8 @@ def test_cache_against_oracle(alpha):
     max_iter = 12 if alpha <= 2 else 40
     bwd = alpha <= 2
     for causal in (False, True):
-        inp = synth.attention_inputs(1, 2, 700, 64, c=1.0, dtype="bf16", with_dout=bwd, seed=99)
-        log("cache vs oracle alpha=%g causal=%d" % (alpha, causal))
+        inp = synth.attention_inputs(1, 2, n, 64, c=1.0, dtype="bf16", with_dout=bwd, seed=99)
+        log("cache vs oracle n=%d alpha=%g causal=%d" % (n, alpha, causal))
         gpu = run_gpu(inp, alpha, 64 ** -0.5, causal, bwd, max_iter=max_iter)
         check_tables(gpu, causal, columns=bwd)
         for bh in range(2):
@@ -167,10 +177,8 @@ def test_cache_uncompacted_quads():
 @pytest.mark.parametrize("wide", [0.2, 0.35, 0.5])
 def test_cache_wide_rows_among_narrow(alpha, wide):
     """A few rows of a wide support among rows whose lists fit (queries of
-    temperature `wide` among ones of temperature 2): their lists fill up late,
-    the bound they are collected with is refined from the lists themselves,
-    and the dropped scores must all lie below the returned tau.  tau, O and
-    the mask equal streaming whether or not the lists fit in the end."""
+    temperature `wide` among ones of temperature 2), which overflow at alpha
+    1.25 and 1.5 and fit at 2: tau, O and the mask equal streaming either way."""
     inp = synth.attention_inputs(1, 2, 4096, 64, c=2.0, dtype="bf16", seed=4321)
     raw = inp["q"].f32().copy()
     raw[:, :, [5, 300, 1500, 4095]] *= wide / 2.0
@@ -178,12 +186,27 @@ def test_cache_wide_rows_among_narrow(alpha, wide):
     (o0, r0), (o1, r1) = _both(inp, alpha, False)
     dt = ((r1.tau.double() - r0.tau.double()).abs() / r0.tau.double().abs().clamp(min=1.0)).max().item()
     log("wide rows %g alpha %g: dtau %.2e, K passes max %d" % (wide, alpha, dt, r1.stats[0].max().item()))
+    assert (r1.stats[0].max().item() > 1) == (alpha < 2)
     # each side stops with |f| <= 1e-5, and |f'| >= 1 at the root, so the two
     # are within 2e-5 but where the cap of 12 updates ends the iteration
     assert dt <= 1e-4
     assert (o1.float() - o0.float()).abs().max().item() <= BF16_TOL
     assert torch.equal(r0.block_mask, r1.block_mask) or \
         (r0.block_mask != r1.block_mask).float().mean().item() < 1e-3
+
+
+def test_cache_refined_bound():
+    """alpha 1.5, c = 1 at n = 8192, d = 128: the lists of a few rows fill up in
+    the last quarter of the key blocks, and the bound they are collected with is
+    then refined from the lists themselves, so that all tiles finish on their
+    lists (without it the longest take 3 K passes); the dropped scores all lie
+    below the returned tau, which is streaming's."""
+    inp = synth.attention_inputs(1, 16, 8192, 128, c=1.0, dtype="bf16", seed=synth.SEED_BASE)
+    (o0, r0), (o1, r1) = _both(inp, 1.5, False)
+    dt = ((r1.tau.double() - r0.tau.double()).abs() / r0.tau.double().abs().clamp(min=1.0)).max().item()
+    log("refined: dtau %.2e, K passes max %d" % (dt, r1.stats[0].max().item()))
+    assert r1.stats[0].max().item() == 1
+    assert dt <= 1e-4 and (o1.float() - o0.float()).abs().max().item() <= BF16_TOL
 
 
 @pytest.mark.parametrize("c,evals", [(0.273, 4), (2.0, 3.5)])
