@@ -653,13 +653,14 @@ def rows_backward(s, tau, dp, alpha=1.5, scale=1.0):
 def _dense_backward_pays(shape, params) -> bool:
     """Whether the no-mask backward takes long enough by products (120 us and
     more; about 3.5 us per block of keys that a workgroup walks, or 215 blocks
-    of 64 x 64 x 64 a microsecond) for the launches that look for sparse heads
+    of 64 x 64 x 64 a microsecond, 1.6 times that with a general alpha) for the launches that look for sparse heads
     (15 us) and what those may gain: B4 H2 n1920 d64 causal, 88 us by products
     and 75 with lists at c = 12, is left out, B1 H8 n2431 d128 (181 us, 100 with
     lists) is not.  fp32 products take 16 times as long."""
     T = (shape.seqlen + 63) // 64
     blocks = shape.batch * shape.heads * T * (T + 1 if params.causal else 2 * T) // 2 * shape.head_dim // 64
-    return shape.dtype == EA_F32 or max(3.5 * T, blocks / 215) >= 120
+    us = max(3.5 * T, blocks / 215) * (1.0 if params.alpha in (1.25, 1.5, 2.0) else 1.6)
+    return shape.dtype == EA_F32 or us >= 120
 
 
 def _scratch_lists(shape, params, device, lists):

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
   const int nr = min(BLK, a.n - qb * BLK);
   const long long row0 = (long long)bh * a.n + (long long)qb * BLK;
   // uses of the head's blocks, or of every head's in a small grid (see below)
-  const bool small = a.BH * a.T <= PREP_SMALL;
+  const bool small = sizeof(E) == 2 && a.BH * a.T <= PREP_SMALL;
   const int h0 = small ? 0 : bh, heads = small ? a.BH : 1;
   int all_use[PREP_SMALL / PREP_NT];
 #pragma unroll
@@ -135,7 +135,9 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
   // to be so.  (dK/dV and sort, with against without lists, in us: B1 H4
   // n11392 d128 causal, 537 of 712 blocks listed 689 against 459, 618 of them
   // 303 against 470; B8 H8 n3000 d64 causal, 2192 of 3008 329 against 234;
-  // B4 H12 n4096 d64 causal, 2478 of 3072 319 against 306.)
+  // B4 H12 n4096 d64 causal, 2478 of 3072 319 against 306.)  fp32 products take
+  // 16 times as long: three quarters of the head alone do there (step of B1 H2
+  // n1984 d128 causal c = 0.6 1030 us against 1456 with the rule of bf16).
   bool split = true;
   if (use & LIST_DKDV || qb == 0) {
     uint32_t* const rest = &cursor[0][0];  // unlisted blocks of each head
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
       if (x < heads * T && !(all_use[k] & LIST_DKDV)) atomicAdd(&rest[(int)(((float)x + 0.5f) * per_head)], 1u);
     }
     __syncthreads();
-    for (int h = t; h < heads; h += PREP_NT) split &= 8 * (int)rest[h] <= T;
+    for (int h = t; h < heads; h += PREP_NT) split &= (sizeof(E) == 2 ? 8 : 4) * (int)rest[h] <= T;
     split = __syncthreads_and(split);
     if (qb == 0 && t == 0) a.buckets.heads[bh] = split;
   }
@@ -274,11 +276,16 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(DeltaArgs a) {
 // collect_kernel leaves a head that looks denser than that alone (about 10 us,
 // where the whole pass was 115 us of 895 at B4 H21 n3136 d64 causal c = 0.5;
 // with every query block sampled probe_kernel took 15 us at B1 H16 n4096 d128).
+// With a general alpha the maps of the products take longer, and both limits
+// are higher (B2 H3 n11674 d64 alpha 1.75 c = 0.3: 1975 against 3261 us a step).
+// fp32 calls always collect: their products take 16 times as long, and the
+// sample 20 us.
 constexpr int COL_NT = 256;
-constexpr int COL_MOST = 28;          // entries per key block (four times that for fp32)
+constexpr int COL_MOST = 28;          // entries per key block (twice that with a general alpha)
 constexpr int COL_SAMPLE = 4;         // sub-tiles of 32 keys, per sampled query block
 constexpr int COL_EVERY = 8;          // query blocks a sampled one stands for: 4, 12, 20, ...
-constexpr int COL_LONG = 2600;        // entries of a block some of whose rows (40 on average) may not fit 2 x LIST_CAP
+// entries of a block some of whose rows (40 or 56 on average) may not fit 2 x LIST_CAP
+constexpr int COL_LONG = 2600, COL_LONG_GENERAL = 3600;
 
 __host__ __device__ inline int sampled_blocks(int T) { return (T + COL_EVERY - 1) / COL_EVERY; }
 __host__ __device__ inline int sampled_block(int s, int T) {
@@ -330,7 +337,6 @@ __global__ __launch_bounds__(COL_NT) void probe_kernel(CollectArgs a) {
 // not takes longest (B4 H21 n3136 d64 causal at 28 entries a key block: 733 us
 // against 565 and 575).  `sums` holds two counters per head.  Every thread of
 // the workgroup.
-template <typename E>
 __device__ bool looks_sparse(const CollectArgs& a, int bh, int* sums) {
   __shared__ unsigned long long all;
   const int T = a.T, per = sampled_blocks(T), t = threadIdx.x;
@@ -346,7 +352,7 @@ __device__ bool looks_sparse(const CollectArgs& a, int bh, int* sums) {
     mine += (unsigned)expected;
     if (h >= h0 && h < h0 + heads) {
       atomicAdd(&sums[2 * (h - h0)], expected >> 6);
-      if (expected > 2 * COL_LONG) atomicAdd(&sums[2 * (h - h0) + 1], 1);
+      if (expected > 2 * (a.gk == 0 ? COL_LONG_GENERAL : COL_LONG)) atomicAdd(&sums[2 * (h - h0) + 1], 1);
     }
   }
 #pragma unroll
@@ -358,7 +364,7 @@ __device__ bool looks_sparse(const CollectArgs& a, int bh, int* sums) {
     valid = 0;
     for (int s = 0; s < per; ++s) valid += sampled_block(s, T) + 1;
   }
-  const int most = COL_MOST * (sizeof(E) == 4 ? 4 : 1);
+  const int most = a.gk == 0 ? 2 * COL_MOST : COL_MOST;
   const int limit = (all <= 2ull * most * valid * a.BH ? 3 * most / 2 : most / 2) * (valid / 32 + 1);
   bool sparse = true;
   for (int h = t; h < heads; h += COL_NT) sparse &= sums[2 * h] <= limit && 8 * sums[2 * h + 1] <= per;
@@ -390,7 +396,7 @@ __global__ __launch_bounds__(COL_NT, sizeof(E) == 4 && D == 128 ? 1 : 3) void co
       (double)tau + (PRECISE && a.tau_lo && row_ok ? (double)a.tau_lo[(size_t)bh * n + i] : 0.0);
   [[maybe_unused]] const float band = PRECISE_BAND * fmaxf(1.f, fabsf(tau));
   static_assert(sizeof(kbuf) >= 2 * PREP_SMALL * sizeof(int), "looks_sparse");
-  if (!looks_sparse<E>(a, bh, reinterpret_cast<int*>(&kbuf[0][0]))) {
+  if (sizeof(E) == 2 && !looks_sparse(a, bh, reinterpret_cast<int*>(&kbuf[0][0]))) {
     if ((w & 1) == 0 && lane == 0 && qb < T) a.use[(size_t)bh * T + qb] = LIST_NONE;
     return;
   }
@@ -1547,8 +1553,11 @@ hipError_t launch_dq_d(const BwdArgs& a, hipStream_t s) {
 
 template <typename E, int D>
 hipError_t launch_collect_d(const CollectArgs& a, hipStream_t s) {
-  const hipError_t e = launch_kernel(probe_kernel<E, D>, dim3((unsigned)(a.BH * sampled_blocks(a.T))), dim3(COL_NT), s, a);
-  if (e != hipSuccess) return e;
+  if constexpr (sizeof(E) == 2) {
+    const dim3 sampled((unsigned)(a.BH * sampled_blocks(a.T)));
+    const hipError_t e = launch_kernel(probe_kernel<E, D>, sampled, dim3(COL_NT), s, a);
+    if (e != hipSuccess) return e;
+  }
   dim3 grid((unsigned)(a.BH * ((a.T + 1) / 2))), block(COL_NT);
   auto kernel = collect_kernel<E, D, 1>;  // the kinds but fp32's general alpha differ in nothing here
   if (sizeof(E) == 4 && a.gk == 0) kernel = collect_kernel<E, D, 0>;

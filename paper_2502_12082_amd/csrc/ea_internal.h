@@ -72,8 +72,9 @@ static_assert(sizeof(ListBlock) % 128 == 0, "records keep their alignment");
 // against 59; at 55 dK/dV with the sort 95 against 108; B8 H4 n1169 at 107
 // solver and forward 169 against 166.  B64 H16 n128, at 512: 34 against 33, 42
 // against 28, 103 against 42).  fp32 products take 16
-// times as long, but a listed entry twice the bytes: four times the limits (B8
-// H16 n512 d64, 136 per block: forward 31 against 124, dQ 41 against 127).
+// times as long, but a listed entry twice the bytes and a store the same: four
+// and six times the limits (B8 H16 n512 d64, 136 per block: forward 31 against
+// 124, dQ 41 against 127).
 // Among many key blocks a few entries are always listed for dK/dV (the first
 // rows of a causal head), since one block that is not makes the whole head
 // take both ways; the forward and dQ of such a block are a step or two of
@@ -81,7 +82,7 @@ static_assert(sizeof(ListBlock) % 128 == 0, "records keep their alignment");
 // 1000 entries a key block: dQ 131 us without lists, 141 with).
 // (An array of their own beside the records: kernels read one of many blocks.)
 enum ListUse { LIST_NONE = 0, LIST_FWD = 1, LIST_DQ = 2, LIST_DKDV = 4 };  // bits
-constexpr int LIST_MOST = 100;  // entries per key block, for any use
+constexpr int LIST_MOST = 100, LIST_MOST_F32 = 600;  // entries per key block, for any use
 #if defined(__HIPCC__)
 __host__ __device__ inline int list_few(int T) { return 32 * T < 1024 ? 32 * T : 1024; }
 __host__ __device__ inline int list_use(int entries, int blocks, int T, bool f32) {
@@ -89,7 +90,7 @@ __host__ __device__ inline int list_use(int entries, int blocks, int T, bool f32
   if (entries > LIST_ENTRIES) return LIST_NONE;
   if (entries <= 64 * per) return LIST_FWD | LIST_DQ | LIST_DKDV;
   const int few = entries <= list_few(T) ? LIST_DKDV : LIST_NONE;
-  return entries <= LIST_MOST * per ? few | LIST_FWD | LIST_DQ : few;
+  return entries <= (f32 ? LIST_MOST_F32 : LIST_MOST) * blocks ? few | LIST_FWD | LIST_DQ : few;
 }
 #endif
 

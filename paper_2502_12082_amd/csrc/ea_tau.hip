@@ -61,9 +61,13 @@ constexpr int WARM_STOP = SV_NT / 2;
 // above it, at d = 64, the first stream covers every key block
 constexpr int WARM_ALL = 3 * SV_NT / 4;
 // Newton steps of a refined collection bound, and the most lists of a wave
-// (of 64) over half of their capacity for which it is tried (in the last quarter of the blocks)
+// (of 64) over half of their capacity for which it is tried (in the last
+// quarter of the blocks); in a launch of one wave of workgroups with at least
+// REFINE_MORE_BLOCKS key blocks, the most over three quarters of it
 constexpr int REFINE_STEPS = 3;
 constexpr int REFINE_LISTS = 4;
+constexpr int REFINE_MORE_LISTS = 16;
+constexpr int REFINE_MORE_BLOCKS = 32;
 // quads beyond their share of 1.5 times the capacity at which lists are given up
 constexpr int GIVE_UP_MIN = 24;
 static_assert(SV_ROWS == 64 * SV_WAVES, "one 64-row query block per wave (G = 2)");
@@ -635,6 +639,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   // scores pass than at the bound of the first stream alone.
   const int first = W < nkb ? W : 0;
   int seen = 0;  // key blocks searched for the lists
+  const bool more = g <= 2.f && T >= REFINE_MORE_BLOCKS && a.BH * nqt <= SV_G1_BELOW * 2 / G;
   auto nth = [&](int kb) { return kb >= first ? kb - first : kb - first + nkb; };  // its place in the stream
   stream_from(first, [&](int kb, const E* kt) {
     // once the lists have overflowed, the first stream's blocks need nothing
@@ -682,11 +687,18 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     // evaluation, and the launch wait for it (n = 8192, d = 128, alpha 1.5,
     // c = 1: 0.67 against 1.16 ms with 2 such tiles of 512).  Where many are
     // long the scans cost more than they save (alpha 1.25, c = 2: 2.27
-    // against 1.60 ms).
+    // against 1.60 ms), unless all tiles run at once and the last one decides:
+    // then more of them may be long (no-mask forward, us, with against without:
+    // B1 H8 n2431 d128 c = 0.7 246 against 356, B1 H16 n4096 d128 c = 0.85 403
+    // against 530, B1 H8 n8192 d64 c = 1 558 against 639; but B4 H21 n3136 d64,
+    // two waves of tiles, c = 0.5 1639 against 1568, B8 H12 n1024 c = 0.4 708
+    // against 591, alpha 1.25 B4 H8 n4096 c = 2 969 against 711).
 #pragma unroll
     for (int gq = 0; gq < G; ++gq) {
       if (__ballot(cc[gq] > a.cap - 8) != 0ull) {
-        if (newton_bound && 4 * nth(kb) >= 3 * nkb && __popcll(__ballot(cc[gq] > a.cap / 2)) <= REFINE_LISTS) refine(gq);
+        if (newton_bound && 4 * nth(kb) >= 3 * nkb &&
+            (int)__popcll(__ballot(cc[gq] > (more ? 3 * a.cap / 4 : a.cap / 2))) <= (more ? REFINE_MORE_LISTS : REFINE_LISTS))
+          refine(gq);
         filter(gq, sb[gq]);
         if (__ballot(cc[gq] > a.cap - 8) != 0ull) {
           fill_dead = 1;
@@ -1047,7 +1059,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   // among many that are keeps the launches of the later kernels waiting for it;
   // nor where the support is more than any use takes: B8 H12 n1024 d64 c = 0.5,
   // 460 against 408 us)
-  const int most = LIST_MOST * 33 / 32 * (sizeof(E) == 4 ? 4 : 1) * (a.causal ? qb + 1 : T);
+  const int most = (sizeof(E) == 4 ? LIST_MOST_F32 : LIST_MOST) * 33 / 32 * (a.causal ? qb + 1 : T);
   const bool listable =
       cached && __popcll(__ballot(any_over(lists == 1 ? ns : cc, LIST_CAP * 3 / 2))) <= 8 &&
       (support <= list_few(T) || support <= most);

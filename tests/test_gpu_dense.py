@@ -106,7 +106,8 @@ def test_dense_f32_general_alpha(n, causal, d):
     ("bf16", 2200, True, 8.0, True), ("f32", 700, False, 0.1, False), ("f32", 700, False, 4.0, True)])
 def test_dense_backward_samples_first(dtype, n, causal, c, listed):
     """The no-mask backward samples the density and collects the lists of
-    sparse heads alone; the gradients are the masked path's either way."""
+    sparse heads alone (fp32 collects always, and lists what is sparse); the
+    gradients are the masked path's either way."""
     import ctypes
     import paper_2502_12082_amd as ea
     from gpu_util import list_uses
