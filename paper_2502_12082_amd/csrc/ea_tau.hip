@@ -638,8 +638,8 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   // in, and takes them last, at the bound of all the others: fewer of their
   // scores pass than at the bound of the first stream alone.
   const int first = W < nkb ? W : 0;
-  int seen = 0;  // key blocks searched for the lists
-  const bool more = g <= 2.f && T >= REFINE_MORE_BLOCKS && a.BH * nqt <= SV_G1_BELOW * 2 / G;
+  [[maybe_unused]] int seen = 0;  // key blocks searched for the lists
+  const bool more = sizeof(E) == 2 && g <= 2.f && T >= REFINE_MORE_BLOCKS && a.BH * nqt <= SV_G1_BELOW * 2 / G;
   auto nth = [&](int kb) { return kb >= first ? kb - first : kb - first + nkb; };  // its place in the stream
   stream_from(first, [&](int kb, const E* kt) {
     // once the lists have overflowed, the first stream's blocks need nothing
@@ -769,8 +769,12 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   // clamped to 1 there and f reads 0 all the way to the root.
 #pragma unroll
   for (int gq = 0; gq < G; ++gq) {
-    const int quads = cc[gq] + __shfl_xor(cc[gq], 32);  // of 16 a key block
-    const bool near = g > 2.f && seen > 0 && quads <= 14 * seen;
+    bool near = false;
+    // (fp32 at d = 128 has no registers left for it)
+    if constexpr ((GK == 4 || GK == 0) && !(sizeof(E) == 4 && D == 128)) {
+      const int quads = cc[gq] + __shfl_xor(cc[gq], 32);  // of 16 a key block
+      near = g > 2.f && seen > 0 && quads <= 14 * seen;
+    }
     if (!newton_bound || !(cached || near)) tau[gq] = 0.5f * (lo[gq] + hi[gq]);
   }
   int attempts = cache ? 1 : 0;  // cache fills tried (pass 0 is the first)
@@ -781,7 +785,7 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
 #pragma unroll
   for (int gq = 0; gq < G; ++gq) f_prev[gq] = INFINITY;
 
-  int last_mc[G] = {};  // support counted by the last evaluation
+  int support = 0;  // of the wave's rows, at the last evaluation (uniform)
   for (int it = 0;; ++it) {
     // ---- evaluation at tau (per group): m0 = sum z^gamma, m1 = sum
     // z^(gamma-1), m2 = sum z^(gamma-2) over the strict support z > 0, mc =
@@ -984,7 +988,6 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     float f[G], f1[G], f2[G];
 #pragma unroll
     for (int gq = 0; gq < G; ++gq) {
-      last_mc[gq] = mc[gq];
       if constexpr (GK == 1) m1[gq] = (float)mc[gq];
       if constexpr (GK == 2) m2[gq] = (float)mc[gq];
       m0[gq] = sum_halves(m0[gq]);
@@ -1013,6 +1016,13 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     const bool stop = __syncthreads_and(conv) || it >= a.max_iter;
     evals = it + 1;
     if (stop && !cached) break;
+    if (sizeof(E) == 2 && stop && a.lists) {
+#pragma unroll
+      for (int gq = 0; gq < G; ++gq) support += mc[gq];
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) support += __shfl_xor(support, o);
+      support = __builtin_amdgcn_readfirstlane(support);
+    }
 #pragma unroll
     for (int gq = 0; gq < G; ++gq) {
       if (!row_ok[gq]) continue;
@@ -1046,23 +1056,19 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
   __shared__ int lsum[SV_WAVES], ssum[SV_WAVES];
   if (lane == 0 && writer) lsum[qbl] = ssum[qbl] = 0;
   __syncthreads();
-  int support = 0;  // of the block's rows, at the last evaluation
-#pragma unroll
-  for (int gq = 0; gq < G; ++gq) support += last_mc[gq];
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) support += __shfl_xor(support, o);
-  if (lane == 0) atomicAdd(&ssum[qbl], support);
-  __syncthreads();
-  support = ssum[qbl];
   // (not tried where many rows hold half as many candidates again as a list
   // takes; a few such rows may still fit, and one block that is not listed
-  // among many that are keeps the launches of the later kernels waiting for it;
-  // nor where the support is more than any use takes: B8 H12 n1024 d64 c = 0.5,
-  // 460 against 408 us)
-  const int most = (sizeof(E) == 4 ? LIST_MOST_F32 : LIST_MOST) * 33 / 32 * (a.causal ? qb + 1 : T);
-  const bool listable =
-      cached && __popcll(__ballot(any_over(lists == 1 ? ns : cc, LIST_CAP * 3 / 2))) <= 8 &&
-      (support <= list_few(T) || support <= most);
+  // among many that are keeps the launches of the later kernels waiting for it)
+  bool listable = cached && __popcll(__ballot(any_over(lists == 1 ? ns : cc, LIST_CAP * 3 / 2))) <= 8;
+  // (nor where the support is more than any use takes: B8 H12 n1024 d64 c =
+  // 0.5, 460 against 408 us; not for fp32, whose limits are wide, and which at
+  // d = 128 would pass 256 registers and run one wave per SIMD)
+  if constexpr (sizeof(E) == 2) {
+    if (lane == 0) atomicAdd(&ssum[qbl], support);
+    __syncthreads();
+    support = __builtin_amdgcn_readfirstlane(ssum[qbl]);
+    listable &= support <= list_few(T) || support <= LIST_MOST * 33 / 32 * (a.causal ? qb + 1 : T);
+  }
   ListBlock* const lb = a.lists && listable && qb < T ? a.lists + ((size_t)bh * T + qb) : nullptr;
   int lc[G] = {};
   auto list_id = [&](int gq) { return 64 * (lane >> 5) + (q0 - qb * BLK) + 32 * gq + (lane & 31); };
