@@ -495,10 +495,10 @@ def rows_bench(steps=20, warmup=3, rows=8192, n=8192, alpha=1.5):
 
 
 def dense_mode_bench(run, steps=5, warmup=2):
-    """The no-mask mode (fused tau + O forward, table-free backward) on the
-    headline workload: ms per fwd+bwd step and dense-equivalent TFLOP/s.  All
-    buffers are allocated before the timed loop, which makes only the two C
-    ABI calls per step."""
+    """The no-mask mode (no mask, no tables; element lists as scratch, as
+    forward_dense and backward_dense use them) on the headline workload: ms per
+    fwd+bwd step and dense-equivalent TFLOP/s.  All buffers are allocated before
+    the timed loop, which makes only the two C ABI calls per step."""
     import ctypes
     import torch
     import paper_2502_12082_amd as ea
@@ -509,18 +509,22 @@ def dense_mode_bench(run, steps=5, warmup=2):
     f32 = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
     o2, dq, dk, dv = f32(), f32(), f32(), f32()
     ws = ea.forward_workspace(run.res, q.device)
-    wsb = torch.empty(run.res.sizes.ws_bwd // 4 + 4, dtype=torch.float32, device=q.device)
+    byte = lambda size: torch.empty(max(size, 16), dtype=torch.uint8, device=q.device)
+    lists = byte(ea.entmax_attn_lists_bytes(run.shape, p))
+    wsb = byte(ea.entmax_attn_bwd_lists_workspace(run.shape, p))
+    nlists = lists.numel() if run.n <= 65536 else 0
     shape, stream = run.shape, torch.cuda.current_stream().cuda_stream
     ptr = lambda t: t.data_ptr()
 
     def step():
-        ea._check(ea._lib.entmax_attn_fwd_dense(
+        ea._check(ea._lib.entmax_attn_fwd_dense_lists(
             ctypes.byref(shape), ctypes.byref(p), ptr(q), ptr(k), ptr(v), ptr(o), ptr(tau),
-            None, ptr(o2), ptr(ws), ws.numel(), stream), "entmax_attn_fwd_dense")
-        ea._check(ea._lib.entmax_attn_bwd_dense(
+            None, ptr(o2), ptr(lists) if nlists else None, nlists, ptr(ws), ws.numel(), stream),
+            "entmax_attn_fwd_dense_lists")
+        ea._check(ea._lib.entmax_attn_bwd_dense_lists(
             ctypes.byref(shape), ctypes.byref(p), ptr(q), ptr(k), ptr(v), ptr(do), ptr(tau),
-            None, ptr(o2), ptr(dq), ptr(dk), ptr(dv), ptr(wsb), wsb.numel() * 4, stream),
-            "entmax_attn_bwd_dense")
+            None, ptr(o2), ptr(lists) if nlists else None, nlists, ptr(dq), ptr(dk), ptr(dv), ptr(wsb),
+            wsb.numel(), stream), "entmax_attn_bwd_dense_lists")
 
     for _ in range(warmup):
         step()
@@ -607,6 +611,7 @@ def long_context(args, lengths, steps=3):
         w = r.work()
         z = r.res.sizes
         resid = z.tau + z.o2 + z.block_mask + z.q_count + z.q_index + z.k_count + z.k_index + z.stats
+        resid += r.res.lists.numel() if r.res.lists is not None else 0
         io = 4 * r.q.numel() * r.q.element_size() + 3 * r.q.numel() * 4  # Q K V dO O, dQ dK dV
         out.append({"seqlen": n, "ms": round(ms, 3),
                     "tflops_dense_equiv": round(w["dense_flops"] / (ms * 1e-3) / 1e12, 3),
@@ -615,7 +620,7 @@ def long_context(args, lengths, steps=3):
                     "solver_passes_mean": round(w["passes_mean"], 3),
                     "peak_device_mib": round(peak / 2**20, 1),
                     "library_residual_mib": round(resid / 2**20, 1),
-                    "library_workspace_mib": round((z.ws_fwd + z.ws_bwd) / 2**20, 1),
+                    "library_workspace_mib": round((r.ws_fwd.numel() + r.ws.numel()) / 2**20, 1),
                     "inputs_outputs_mib": round(io / 2**20, 1)})
         del r
     torch.cuda.empty_cache()

@@ -53,7 +53,9 @@ typedef struct {
   float alpha;      /* > 1; 2 = sparsemax, 1.5 = 1.5-entmax; finite */
   float scale;      /* > 0, finite; usually 1/sqrt(head_dim) */
   int32_t causal;   /* 0 or 1 */
-  int32_t max_iter; /* Halley-bisection updates after the initial midpoint (Algorithm 1's T), 0..64 */
+  int32_t max_iter; /* Halley-bisection updates (Algorithm 1's T) after the first evaluation, 0..64:
+                       at the bracket's midpoint, or for alpha <= 2 at its lower end where that
+                       is the better guess (the largest scores' own root) */
   float tol;        /* >= 0: the solver stops on a tile of query rows  (256, 128 or 64)
                        once every row has |f(tau)| <= tol */
   int32_t need_bwd; /* 1: also write o2 for a later entmax_attn_bwd */
@@ -130,7 +132,9 @@ ea_status entmax_attn_sizes(const ea_shape* shape, const ea_params* params, ea_s
  *            stored scores do not fit, it streams K, and collects once more
  *            if its first streamed evaluation counts few enough scores above
  *            the lower end).  Without a workspace (NULL, or too small for
- *            one slot) every tile streams K on every pass.  Results agree up
+ *            one slot) every tile streams K on every pass.  Short sequences
+ *            (n <= 512, or 1024 on small grids; fp32 with alpha 1.25, 1.5 or 2
+ *            only) need none: K is read once either way.  Results agree up
  *            to rounding either way.  Contents are scratch.
  * Launches 2 kernels on `stream` (the solver one more per S workgroups
  * beyond the first S).
@@ -236,7 +240,7 @@ ea_status entmax_attn_bwd_noalloc(const ea_shape* shape, const ea_params* params
 
 /*
  * No-mask ("memory-efficient") mode, Algorithm 2 as written (Sec. 3.2.1): the
- * forward solves tau and accumulates O (and, if need_bwd, o2), visiting every
+ * forward solves tau and then accumulates O (and, if need_bwd, o2) over every
  * valid key block; no block mask or tables exist, so memory beyond the inputs
  * and outputs is O(n) per head.
  *   tau  fp32 [BH, n] (written); o2 fp32 [BH, n, d] (written if need_bwd)

@@ -83,12 +83,11 @@ ea_status check_shape(const ea_shape* s, const ea_params* p, Dims* out) {
 // delta, one fp32 per row
 size_t bwd_ws_bytes(const Dims& d) { return (size_t)(d.BH * d.n) * 4; }
 
-// One cache slot per solver tile (256 rows on the masked path, 128 rows in
-// the no-mask fused forward), at most MAX_SOLVE_SLOTS of the masked path's
-// size: two co-resident workgroups per CU of a 256-CU MI355X.  With fewer
-// slots than tiles the solvers run one workgroup per slot, each solving
-// tiles in turn, so the workspace does not grow with B * H * n.  The masked
-// path's sizing covers both.
+// One cache slot per solver tile of 256 rows, at most MAX_SOLVE_SLOTS: two
+// co-resident workgroups per CU of a 256-CU MI355X.  With fewer slots than
+// tiles the solver runs in launches of one workgroup per slot, so the workspace
+// does not grow with B * H * n.  (Sequences that the solver for short ones takes
+// use none of it.)
 constexpr int64_t MAX_SOLVE_SLOTS = 512;
 int64_t solve_tiles(const Dims& d) { return d.BH * ((d.n + SOLVE_ROWS - 1) / SOLVE_ROWS); }
 int64_t solve_slots(const Dims& d) {

@@ -16,17 +16,12 @@
 // the mask describes exactly the probabilities that the forward and backward
 // kernels recompute from that tau.
 //
-// Two kernels.  solve_kernel is the masked path's solver (tau, the block
-// mask and stats; its layout is described where it is defined).
-// tau_solve_kernel is the no-mask forward: the same solver followed, in the
-// same workgroup, by the O (and O2) pass of Algorithm 2.  Its layout on
-// gfx950: one workgroup = 4 waves = 128 query rows; each wave keeps its 32
-// query rows as MFMA B operands in registers and computes S^T tiles (keys x
-// queries), so every lane owns one query and the per-row sums stay in-lane
-// until the end of a pass.  In both, K tiles of 64 keys are copied into a
-// double-buffered LDS tile by global_load_lds, the next one in flight while
-// the current one is consumed, and a workgroup stops as soon as every row it
-// owns has |f(tau)| <= tol, or after max_iter updates.
+// solve_kernel serves both modes (the no-mask mode takes tau and the element
+// lists, but no mask and no tables); sequences of up to 1024 keys may go to the
+// solver of ea_small.hip instead (see small_solver below).  K tiles of 64 keys
+// are copied into a double-buffered LDS tile by global_load_lds, the next one
+// in flight while the current one is consumed, and a workgroup stops as soon as
+// every row it owns has |f(tau)| <= tol, or after max_iter updates.
 #include <type_traits>
 
 #include "ea_common.h"
@@ -36,16 +31,14 @@ namespace ea {
 
 namespace {
 
-// ----------------------------------------------------------- masked solver
+// ------------------------------------------------------------------ solver
 //
-// The solver of the masked path (tau, the block mask and stats).  One
-// workgroup = 4 waves = 256 query rows; wave w owns the 64-row query block
+// One workgroup = 4 waves = 256 query rows; wave w owns the 64-row query block
 // qb = 4 qt + w, i.e. one row of the block mask, as two groups of 32 rows
 // (g = 0, 1) that are the B operands of its MFMAs.  Every K fragment read
 // from LDS feeds two MFMAs (one per group), so a pass reads the K tile from
 // LDS half as often per product as with one group per wave; lane l holds
-// query l % 32 of each group, so every lane keeps two rows' sums.  The
-// evaluation, bracket and cache rules are those of tau_solve_kernel.
+// query l % 32 of each group, so every lane keeps two rows' sums.
 constexpr int SV_WAVES = SOLVE_THREADS / 64;
 constexpr int SV_NT = SOLVE_THREADS;
 constexpr int SV_ROWS = SOLVE_ROWS;
@@ -242,9 +235,9 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
     return true;
   };
 
-  // ---- pass 0: row maxima and the top-eight bound of each row (see
-  // tau_solve_kernel): each lane keeps, per group, the four largest maxima of
-  // its 16-score sub-tile columns.
+  // ---- pass 0: row maxima and the top-eight bound of each row (x_bound
+  // below): each lane keeps, per group, the four largest maxima of its 16-score
+  // sub-tile columns, so that a row's two lanes hold eight distinct keys' scores.
   //
   // With a cache slot, the same pass collects the candidate lists: every
   // score above the running value of the bound.  Sub-tile maxima only grow,
@@ -1026,9 +1019,11 @@ __global__ __launch_bounds__(SV_NT, G == 1 ? SV_OCC1 : (sizeof(E) == 4 && D == 1
 #pragma unroll
     for (int gq = 0; gq < G; ++gq) {
       if (!row_ok[gq]) continue;
-      // the update rules of tau_solve_kernel: B_f (Eq. 4), the Newton lower
-      // bound for convex f, H_f (Eq. 5) with the bracket test and slack, and
-      // for gamma < 1 the midpoint when |f| has not halved
+      // The update rules: B_f (Eq. 4); for gamma >= 1, where f is convex, the
+      // Newton step from tau bounds the root from below (less a slack for the
+      // rounding of f); H_f (Eq. 5) where it lands inside the bracket, widened
+      // by the slack of its fp32 ends, and for gamma < 1 only if |f| has halved
+      // since the last step; otherwise the midpoint.
       if (f[gq] < 0.f)
         hi[gq] = tau[gq];
       else
@@ -1327,7 +1322,7 @@ hipError_t launch_solve_d(const TauArgs& a, hipStream_t s) {
 
 // Every part of this file is compiled on its own (EA_TAU_PART, see build.py),
 // since its instantiations take minutes to compile one after another: the
-// solver for each input type and head dimension, and the no-mask forward.
+// solver for each input type and head dimension, and the choice of the solver.
 #if EA_TAU_PART == 0
 hipError_t launch_tau_bf16_64(const TauArgs& a, hipStream_t s) { return launch_solve_d<__bf16, 64>(a, s); }
 #elif EA_TAU_PART == 1

@@ -1,7 +1,8 @@
-"""GPU parity of the no-mask ("memory-efficient") mode: the fused forward
-(tau and O, O2 in one kernel, no block mask or tables) and the backward that
-visits every valid block, against the fp64 oracle and against the masked
-path on the same inputs."""
+"""GPU parity of the no-mask ("memory-efficient") mode: the forward (tau, then
+O and O2 over every valid key block, no block mask or tables) and the backward
+that visits every valid block or, where a sample finds few nonzero
+probabilities, their lists, against the fp64 oracle and against the masked path
+on the same inputs."""
 import numpy as np
 import pytest
 
@@ -83,7 +84,7 @@ def test_dense_matches_masked_path():
 @pytest.mark.parametrize("d", [64, 128])
 def test_dense_f32_general_alpha(n, causal, d):
     """fp32 inputs at alpha in (1.5, 2), where u = z^(gamma-1) is steep near
-    the support edge: the fused forward refines tau in fp64 (tau + tau_lo) and
+    the support edge: the forward refines tau in fp64 (tau + tau_lo) and
     takes x - tau in fp64 near the edge, and the backward reads tau_lo."""
     B, H = 1, 2
     for alpha in (1.6, 1.7, 1.75):
