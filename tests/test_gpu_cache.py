@@ -196,12 +196,12 @@ def test_cache_wide_rows_among_narrow(alpha, wide):
 
 
 def test_cache_refined_bound():
-    """alpha 1.5, c = 1 at n = 8192, d = 128: the lists of a few rows fill up in
+    """alpha 1.5, c = 0.9 at n = 8192, d = 128: the lists of a few rows fill up in
     the last quarter of the key blocks, and the bound they are collected with is
     then refined from the lists themselves, so that all tiles finish on their
-    lists (without it the longest take 3 K passes); the dropped scores all lie
+    lists (without it 6% of them take 3 K passes); the dropped scores all lie
     below the returned tau, which is streaming's."""
-    inp = synth.attention_inputs(1, 16, 8192, 128, c=1.0, dtype="bf16", seed=synth.SEED_BASE)
+    inp = synth.attention_inputs(1, 16, 8192, 128, c=0.9, dtype="bf16", seed=7)
     (o0, r0), (o1, r1) = _both(inp, 1.5, False)
     dt = ((r1.tau.double() - r0.tau.double()).abs() / r0.tau.double().abs().clamp(min=1.0)).max().item()
     log("refined: dtau %.2e, K passes max %d" % (dt, r1.stats[0].max().item()))
