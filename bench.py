@@ -37,9 +37,11 @@ PEAK_BF16_TFLOPS = 2500.0
 KERNELS = ("tau_solve", "fwd_sparse", "bwd_delta", "bwd_dkdv", "bwd_dq")
 # MFMA block products (64 x 64 x d each) per listed block, by kernel
 PRODUCTS_PER_ACTIVE = {"fwd_sparse": 3, "bwd_dkdv": 4, "bwd_dq": 3}
-# kernel name fragment in profiler output, and the sources that define each kernel
-PROFILE_NAMES = {"tau_solve": "solve_kernel", "fwd_sparse": "fwd_kernel",
-                 "bwd_dkdv": "dkdv2_kernel", "bwd_dq": "dq_kernel"}
+# kernel name fragments in profiler output, and the sources that define each
+# kernel; a stage's summary is of the first kernel that ran (where dK/dV of the
+# listed blocks are summed in their own kernel, it has nearly all of the work)
+PROFILE_NAMES = {"tau_solve": ("solve_kernel",), "fwd_sparse": ("fwd_kernel",),
+                 "bwd_dkdv": ("dkdv_lists_kernel", "dkdv2_kernel"), "bwd_dq": ("dq_kernel",)}
 KERNEL_SOURCES = {"tau_solve": ["ea_tau.hip"], "fwd_sparse": ["ea_fwd.hip"],
                   "bwd_dkdv": ["ea_bwd.hip"], "bwd_dq": ["ea_bwd.hip"]}
 COMMON_SOURCES = ["ea_common.h", "ea_internal.h", "../build.py"]
@@ -106,8 +108,8 @@ def write_mfma(pmc_csv, command, head_dim=128):
     vals = collections.defaultdict(lambda: collections.defaultdict(list))
     for row in csv.DictReader(open(pmc_csv)):
         vals[row["Kernel_Name"]][row["Counter_Name"]].append(float(row["Counter_Value"]))
-    for kernel, frag in PROFILE_NAMES.items():
-        names = [k for k in vals if frag in k and headline_instance(k, head_dim)]
+    for kernel in PROFILE_NAMES:
+        frag, names = profiled_kernel(kernel, vals, head_dim)
         if not names:
             continue
         util = [v for k in names for v in vals[k]["MfmaUtil"]]
@@ -153,8 +155,9 @@ def write_kernel_stats(stats_csv, bench_json, out_md, command):
             fh.write("| `%s` | %s | %.1f | %.2f |\n" % (short, r["Calls"],
                                                      float(r["AverageNs"]) / 1e3,
                                                      float(r["Percentage"])))
-            for kernel, frag in PROFILE_NAMES.items():
-                if frag in name and headline_instance(name, line["config"]["head_dim"]):
+            for kernel in PROFILE_NAMES:
+                if name in profiled_kernel(kernel, [q["Name"] for q in rows],
+                                           line["config"]["head_dim"])[1]:
                     avg[kernel] = float(r["AverageNs"]) / 1e6
         fh.write("\nSame kernels, HIP-event times of the unprofiled run (`python bench.py` with "
                  "the arguments above, no profiler attached), and the fraction of the 2.5 PFLOP/s "
@@ -186,6 +189,16 @@ def headline_instance(name, head_dim):
     return ("<%d," % head_dim) in name or ("__bf16, %d," % head_dim) in name
 
 
+def profiled_kernel(kernel, names, head_dim):
+    """(name fragment, the bf16 instantiations for head_dim among `names`) of the
+    kernel that a stage's summary describes."""
+    for frag in PROFILE_NAMES[kernel]:
+        found = [k for k in names if frag in k and headline_instance(k, head_dim)]
+        if found:
+            return frag, found
+    return PROFILE_NAMES[kernel][0], []
+
+
 def write_traffic(fetch_csv, write_csv, calib_mib, command, head_dim=128):
     """Scale each kernel's FETCH_SIZE and WRITE_SIZE (KiB per dispatch) by what
     the same counter reads for the plain copy of `calib_mib` MiB, and write
@@ -211,8 +224,8 @@ def write_traffic(fetch_csv, write_csv, calib_mib, command, head_dim=128):
     cname = max(copy_name, key=lambda k: max(fetch[k]))
     f_scale = calib_kib / max(fetch[cname])
     w_scale = calib_kib / max(write[cname])
-    for kernel, frag in PROFILE_NAMES.items():
-        names = [k for k in fetch if frag in k and headline_instance(k, head_dim)]
+    for kernel in PROFILE_NAMES:
+        frag, names = profiled_kernel(kernel, fetch, head_dim)
         if not names:
             continue
         fk = [v for k in names for v in fetch[k]]
